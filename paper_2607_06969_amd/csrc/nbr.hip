@@ -19,6 +19,8 @@
 // rc_radial and within rc_angular, which all later kernels iterate.
 #include "nbr.hpp"
 
+#include <algorithm>
+
 namespace nepmi {
 
 // ------------------------------------------------------------------ staging
@@ -35,13 +37,10 @@ __device__ __forceinline__ int bin_key(const CfgDev& C, int b0, int b1, int b2) 
   return C.bin_off + (t << 6) + (((b0 & 3) << 4) | ((b1 & 3) << 2) | (b2 & 3));
 }
 
-// Bin coordinates packed into one int (each below 1024).
-__device__ __forceinline__ int pack_bin(int b0, int b1, int b2) { return b0 | (b1 << 10) | (b2 << 20); }
-
 __global__ void k_stage(int64_t N, int n_cfg, const int64_t* __restrict__ atom_off, const CfgDev* __restrict__ cfgs,
                         const float* __restrict__ pos, int pos_stride, const int32_t* __restrict__ species,
                         int n_species, int total_bins, float4* __restrict__ pos_tmp, int* __restrict__ cfg_tmp,
-                        int* __restrict__ crd_tmp, int* __restrict__ key, int* __restrict__ cnt, int* __restrict__ flags,
+                        int* __restrict__ key, int* __restrict__ cnt, int* __restrict__ flags,
                         const int* __restrict__ gate) {
   if (gate && *gate == 0) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -87,7 +86,6 @@ __global__ void k_stage(int64_t N, int n_cfg, const int64_t* __restrict__ atom_o
   key[i] = k;
   pos_tmp[i] = make_float4(o[0], o[1], o[2], __int_as_float(z));
   cfg_tmp[i] = lo;
-  crd_tmp[i] = pack_bin(b[0], b[1], b[2]);
   atomicAdd(&cnt[k], 1);
 }
 
@@ -227,17 +225,17 @@ __global__ void k_sort_keys(int M, const int* __restrict__ start, const int* __r
   }
 }
 
-// Fill the slot arrays.  Padding slots get orig = -1 and their group's species.
+// Fill the slot arrays.  Padding slots get orig = -1, their group's species and
+// empty lists.
 // With carry.xd set, the carried state moves into the slot as well: the
 // staging wraps again only in a last-ulp case at a cell face, and that shift
 // (zero otherwise) is carried into the float64 position.
 __global__ void k_fill_slots(int64_t n_slots, const int* __restrict__ base, const int* __restrict__ start,
                              int total_bins, int n_species, const int* __restrict__ perm,
                              const float4* __restrict__ pos_tmp, const int* __restrict__ cfg_tmp,
-                             const int* __restrict__ crd_tmp,
-                             const int* __restrict__ key, float4* __restrict__ pos4, int* __restrict__ cfg_of,
-                             int* __restrict__ orig, int* __restrict__ bin_of, int* __restrict__ slot_of,
-                             SlotCarry carry, const int* __restrict__ gate) {
+                             float4* __restrict__ pos4, int* __restrict__ cfg_of,
+                             int* __restrict__ orig, int* __restrict__ slot_of, int* __restrict__ cntR,
+                             int* __restrict__ cntAV, SlotCarry carry, const int* __restrict__ gate) {
   if (gate && *gate == 0) return;
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n_slots) return;
@@ -253,7 +251,6 @@ __global__ void k_fill_slots(int64_t n_slots, const int* __restrict__ base, cons
       pos4[p] = xs;
       cfg_of[p] = cfg_tmp[i];
       orig[p] = i;
-      bin_of[p] = crd_tmp[i];  // packed bin coordinates
       if (slot_of) slot_of[i] = (int)p;
       if (carry.xd) {
         const float4 xu = carry.x_user[i];
@@ -274,153 +271,361 @@ __global__ void k_fill_slots(int64_t n_slots, const int* __restrict__ base, cons
   pos4[p] = make_float4(0.f, 0.f, 0.f, __int_as_float(z));
   cfg_of[p] = -1;
   orig[p] = -1;
-  bin_of[p] = -1;
+  cntR[p] = 0;  // the list build visits atoms only
+  cntAV[p] = 0;
 }
 
 // --------------------------------------------------------- Verlet lists
 
-// For every active slot, scan the 27 stencil bins (with periodic images) and
-// keep neighbours within the radial and angular list cutoffs.  Along a
+// Compacted position of this lane in a ballot: set bits below the lane.
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Order between one wavefront's LDS writes and its other lanes' reads.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Smallest and largest value over the wavefront (DPP butterfly towards lane 63;
+// lanes without a source keep their own value, which changes neither).
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+  const int i = __float_as_int(v);
+  return __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane63(float v) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ float wave_min(float v) {
+  v = fminf(v, dpp_move<0x111>(v));  // row_shr 1, 2, 4, 8
+  v = fminf(v, dpp_move<0x112>(v));
+  v = fminf(v, dpp_move<0x114>(v));
+  v = fminf(v, dpp_move<0x118>(v));
+  v = fminf(v, dpp_move<0x142>(v));  // row_bcast 15, 31
+  v = fminf(v, dpp_move<0x143>(v));
+  return lane63(v);
+}
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, dpp_move<0x111>(v));
+  v = fmaxf(v, dpp_move<0x112>(v));
+  v = fmaxf(v, dpp_move<0x114>(v));
+  v = fmaxf(v, dpp_move<0x118>(v));
+  v = fmaxf(v, dpp_move<0x142>(v));
+  v = fmaxf(v, dpp_move<0x143>(v));
+  return lane63(v);
+}
+
+// Verlet lists, one home bin per wavefront: the atoms of a bin share their
+// candidates (the atoms of the 27 stencil bins with their periodic images).
+// The wavefront collects those once, in list order, drops the ones beyond the
+// list cutoff from the box of the bin's atoms, and then takes the atoms in
+// turn, 64 candidates per round, one per lane.  Kept entries are compacted by
+// ballot into a stage in LDS and leave it together.
+//
+// The list comes out in slot order: slots are ordered by (species, bin key),
+// so the stencil bins are visited per species in ascending bin key.
+// Neighbouring atoms then tend to have their k-th neighbours in the same
+// cache lines.  Each bin is packed with its image code (bin key << 5 | code:
+// unique, so the order is total; bin keys are below 2^27).  Along a
 // non-periodic direction a stencil bin beyond the cell has no atoms (no
 // images): it is skipped.
-__global__ __launch_bounds__(256) void k_build_lists(int64_t n_slots, int n_species, int total_bins,
-                                                     const CfgDev* __restrict__ cfgs,
-                                                     const float4* __restrict__ pos4, const int* __restrict__ cfg_of,
-                                                     const int* __restrict__ bin_of, const int* __restrict__ start,
-                                                     const int* __restrict__ base, float rclR2, float rclA2, int capR,
-                                                     int capA, int rowTA, uint32_t* __restrict__ nbrR,
-                                                     uint32_t* __restrict__ nbrTA, uint32_t* __restrict__ angm,
-                                                     int* __restrict__ cntR, int* __restrict__ cntAV,
-                                                     int* __restrict__ flags, const int* __restrict__ gate) {
+//
+// The entries within rc_angular + skin (the angular part of the list, which
+// the reverse index searches) are also kept in their own row-major list, and
+// marked in a bit mask over the list (bit k % 32 of word k / 32: entry k is in
+// that part).
+//
+// Grid (bins, parts): part y of a bin takes its atoms y, y + parts, ...; a
+// batch of few bins takes several parts, so that a wavefront has a few atoms
+// whatever the bin holds (see launch_lists).
+//
+// What bounds it: with one atom per thread and a scan of the 27 bins each, the
+// bins of a wavefront's lanes differ in occupancy (45 % of the lanes in use),
+// every candidate is a gather of its own, and a small batch leaves all but a
+// few SIMDs idle.  Sharing a bin's candidates removes the gathers and fills the
+// lanes; what remains is issue: about 520 VALU instructions to set a bin up and
+// 97 per atom.  One thread per atom -> one bin per wavefront (us): 900,000
+// atoms 610 -> 346, 64 cells of 64..512 atoms 189 -> 35, 3,686 atoms 160 -> 20,
+// 64 atoms 77 -> 9.
+constexpr int kListSpecies = 4;                 // species the range tables hold
+constexpr int kListRanges = 27 * kListSpecies;  // (species, stencil bin) slot ranges
+constexpr int kListCandMin = 512, kListCandMax = 2048;  // candidates listed in LDS (CAND); longer lists are searched
+constexpr int kListRegs = 3;                    // rounds of candidates held in registers
+constexpr int kListWaves = 1024;                // wavefronts a small batch is split into
+constexpr unsigned kListGated = 16384;          // most blocks of a gated launch
+template <int CAND>
+__global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_species, int total_bins,
+                                                       const CfgDev* __restrict__ cfgs,
+                                                       const float4* __restrict__ pos4, const int* __restrict__ cfg_of,
+                                                       const int* __restrict__ start, const int* __restrict__ base,
+                                                       float rclR2, float rclA2, int capR, int capA, int rowTA,
+                                                       uint32_t* __restrict__ nbrR, uint32_t* __restrict__ nbrTA,
+                                                       uint32_t* __restrict__ angm, int* __restrict__ cntR,
+                                                       int* __restrict__ cntAV, int* __restrict__ flags,
+                                                       const int* __restrict__ gate) {
   if (gate && *gate == 0) return;
-  const int64_t p = xcd_tile() * blockDim.x + threadIdx.x;
-  if (p >= n_slots) return;
-  const int c = cfg_of[p];
-  if (c < 0) {
-    cntR[p] = 0;
-    cntAV[p] = 0;
-    return;
-  }
-  const CfgDev& C = cfgs[c];
-  const float4 xi = pos4[p];
-  const int pb = bin_of[p];
-  const int b0 = pb & 1023, b1 = (pb >> 10) & 1023, b2 = pb >> 20;
-  // The 27 stencil bins in ascending bin key, visited per species: slots are
-  // ordered by (species, bin key), so the list comes out in slot order.
-  // Neighbouring atoms then tend to have their k-th neighbours in the same
-  // cache lines, and a wavefront's gather of the k-th neighbours touches fewer
-  // lines than with the stencil order.  Each bin is packed with its image code
-  // (bin key << 5 | code: unique, so the order is total; bin keys are below
-  // 2^27) and sorted by a compare-exchange network with fixed indices, which
-  // stays in registers; the sorted bins wait in this thread's LDS column.
-  // Skipped bins are kNoBin, which sorts last.
   constexpr uint32_t kNoBin = 0xFFFFFFFFu;
-  __shared__ uint32_t sorted_bins[27 * 256];
-  uint32_t sb[27];
-  const int per = C.periodic;
-#pragma unroll
-  for (int o = 0; o < 27; ++o) {
-    int t0 = b0 + o / 9 - 1, t1 = b1 + (o / 3) % 3 - 1, t2 = b2 + o % 3 - 1;
-    const int w0 = t0 < 0 ? -1 : (t0 >= C.nb[0] ? 1 : 0);
-    const int w1 = t1 < 0 ? -1 : (t1 >= C.nb[1] ? 1 : 0);
-    const int w2 = t2 < 0 ? -1 : (t2 >= C.nb[2] ? 1 : 0);
-    const bool skip = (w0 && !(per & 1)) || (w1 && !(per & 2)) || (w2 && !(per & 4));
-    t0 -= w0 * C.nb[0];
-    t1 -= w1 * C.nb[1];
-    t2 -= w2 * C.nb[2];
-    const uint32_t code = (uint32_t)((w0 + 1) * 9 + (w1 + 1) * 3 + (w2 + 1));
-    sb[o] = skip ? kNoBin : (((uint32_t)bin_key(C, t0, t1, t2) << 5) | code);
-  }
-#pragma unroll
-  for (int i = 1; i < 27; ++i)
-#pragma unroll
-    for (int j = i; j > 0; --j) {
-      const uint32_t lo = sb[j - 1] < sb[j] ? sb[j - 1] : sb[j];
-      const uint32_t hi = sb[j - 1] < sb[j] ? sb[j] : sb[j - 1];
-      sb[j - 1] = lo;
-      sb[j] = hi;
-    }
-#pragma unroll
-  for (int o = 0; o < 27; ++o) sorted_bins[o * 256 + threadIdx.x] = sb[o];
-  // Entries are collected four at a time and stored as one group: one store
-  // per four entries instead of one per entry.  The entries within
-  // rc_angular + skin (the angular part of the list, which the reverse index
-  // searches) are also kept in their own row-major list, and marked in a bit
-  // mask over the list (bit k % 32 of word k / 32: entry k is in that part).
-  // Entries and mask bits shift in from the top, so a full group or word
-  // holds them in list order; the store pointers advance one column at a time.
+  __shared__ uint32_t bin_s[27];
+  __shared__ float4 shift_s[27];
+  __shared__ int pre_s[kListRanges + 1];
+  __shared__ uint32_t first_s[kListRanges];
+  __shared__ uint32_t cand_s[CAND];
+  __shared__ uint2 st[2 * kWave];  // kept entries waiting for a full round: (entry, |r|^2)
+  const int lane = threadIdx.x;
+  const int nr = 27 * n_species;
   const int capG = 4 * list_groups(capR);   // entries the groups can hold
   const int capGA = 4 * list_groups(capA);
-  uint4 grp = make_uint4(0u, 0u, 0u, 0u), gra = grp;
-  uint32_t mword = 0;
-  uint4* colG = reinterpret_cast<uint4*>(nbrR) + p;         // next group, column-major
-  uint4* rowA = reinterpret_cast<uint4*>(nbrTA + p * rowTA);  // angular part, row-major
-  uint32_t* colM = angm + p;                                // next mask word, column-major
-  int kR = 0, kA = 0;
-  for (int z = 0; z < n_species; ++z) {
-    for (int o = 0; o < 27; ++o) {
-      const uint32_t sbo = sorted_bins[o * 256 + threadIdx.x];
-      if (sbo == kNoBin) break;
-      const int tb = (int)(sbo >> 5);
-      const uint32_t code = sbo & 31u;
+  const int64_t group_off = group_index(n_slots, 0, lane);
+  int zoff[kListSpecies];  // slot of key k of species z: zoff[z] + start[k]
+#pragma unroll
+  for (int z = 0; z < kListSpecies; ++z) zoff[z] = z < n_species ? base[z] - start[z * total_bins] : 0;
+  int maxR = 0, maxA = 0;
+  // every XCD takes one contiguous range of bins (see xcd_tile)
+  const int per = (total_bins + (int)kXcds - 1) / (int)kXcds;
+  const int b_lo = (int)(blockIdx.x % kXcds) * per;
+  const int b_hi = b_lo + per < total_bins ? b_lo + per : total_bins;
+  for (int hb = b_lo + (int)(blockIdx.x / kXcds); hb < b_hi; hb += (int)(gridDim.x / kXcds)) {
+    // the bin's atoms: slots hq[z] .. hq[z] + hn[z] - 1 (most padding bins are empty)
+    int hq[kListSpecies], hn[kListSpecies], nh = 0;
+#pragma unroll
+    for (int z = 0; z < kListSpecies; ++z) {
+      hq[z] = hn[z] = 0;
+      if (z < n_species) {
+        const int k = z * total_bins + hb;
+        hq[z] = zoff[z] + start[k];
+        hn[z] = start[k + 1] - start[k];
+      }
+      nh += hn[z];
+    }
+    if (nh <= (int)blockIdx.y) continue;
+    // slot of home atom h (clamped to the last)
+    auto home = [&](int h) {
+      h = h < nh ? h : nh - 1;
+      int p = 0, acc = 0;
+#pragma unroll
+      for (int z = 0; z < kListSpecies; ++z) {
+        if (h >= acc && h < acc + hn[z]) p = hq[z] + h - acc;
+        acc += hn[z];
+      }
+      return p;
+    };
+    int hp = home(lane);  // one home atom per lane
+    float4 hx = pos4[hp];
+    float lox = hx.x, loy = hx.y, loz = hx.z, hix = hx.x, hiy = hx.y, hiz = hx.z;
+    for (int h0 = kWave; h0 < nh; h0 += kWave) {
+      const float4 x = pos4[home(h0 + lane)];
+      lox = fminf(lox, x.x);
+      loy = fminf(loy, x.y);
+      loz = fminf(loz, x.z);
+      hix = fmaxf(hix, x.x);
+      hiy = fmaxf(hiy, x.y);
+      hiz = fmaxf(hiz, x.z);
+    }
+    const CfgDev& C = cfgs[cfg_of[__builtin_amdgcn_readfirstlane(hp)]];
+    __syncthreads();  // the previous bin's tables are no longer read
+    uint32_t v = kNoBin;
+    if (lane < 27) {
+      const int rel = hb - C.bin_off, tl = rel >> 6;
+      const int nt1 = (C.nb[1] + 3) >> 2, nt2 = (C.nb[2] + 3) >> 2;
+      const int h0 = ((tl / (nt1 * nt2)) << 2) | ((rel >> 4) & 3), h1 = (((tl / nt2) % nt1) << 2) | ((rel >> 2) & 3),
+                h2 = ((tl % nt2) << 2) | (rel & 3);
+      int t0 = h0 + lane / 9 - 1, t1 = h1 + (lane / 3) % 3 - 1, t2 = h2 + lane % 3 - 1;
+      const int w0 = t0 < 0 ? -1 : (t0 >= C.nb[0] ? 1 : 0);
+      const int w1 = t1 < 0 ? -1 : (t1 >= C.nb[1] ? 1 : 0);
+      const int w2 = t2 < 0 ? -1 : (t2 >= C.nb[2] ? 1 : 0);
+      const bool skip = (w0 && !(C.periodic & 1)) || (w1 && !(C.periodic & 2)) || (w2 && !(C.periodic & 4));
+      t0 -= w0 * C.nb[0];
+      t1 -= w1 * C.nb[1];
+      t2 -= w2 * C.nb[2];
+      const uint32_t code = (uint32_t)((w0 + 1) * 9 + (w1 + 1) * 3 + (w2 + 1));
+      if (!skip) v = ((uint32_t)bin_key(C, t0, t1, t2) << 5) | code;
       float sx, sy, sz;
-      image_shift(C.H, code, sx, sy, sz);
-      const int k = z * total_bins + tb;
-      const int q0 = base[z] + start[k] - start[z * total_bins];
-      const int q1 = q0 + start[k + 1] - start[k];
-      // four candidates per round, loaded together (indices clamped into the
-      // bin's range, so every load is in bounds; the extra ones are skipped)
-      for (int q4 = q0; q4 < q1; q4 += 4) {
-        float4 xs[4];
+      image_shift(C.H, (uint32_t)lane, sx, sy, sz);
+      shift_s[lane] = make_float4(sx, sy, sz, 0.f);
+    }
+    // rank of every bin among the 27; skipped ones at the end
+    const uint64_t none = __ballot(lane < 27 && v == kNoBin);
+    int rank = 0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) xs[u] = pos4[q4 + u < q1 ? q4 + u : q1 - 1];
+    for (int o = 0; o < 27; ++o) rank += (uint32_t)__builtin_amdgcn_readlane(v, o) < v ? 1 : 0;
+    if (v == kNoBin) rank += lanes_below(none);
+    if (lane < 27) bin_s[rank] = v;
+    wave_fence();
+    // the slot ranges in list order and the running number of candidates
+    int total = 0;
+    for (int r0 = 0; r0 < nr; r0 += kWave) {
+      const int r = r0 + lane;
+      int n = 0;
+      uint32_t first = 0;
+      if (r < nr) {
+        const int z = r / 27;
+        const uint32_t b = bin_s[r - 27 * z];
+        if (b != kNoBin) {
+          const int k = z * total_bins + (int)(b >> 5);
+          const int s = start[k];
+          n = start[k + 1] - s;
+          int zo = zoff[0];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int q = q4 + u;
-          if (q >= q1 || (q == (int)p && code == 13u)) continue;
-          const float rx = (xs[u].x - xi.x) + sx, ry = (xs[u].y - xi.y) + sy, rz = (xs[u].z - xi.z) + sz;
-          const float d2 = pair_d2(rx, ry, rz);
-          if (d2 < rclR2) {
-            // entries shift into a group from the top (four register moves,
-            // no selects); a full group holds them in list order
-            const uint32_t e = (uint32_t)q | (code << kNbrShift);
-            grp = make_uint4(grp.y, grp.z, grp.w, e);
-            mword = (mword >> 1) | (d2 < rclA2 ? 0x80000000u : 0u);
-            ++kR;
-            if ((kR & 3) == 0 && kR <= capG) {
-              *colG = grp;
-              colG += n_slots;
-            }
-            if ((kR & 31) == 0 && kR <= capG) {
-              *colM = mword;
-              colM += n_slots;
-            }
-            if (d2 < rclA2) {
-              gra = make_uint4(gra.y, gra.z, gra.w, e);
-              ++kA;
-              if ((kA & 3) == 0 && kA <= capGA) rowA[(kA >> 2) - 1] = gra;
-            }
-          }
+          for (int u = 1; u < kListSpecies; ++u) zo = z == u ? zoff[u] : zo;
+          first = (uint32_t)(zo + s) | ((b & 31u) << kNbrShift);
         }
       }
+      int s = n;
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int u = __shfl_up(s, o, kWave);
+        if (lane >= o) s += u;
+      }
+      const int c0 = total + s - n;  // first candidate of this range
+      if (r < nr) {
+        pre_s[r] = c0;
+        first_s[r] = first;
+      }
+      for (int j = 0; j < n && c0 + j < CAND; ++j) cand_s[c0 + j] = first + (uint32_t)j;
+      total += __builtin_amdgcn_readlane(s, kWave - 1);
+    }
+    if (lane == 0) pre_s[nr] = total;
+    wave_fence();
+    const bool listed = total <= CAND;
+    if (listed) {
+      // drop the candidates farther than the list cutoff from the box of the
+      // home atoms (with a margin far above the rounding), keeping the order
+      lox = wave_min(lox);
+      loy = wave_min(loy);
+      loz = wave_min(loz);
+      hix = wave_max(hix);
+      hiy = wave_max(hiy);
+      hiz = wave_max(hiz);
+      const float far2 = rclR2 * 1.001f + 1e-3f;
+      int out = 0;
+      for (int c0 = 0; c0 < total; c0 += kWave) {
+        const int c = c0 + lane;
+        const uint32_t e = cand_s[c < total ? c : total - 1];
+        const float4 x = pos4[e & kNbrMask];
+        const float4 s = shift_s[e >> kNbrShift];
+        const float px = x.x + s.x, py = x.y + s.y, pz = x.z + s.z;
+        // distance to the box (the point minus its nearest point in it)
+        const float dx = px - __builtin_amdgcn_fmed3f(px, lox, hix);
+        const float dy = py - __builtin_amdgcn_fmed3f(py, loy, hiy);
+        const float dz = pz - __builtin_amdgcn_fmed3f(pz, loz, hiz);
+        const bool keep = c < total && pair_d2(dx, dy, dz) < far2;
+        const uint64_t m = __ballot(keep);
+        wave_fence();
+        if (keep) cand_s[out + lanes_below(m)] = e;
+        out += __builtin_popcountll(m);
+        wave_fence();
+      }
+      total = out;
+    }
+    // entry of candidate c (slot | image code)
+    auto cand = [&](int c) -> uint32_t {
+      if (listed) return cand_s[c];
+      int lo = 0, hi = nr;  // last range with pre_s[lo] <= c
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (pre_s[mid] <= c) lo = mid; else hi = mid;
+      }
+      return first_s[lo] + (uint32_t)(c - pre_s[lo]);
+    };
+    // the first rounds of candidates, held through all atoms of the bin (a
+    // lane without one holds a point that no distance test accepts)
+    uint32_t ce[kListRegs];
+    float4 cx[kListRegs], cs[kListRegs];
+#pragma unroll
+    for (int u = 0; u < kListRegs; ++u) {
+      const int c = kWave * u + lane;
+      ce[u] = cand(c < total ? c : total - 1);
+      cx[u] = pos4[ce[u] & kNbrMask];
+      cs[u] = shift_s[ce[u] >> kNbrShift];
+      if (c >= total) cx[u].x = __builtin_inff();
+    }
+    for (int h = (int)blockIdx.y; h < nh; h += (int)gridDim.y) {
+      if (nh > kWave && (h & (kWave - 1)) < (int)gridDim.y) {  // the next 64 home atoms
+        hp = home((h & ~(kWave - 1)) + lane);
+        hx = pos4[hp];
+      }
+      const int hl = h & (kWave - 1);
+      const int64_t p = __builtin_amdgcn_readlane(hp, hl);
+      const float xi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(hx.x), hl));
+      const float yi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(hx.y), hl));
+      const float zi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(hx.z), hl));
+      const uint32_t self = (uint32_t)p | (13u << kNbrShift);
+      int kR = 0, kA = 0, ns = 0;  // entries out, angular entries out, entries staged
+      uint32_t last_a = 0;
+      // the first n staged entries leave as groups and mask words (kR is a
+      // multiple of 64 before every call)
+      auto emit = [&](int n) {
+        wave_fence();
+        const uint2 w = st[lane < n ? lane : n - 1];
+        const bool ang = lane < n && __uint_as_float(w.y) < rclA2;
+        // the last group repeats the last entry
+        uint32_t* col = nbrR + 4 * ((int64_t)(kR >> 2) * n_slots + p);
+        if (lane < ((n + 3) & ~3) && kR + lane < capG) col[group_off] = w.x;
+        const uint64_t am = __ballot(ang);
+        if (lane < 2 && 32 * lane < n && kR + 32 * lane < capG)
+          angm[(int64_t)((kR >> 5) + lane) * n_slots + p] = (uint32_t)(am >> (32 * lane));
+        const int ka = kA + lanes_below(am);
+        if (ang && ka < capGA) (nbrTA + p * rowTA)[ka] = w.x;
+        if (am) last_a = __builtin_amdgcn_readlane(w.x, 63 - __builtin_clzll(am));
+        kA += __builtin_popcountll(am);
+        kR += n;
+      };
+      auto round = [&](uint32_t e, const float4& x, const float4& s) {
+        const float rx = (x.x - xi) + s.x, ry = (x.y - yi) + s.y, rz = (x.z - zi) + s.z;
+        const float d2 = pair_d2(rx, ry, rz);
+        const bool in = d2 < rclR2 && e != self;
+        const uint64_t m = __ballot(in);
+        if (in) st[ns + lanes_below(m)] = make_uint2(e, __float_as_uint(d2));
+        ns += __builtin_popcountll(m);
+      };
+      auto flush = [&] {
+        if (ns < kWave) return;
+        emit(kWave);
+        const uint2 w = st[kWave + lane];
+        wave_fence();
+        st[lane] = w;
+        ns -= kWave;
+      };
+#pragma unroll
+      for (int u = 0; u < kListRegs; ++u)
+        if (kWave * u < total) {
+          round(ce[u], cx[u], cs[u]);
+          if (u > 0) flush();  // (the first round stages 64 at most)
+        }
+      for (int c0 = kWave * kListRegs; c0 < total; c0 += kWave) {
+        const int c = c0 + lane;
+        const uint32_t e = cand(c < total ? c : total - 1);
+        float4 x = pos4[e & kNbrMask];
+        if (c >= total) x.x = __builtin_inff();
+        round(e, x, shift_s[e >> kNbrShift]);
+        flush();
+      }
+      if (ns > 0) emit(ns);
+      if ((kA & 3) && kA < capGA && lane < 4 - (kA & 3)) (nbrTA + p * rowTA)[kA + lane] = last_a;
+      if (lane == 0) {
+        cntR[p] = kR < capR ? kR : capR;
+        cntAV[p] = kA < capA ? kA : capA;
+      }
+      // the angular pairs within rc_angular at any step between rebuilds are
+      // among those within rc_angular + skin now, so kA bounds the per-step
+      // angular list
+      maxR = kR > maxR ? kR : maxR;
+      maxA = kA > maxA ? kA : maxA;
+      wave_fence();
     }
   }
-  // the last, partly filled groups (their r entries sit in the top r
-  // components: moved down to the front) and mask word
-  auto front = [](uint4 g, int r) {
-    return r == 1 ? make_uint4(g.w, g.w, g.w, g.w) : r == 2 ? make_uint4(g.z, g.w, g.w, g.w)
-                                                           : make_uint4(g.y, g.z, g.w, g.w);
-  };
-  if ((kR & 3) && kR < capG) *colG = front(grp, kR & 3);
-  if ((kR & 31) && kR < capG) *colM = mword >> (32 - (kR & 31));
-  if ((kA & 3) && kA < capGA) rowA[kA >> 2] = front(gra, kA & 3);
-  cntR[p] = kR < capR ? kR : capR;
-  cntAV[p] = kA < capA ? kA : capA;
-  // the angular pairs within rc_angular at any step between rebuilds are among
-  // those within rc_angular + skin now, so kA bounds the per-step angular list
-  if (kR > capR || kA > capA) atomicOr(&flags[kFlagOverflow], 1);
-  atomicMax(&flags[kFlagMaxR], kR);
-  atomicMax(&flags[kFlagMaxA], kA);
+  if (lane == 0) {
+    if (maxR > capR || maxA > capA) atomicOr(&flags[kFlagOverflow], 1);
+    // read first, past the L2 of this XCD: few wavefronts raise the maximum, and
+    // atomics on one address run one after another
+    auto raise = [&](int f, int v) {
+      if (v > __hip_atomic_load(&flags[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&flags[f], v);
+    };
+    raise(kFlagMaxR, maxR);
+    raise(kFlagMaxA, maxA);
+  }
 }
 
 // Reverse index: for every entry k of i's Verlet list whose pair is within
@@ -598,7 +803,7 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
   }
   const double rcl = rcR + skin_;
   std::vector<CfgDev> hc((size_t)n_cfg_);
-  int64_t bins = 0;
+  int64_t bins = 0, real = 0, most = 0;
   for (int c = 0; c < n_cfg_; ++c) {
     CfgDev& C = hc[(size_t)c];
     const double* H = cells + 9 * (size_t)c;
@@ -635,6 +840,9 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
     C.bin_off = (int)bins;
     C.atom_off = atom_off[c];
     C.n_atoms = (int)(atom_off[c + 1] - atom_off[c]);
+    const int64_t nb = (int64_t)C.nb[0] * C.nb[1] * C.nb[2];
+    real += nb;
+    most = std::max(most, (C.n_atoms + nb - 1) / nb);
     bins += (int64_t)((C.nb[0] + 3) / 4) * ((C.nb[1] + 3) / 4) * ((C.nb[2] + 3) / 4) * 64;
   }
   // bin keys below 2^27: the list build packs a key and a 5-bit image code
@@ -648,6 +856,8 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
   n_species = n_species_;
   n_slots = N + (int64_t)kWave * n_species_;
   total_bins = (int)bins;
+  real_bins = (int)real;
+  bin_atoms = (int)most;
   skin = skin_;
   const float rlR = (float)(rcR + skin_), rlA = (float)(rcA + skin_);
   rclR2 = rlR * rlR;
@@ -666,9 +876,9 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
       (rc = key.ensure(4 * Na)) || (rc = cnt.ensure(4 * (size_t)(M + 1))) || (rc = start.ensure(4 * (size_t)(M + 1))) ||
       (rc = cursor.ensure(4 * (size_t)(M + 1))) || (rc = tile_sums.ensure(4 * (size_t)(n_tiles + 1))) ||
       (rc = base.ensure(4 * (size_t)(n_species_ + 1))) || (rc = perm.ensure(4 * (size_t)n_slots)) ||
-      (rc = pos_tmp.ensure(16 * Na)) || (rc = cfg_tmp.ensure(4 * Na)) || (rc = crd_tmp.ensure(4 * Na)) || (rc = pos4.ensure(16 * (size_t)n_slots)) ||
+      (rc = pos_tmp.ensure(16 * Na)) || (rc = cfg_tmp.ensure(4 * Na)) || (rc = pos4.ensure(16 * (size_t)n_slots)) ||
       (rc = cfg_of.ensure(4 * (size_t)n_slots)) || (rc = orig.ensure(4 * (size_t)n_slots)) ||
-      (rc = bin_of.ensure(4 * (size_t)n_slots)) || (rc = slot_of.ensure(4 * Na)) ||
+      (rc = slot_of.ensure(4 * Na)) ||
       (rc = cntR.ensure(4 * (size_t)n_slots)) || (rc = cntAV.ensure(4 * (size_t)n_slots)) ||
       (rc = ccntR.ensure(4 * (size_t)n_slots)) ||
       (rc = ccntA.ensure(4 * (size_t)n_slots)) ||
@@ -697,7 +907,7 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
 
 void NbrPipeline::use_arena(Arena* a) {
   DevBuf* all[] = {&cfgs, &atom_off_dev, &key, &cnt, &start, &cursor, &tile_sums, &base, &perm, &pos_tmp,
-                   &cfg_tmp, &crd_tmp, &pos4, &cfg_of, &orig, &bin_of, &slot_of, &nbrR, &cntR, &cntAV, &nbrTA, &angm, &vrev,
+                   &cfg_tmp, &pos4, &cfg_of, &orig, &slot_of, &nbrR, &cntR, &cntAV, &nbrTA, &angm, &vrev,
                    &cnbrR, &ccntR, &cnbrA, &ccntA, &cposA, &flags};
   for (DevBuf* b : all) {
     b->release();
@@ -774,7 +984,7 @@ int NbrPipeline::launch_sort(hipStream_t st, const float* pos, int pos_stride, c
   if (N > 0)
   hipLaunchKernelGGL(k_stage, dim3(nblk(N, 256)), dim3(256), 0, st, N, n_cfg, atom_off_dev.ptr<int64_t>(),
                      cfgs.ptr<CfgDev>(), pos, pos_stride, species, n_species, total_bins, pos_tmp.ptr<float4>(),
-                     cfg_tmp.ptr<int>(), crd_tmp.ptr<int>(), key.ptr<int>(), cnt.ptr<int>(), flags.ptr<int>(), gate);
+                     cfg_tmp.ptr<int>(), key.ptr<int>(), cnt.ptr<int>(), flags.ptr<int>(), gate);
   const int n_tiles = (M + kScanTile - 1) / kScanTile;
   hipLaunchKernelGGL(k_scan_tiles, dim3(n_tiles), dim3(kScanBlock), 0, st, cnt.ptr<int>(), M, start.ptr<int>(),
                      tile_sums.ptr<int>(), gate);
@@ -789,16 +999,31 @@ int NbrPipeline::launch_sort(hipStream_t st, const float* pos, int pos_stride, c
                      total_bins, perm.ptr<int>(), gate);
   hipLaunchKernelGGL(k_fill_slots, dim3(nblk(n_slots, 256)), dim3(256), 0, st, n_slots, base.ptr<int>(),
                      start.ptr<int>(), total_bins, n_species, perm.ptr<int>(), pos_tmp.ptr<float4>(),
-                     cfg_tmp.ptr<int>(), crd_tmp.ptr<int>(), key.ptr<int>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), orig.ptr<int>(),
-                     bin_of.ptr<int>(), slot_of.ptr<int>(), carry ? *carry : SlotCarry{}, gate);
+                     cfg_tmp.ptr<int>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), orig.ptr<int>(), slot_of.ptr<int>(),
+                     cntR.ptr<int>(), cntAV.ptr<int>(), carry ? *carry : SlotCarry{}, gate);
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }
 
 int NbrPipeline::launch_lists(hipStream_t st, int n_species, const int* gate) {
-  hipLaunchKernelGGL(k_build_lists, dim3(nblk(n_slots, 256)), dim3(256), 0, st, n_slots, n_species, total_bins,
-                     cfgs.ptr<CfgDev>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), bin_of.ptr<int>(), start.ptr<int>(),
-                     base.ptr<int>(), rclR2, rclA2, capR, capA, rowTA, nbrR.ptr<uint32_t>(), nbrTA.ptr<uint32_t>(),
+  if (n_species > kListSpecies) {
+    set_error("too many species for the neighbour lists");
+    return NEPMI_UNSUPPORTED;
+  }
+  // parts: enough that about one wavefront per SIMD is at work
+  const unsigned parts = (unsigned)std::min(bin_atoms, std::max(1, kListWaves / real_bins));
+  // without a gate, a block per bin (at 900k atoms 346 us, 371 in 16384 blocks
+  // and 437 in 8192: most of a block's bins are alike, but the empty ones and
+  // the fuller ones are not spread evenly); with one, fewer blocks, since
+  // blocks cost time even when the gate sends them home at once
+  const unsigned want = ((unsigned)total_bins + kXcds - 1) / kXcds * kXcds;
+  const unsigned blocks = gate && want > kListGated ? kListGated : want;
+  // the larger candidate table takes LDS that the smaller one leaves to more
+  // wavefronts; a third is left for bins fuller than the mean
+  const auto kernel = 27 * bin_atoms * 4 / 3 <= kListCandMin ? k_build_lists<kListCandMin> : k_build_lists<kListCandMax>;
+  hipLaunchKernelGGL(kernel, dim3(blocks, parts), dim3(kWave), 0, st, n_slots, n_species, total_bins,
+                     cfgs.ptr<CfgDev>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), start.ptr<int>(), base.ptr<int>(),
+                     rclR2, rclA2, capR, capA, rowTA, nbrR.ptr<uint32_t>(), nbrTA.ptr<uint32_t>(),
                      angm.ptr<uint32_t>(), cntR.ptr<int>(), cntAV.ptr<int>(), flags.ptr<int>(), gate);
   const unsigned rev_tiles = (nblk(n_slots, 256) + kXcds - 1) / kXcds * kXcds;
   const unsigned rev_rows = rev_tiles >= kRevOneRow ? 1u : (unsigned)kRevSplit;

@@ -68,7 +68,9 @@ struct NbrPipeline {
   int n_cfg = 0;
   int n_species = 0;
   int64_t n_slots = 0;  // N + n_species * wavefront (upper bound of used slots)
-  int total_bins = 0;
+  int total_bins = 0;   // bins of every configuration in whole 4 x 4 x 4 tiles
+  int real_bins = 0;    // those inside the cells
+  int bin_atoms = 0;    // atoms per bin of the fullest configuration (mean over its bins, rounded up)
   int capR = 0, capA = 0;
   float rclR2 = 0.f, rclA2 = 0.f;
   double skin = 0.0;
@@ -76,8 +78,8 @@ struct NbrPipeline {
   std::vector<int64_t> host_off;
 
   DevBuf cfgs, atom_off_dev;
-  DevBuf key, cnt, start, cursor, tile_sums, base, perm, pos_tmp, cfg_tmp, crd_tmp;
-  DevBuf pos4, cfg_of, orig, bin_of, slot_of;
+  DevBuf key, cnt, start, cursor, tile_sums, base, perm, pos_tmp, cfg_tmp;
+  DevBuf pos4, cfg_of, orig, slot_of;
   DevBuf nbrR, cntR;             // Verlet list (rc_radial + skin)
   DevBuf cntAV;                  // entries within rc_angular + skin (the angular part of the list)
   DevBuf nbrTA;                  // the angular part of each list, row-major, rows of rowTA entries (reverse search)
