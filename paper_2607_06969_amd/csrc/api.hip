@@ -22,7 +22,7 @@ static const Ops* ops_of() {
   static const Ops o = {&Launch<S>::desc, &Launch<S>::force, &Launch<S>::gather, &Launch<S>::derive,
                         &TrainLaunch<S>::seeds, &TrainLaunch<S>::backward,
                         &TrainLaunch<S>::forward64, &TrainLaunch<S>::backward64, S::T, S::NR, S::NA, S::BR, S::BA, S::L,
-                        S::D, S::NANG, S::H, S::K, S::P, S::P + S::PCR + S::PCA};
+                        S::D, S::NANG, S::H, S::K, S::P, S::PALL};
   return &o;
 }
 

@@ -83,6 +83,12 @@ struct Shape {
   static constexpr int64_t PCA = (int64_t)T * T * NA * BA;
   static constexpr int64_t PMLP = (int64_t)H * D + 2 * H + 1;
   static constexpr int64_t P = PCR + PCA + T * PMLP;
+  // Derived tables stored after the parameters (see k_derive), 256-byte
+  // aligned: coefficients with the "+1" of Q_k folded in (radial, angular), then
+  // the transposed first-layer weights [T][D][64], hidden units zero padded.
+  static constexpr int64_t PD = (P + 63) / 64 * 64;
+  static constexpr int64_t PWT = PD + (PCR + PCA + 63) / 64 * 64;
+  static constexpr int64_t PALL = PWT + (int64_t)T * D * 64;
 };
 
 // Shapes compiled into the library: the 64-atom single-element test model,
@@ -635,14 +641,25 @@ struct Kappa {
   }
 };
 
+// dxy = x^2 - y^2 of the unit vector (x, y, z) = r inv comes from the caller, in
+// one of two roundings, (x - y)(x + y) with one product fused into the
+// difference and the sum: the sums over pairs take dxy_sums, the pair forces
+// dxy_force.  (Left to the compiler, the choice depends on the code around the
+// call; every form of a kernel has to make the same one.)
+__device__ __forceinline__ float dxy_sums(float rx, float y, float inv) {
+  return fmaf(rx, inv, -y) * fmaf(rx, inv, y);
+}
+__device__ __forceinline__ float dxy_force(float x, float ry, float inv) {
+  return fmaf(-ry, inv, x) * fmaf(ry, inv, x);
+}
+
 template <int L>
-__device__ __forceinline__ void raw_sph(float x, float y, float z, float (&P)[L * L + 2 * L]) {
+__device__ __forceinline__ void raw_sph(float x, float y, float z, float dxy, float (&P)[L * L + 2 * L]) {
   P[0] = z;
   P[1] = x;
   P[2] = y;
   if constexpr (L >= 2) {
     const float z2 = z * z, xy = x * y;
-    const float dxy = (x - y) * (x + y);  // x^2 - y^2
     P[3] = fmaf(3.0f, z2, -1.0f);
     P[4] = x * z;
     P[5] = y * z;
@@ -677,10 +694,11 @@ __device__ __forceinline__ void raw_sph(float x, float y, float z, float (&P)[L 
 }
 
 // v = sum_lm G_lm grad_u Praw_lm(u) (Praw extended off the unit sphere as
-// polynomials); the caller projects out the radial component.
+// polynomials); the caller projects out the radial component.  dxy as for
+// raw_sph.
 template <int L>
-__device__ __forceinline__ void raw_sph_grad_dot(float x, float y, float z, const float (&G)[L * L + 2 * L], float& gx,
-                                                 float& gy, float& gz) {
+__device__ __forceinline__ void raw_sph_grad_dot(float x, float y, float z, float dxy,
+                                                 const float (&G)[L * L + 2 * L], float& gx, float& gy, float& gz) {
   gx = G[1];
   gy = G[2];
   gz = G[0];
@@ -692,7 +710,6 @@ __device__ __forceinline__ void raw_sph_grad_dot(float x, float y, float z, cons
     gz = fmaf(6.0f * z, G[3], fmaf(x, G[4], fmaf(y, G[5], gz)));
     if constexpr (L >= 3) {
       const float z2 = z * z, xy = x * y, xz = x * z, yz = y * z;
-      const float dxy = (x - y) * (x + y);
       const float p5 = fmaf(5.0f, z2, -1.0f);
       // z(5z^2-3): (0,0,15z^2-3)  x(5z^2-1): (p5,0,10xz)  y(5z^2-1): (0,p5,10yz)
       // z(x^2-y^2): (2xz,-2yz,dxy)  xyz: (yz,xz,xy)

@@ -23,7 +23,7 @@ struct Ops {
                     double*, double*);
   int T, NR, NA, BR, BA, L, D, NANG, H, K;
   int64_t P;
-  int64_t P_alloc;  // P parameters + the derived coefficient table
+  int64_t P_alloc;  // P parameters + the derived tables
 };
 
 const Ops* find_ops(const nepmi_hparams& hp);

@@ -1,121 +1,10 @@
 // nep_kernels.hip -- descriptor/network, pair-force and gather kernels.
-#include "nep_kernels.hpp"
+#include "nep_device.hpp"
 #include "nbr.hpp"
 
 namespace nepmi {
 
 constexpr int kBlock = 256;
-
-// Pair vector r_ij = (x_j - x_i) + image shift, computed with the same
-// rounding from either side so that r_ji = -r_ij exactly.
-struct PairVec {
-  float rx, ry, rz, d2;
-  int q, zj;
-};
-
-// Lattice-vector multiples (w0, w1, w2) of the 27 image codes (see
-// image_shift), in LDS: one read per pair instead of the integer decode.
-struct ImageTable {
-  float4 w[32];
-  __device__ void fill() {
-    if (threadIdx.x < 27) {
-      const int c = threadIdx.x;
-      w[c] = make_float4((float)(c / 9 - 1), (float)((c / 3) % 3 - 1), (float)(c % 3 - 1), 0.f);
-    }
-  }
-};
-
-__device__ __forceinline__ PairVec pair_vec(uint32_t e, float4 xq, float4 xi, const float (&H)[9],
-                                            const ImageTable& it) {
-  PairVec v;
-  v.q = (int)(e & kNbrMask);
-  // the same expression as image_shift, so the shift of code 26 - c is again
-  // exactly the negative of the shift of c
-  const float4 w = it.w[e >> kNbrShift];
-  const float sx = w.x * H[0] + w.y * H[3] + w.z * H[6];
-  const float sy = w.x * H[1] + w.y * H[4] + w.z * H[7];
-  const float sz = w.x * H[2] + w.y * H[5] + w.z * H[8];
-  v.rx = (xq.x - xi.x) + sx;
-  v.ry = (xq.y - xi.y) + sy;
-  v.rz = (xq.z - xi.z) + sz;
-  v.d2 = pair_d2(v.rx, v.ry, v.rz);
-  v.zj = __float_as_int(xq.w);
-  return v;
-}
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-// Groups of four list entries fill by shifting entries in from the top
-// (register moves, no selects), so a full group holds them in order; a
-// partly filled one holds its r entries in the top r components, which
-// front4 moves to the front (the rest repeat the last entry, a real one).
-__device__ __forceinline__ void shift_in4(uint4& v, uint32_t e) { v = make_uint4(v.y, v.z, v.w, e); }
-__device__ __forceinline__ uint4 front4(uint4 g, int r) {
-  return r == 1 ? make_uint4(g.w, g.w, g.w, g.w) : r == 2 ? make_uint4(g.z, g.w, g.w, g.w)
-                                                           : make_uint4(g.y, g.z, g.w, g.w);
-}
-
-// One neighbour's radial adjoint row (B_R floats).
-template <int BR>
-struct AdjRow {
-  float4 v[BR / 4];
-};
-
-// Network dimensions padded to the 4-wide groups of the matrix instructions.
-template <class S>
-struct MlpPad {
-  static constexpr int HP = (S::H + 3) / 4 * 4;
-  static constexpr int DP = (S::D + 3) / 4 * 4;
-};
-
-// tanh(x) = 1 - 2 / (1 + e^{2x}) with the hardware exp2 and reciprocal
-// (absolute error a few 1e-7; saturates to +-1 for large |x|).
-__device__ __forceinline__ float tanh_fast(float x) {
-  const float e = __builtin_amdgcn_exp2f(x * 2.8853900817779268f);  // 2 log2(e)
-  return fmaf(-2.0f, __builtin_amdgcn_rcpf(1.0f + e), 1.0f);
-}
-
-
-__device__ __forceinline__ void load_cell(const CfgDev* __restrict__ cfgs, int c, float (&H)[9]) {
-  if (c >= 0) {
-#pragma unroll
-    for (int x = 0; x < 9; ++x) H[x] = cfgs[c].H[x];
-  } else {
-#pragma unroll
-    for (int x = 0; x < 9; ++x) H[x] = 0.f;
-  }
-}
-
-// S_n2m -> symmetric traceless A_n = sum_j g_n (u u^T - I/3) (l = 2 content).
-// Returns A as (xx, yy, zz, xy, xz, yz).
-__device__ __forceinline__ void a_from_s2(const float* s2, float (&A)[6]) {
-  const float azz = s2[0] * (1.0f / (3.0f * sh::k20));
-  const float dif = s2[3] * (1.0f / sh::k22);
-  A[0] = 0.5f * (dif - azz);
-  A[1] = -0.5f * (dif + azz);
-  A[2] = azz;
-  A[3] = s2[4] * (1.0f / sh::k21);
-  A[4] = s2[1] * (1.0f / sh::k21);
-  A[5] = s2[2] * (1.0f / sh::k21);
-}
-
-// A^2 as (xx, yy, zz, xy, xz, yz)
-__device__ __forceinline__ void sym_sq(const float (&A)[6], float (&B)[6]) {
-  const float xx = A[0], yy = A[1], zz = A[2], xy = A[3], xz = A[4], yz = A[5];
-  B[0] = xx * xx + xy * xy + xz * xz;
-  B[1] = xy * xy + yy * yy + yz * yz;
-  B[2] = xz * xz + yz * yz + zz * zz;
-  B[3] = xx * xy + xy * yy + xz * yz;
-  B[4] = xx * xz + xy * yz + xz * zz;
-  B[5] = xy * xz + yy * yz + yz * zz;
-}
-
-// tr(A^3) = sum_ab (A^2)_ab A_ab for symmetric A
-__device__ __forceinline__ float tr_cube(const float (&A)[6]) {
-  float B[6];
-  sym_sq(A, B);
-  return B[0] * A[0] + B[1] * A[1] + B[2] * A[2] + 2.0f * (B[3] * A[3] + B[4] * A[4] + B[5] * A[5]);
-}
 
 // S_nlm (l = 1..L) of one group of NH angular functions, summed over the
 // angular pairs of the atom (Eq. 16): S = sum_j g_n(r_ij) Y_lm(u_ij) with
@@ -147,7 +36,8 @@ __device__ __forceinline__ void angular_sums(const float4* __restrict__ pos4, co
       g[nn] = f.hf * acc;
     }
     float P[K];
-    raw_sph<L>(v.rx * inv, v.ry * inv, v.rz * inv, P);
+    const float uy = v.ry * inv;
+    raw_sph<L>(v.rx * inv, uy, v.rz * inv, dxy_sums(v.rx, uy, inv), P);
 #pragma unroll
     for (int nn = 0; nn < NH; ++nn)
 #pragma unroll
@@ -208,7 +98,7 @@ __device__ __forceinline__ void network(const float (&q)[MlpPad<S>::DP], int Zs,
                                         float* __restrict__ Eproc, int want_adjoint) {
   constexpr int T = S::T, NR = S::NR, BR = S::BR, D = S::D, H = S::H;
   constexpr int HP = MlpPad<S>::HP, DP = MlpPad<S>::DP;
-  const float* __restrict__ dco = params + S::P;
+  const float* __restrict__ dco = params + S::PD;
   const int lq = threadIdx.x & 3;
   const float* b0g = params + S::PCR + S::PCA + (int64_t)Zs * S::PMLP + H * D;
   const float* w1g = b0g + H;
@@ -327,7 +217,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
   constexpr int NH = NA / NSPLIT;
   static_assert(NA % NSPLIT == 0, "NSPLIT must divide n_angular");
   constexpr int HP = MlpPad<S>::HP, DP = MlpPad<S>::DP;
-  const float* __restrict__ dco = params + S::P;  // derived coefficients: radial, then angular
+  const float* __restrict__ dco = params + S::PD;  // derived coefficients: radial, then angular
   __shared__ float cA_s[T * T * NA * BA];
   __shared__ ImageTable itab;
   __shared__ float W0s[NET ? T * HP * DP : 1];   // [Z][h][d] network weights, zero padded
@@ -663,7 +553,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
       for (int nn = 0; nn < NR; ++nn) Fr[nn] = fr_s[wv][nn][lane];
       // radial adjoint atil[b][k] = sum_n dE/dq_n ctil[Z_i][b][n][k]
-      const float* cR = params + S::P + (int64_t)Zs * (T * NR * BR);
+      const float* cR = params + S::PD + (int64_t)Zs * (T * NR * BR);
 #pragma unroll
       for (int b = 0; b < T; ++b) {
         float4* row = reinterpret_cast<float4*>(aR + ((int64_t)b * ns + p) * BR);
@@ -706,7 +596,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
   constexpr int T = S::T, NR = S::NR, NA = S::NA, BR = S::BR, BA = S::BA, L = S::L, K = S::K;
   constexpr int NH = NA / NSPLIT;
   constexpr int RW = lds_row<T * BR>();
-  const float* __restrict__ dco = params + S::P;
+  const float* __restrict__ dco = params + S::PD;
   __shared__ float cA_s[T * T * NA * BA];
   __shared__ float aown_s[T > 1 ? BS * RW : 1];
   __shared__ ImageTable itab;
@@ -821,18 +711,11 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
         float A[6], B[6];
         a_from_s2(&Sg[nn][3], A);
         sym_sq(A, B);
-        const float f4 = 3.0f * fp[(int64_t)(S::OFF4 - NR + n) * n_slots + p];
-#pragma unroll
-        for (int x = 0; x < 6; ++x) B[x] *= f4;
-        s4[0] = (B[2] - 0.5f * (B[0] + B[1])) * (1.0f / (3.0f * sh::k20));
-        s4[1] = 2.0f * B[4] * (1.0f / sh::k21);
-        s4[2] = 2.0f * B[5] * (1.0f / sh::k21);
-        s4[3] = 0.5f * (B[0] - B[1]) * (1.0f / sh::k22);
-        s4[4] = 2.0f * B[3] * (1.0f / sh::k21);
+        s4_from_sq(B, 3.0f * fp[(int64_t)(S::OFF4 - NR + n) * n_slots + p], s4);
       }
       float psi1 = 2.0f * fp[(int64_t)(0 * NA + n) * n_slots + p];
       if constexpr (S::F5) {
-        const float q1 = Sg[nn][0] * Sg[nn][0] + Sg[nn][1] * Sg[nn][1] + Sg[nn][2] * Sg[nn][2];
+        const float q1 = fmaf(Sg[nn][2], Sg[nn][2], fmaf(Sg[nn][0], Sg[nn][0], Sg[nn][1] * Sg[nn][1]));
         psi1 = fmaf(4.0f * q1, fp[(int64_t)(S::OFF5 - NR + n) * n_slots + p], psi1);
       }
 #pragma unroll
@@ -843,7 +726,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
       }
       if constexpr (S::F4) {
 #pragma unroll
-        for (int m = 0; m < 5; ++m) Sg[nn][3 + m] += s4[m];
+        for (int m = 0; m < 5; ++m) Sg[nn][3 + m] = fmaf(s4_scale(m), s4[m], Sg[nn][3 + m]);
       }
 #pragma unroll
       for (int lm = 0; lm < K; ++lm) Sg[nn][lm] *= kap.v[lm];
@@ -888,7 +771,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
         }
       }
       float P[K];
-      raw_sph<L>(ux, uy, uz, P);
+      const float dxy = dxy_force(ux, v.ry, inv);
+      raw_sph<L>(ux, uy, uz, dxy, P);
       float G[K];
 #pragma unroll
       for (int lm = 0; lm < K; ++lm) G[lm] = 0.f;
@@ -904,7 +788,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
         s = fmaf(gp[nn], zn, s);
       }
       float vx, vy, vz;
-      raw_sph_grad_dot<L>(ux, uy, uz, G, vx, vy, vz);
+      raw_sph_grad_dot<L>(ux, uy, uz, dxy, G, vx, vy, vz);
       const float uv = fmaf(ux, vx, fmaf(uy, vy, uz * vz));
       const float fx = fmaf(s, ux, (vx - uv * ux) * inv);
       const float fy = fmaf(s, uy, (vy - uv * uy) * inv);
@@ -1032,14 +916,21 @@ __global__ __launch_bounds__(BS) void k_gather(int64_t n_slots, const int* __res
   if (Fproc) Fproc[p] = F;
 }
 
-// Derived coefficient table: ctil[..][n][0] = c[..][n][0] + sum_k c[..][n][k],
+// Derived tables.  Coefficients: ctil[..][n][0] = c[..][n][0] + sum_k c[..][n][k],
 // ctil[..][n][k] = c[..][n][k] for k >= 1, for every radial row (length BR)
 // and angular row (length BA).  With Q_k = hf (T_k + 1) this gives
-// sum_k c_nk Q_k = hf sum_k ctil_nk T_k.
+// sum_k c_nk Q_k = hf sum_k ctil_nk T_k.  Then the first-layer weights
+// transposed, one thread per entry, for the kernels that give a hidden unit to
+// each lane.
 template <class S>
-__global__ void k_derive(const float* __restrict__ params, float* __restrict__ out) {
+__global__ void k_derive(const float* __restrict__ params, float* __restrict__ out, float* __restrict__ wt) {
   constexpr int rowsR = S::T * S::T * S::NR, rowsA = S::T * S::T * S::NA;
+  static_assert(S::H <= kWave, "the transposed weights hold one wavefront of hidden units");
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r < S::T * S::D * kWave) {
+    const int h = r % kWave, d = (r / kWave) % S::D, z = r / (kWave * S::D);
+    wt[r] = h < S::H ? params[S::PCR + S::PCA + (int64_t)z * S::PMLP + h * S::D + d] : 0.0f;
+  }
   if (r >= rowsR + rowsA) return;
   const int B = r < rowsR ? S::BR : S::BA;
   const int64_t o = r < rowsR ? (int64_t)r * S::BR : S::PCR + (int64_t)(r - rowsR) * S::BA;
@@ -1106,7 +997,9 @@ int Launch<S>::desc(hipStream_t st, const NepIO& io, const float* params, bool w
     case 7: return launch_desc<S, 2, 3, false>(st, io, params, want_adjoint);
     case 8: return launch_desc<S, 2, 2, true, 128>(st, io, params, want_adjoint);
     case 9: return launch_desc<S, 2, 2, true, 512>(st, io, params, want_adjoint);
-    default: return launch_desc<S, 2, 2, true>(st, io, params, want_adjoint);
+    default:
+      return io.n_slots <= kWaveSlots ? WaveLaunch<S>::desc(st, io, params, want_adjoint)
+                                      : launch_desc<S, 2, 2, true>(st, io, params, want_adjoint);
   }
 }
 
@@ -1118,7 +1011,8 @@ int Launch<S>::force(hipStream_t st, const NepIO& io, const float* params, int v
     case 3: return launch_force<S, 1, 1>(st, io, params);
     case 4: return launch_force<S, 2, 2, 128>(st, io, params);
     case 5: return launch_force<S, 2, 2, 512>(st, io, params);
-    default: return launch_force<S, 2, 2>(st, io, params);
+    default:
+      return io.n_slots <= kWaveSlots ? WaveLaunch<S>::force(st, io, params) : launch_force<S, 2, 2>(st, io, params);
   }
 }
 
@@ -1143,8 +1037,9 @@ int Launch<S>::gather(hipStream_t st, const NepIO& io, int variant) {
 
 template <class S>
 int Launch<S>::derive(hipStream_t st, float* params) {
-  constexpr int rows = S::T * S::T * (S::NR + S::NA);
-  hipLaunchKernelGGL(k_derive<S>, dim3((rows + 127) / 128), dim3(128), 0, st, params, params + S::P);
+  constexpr int rows = S::T * S::T * (S::NR + S::NA), wts = S::T * S::D * kWave;
+  constexpr int n = rows > wts ? rows : wts;
+  hipLaunchKernelGGL(k_derive<S>, dim3((n + 127) / 128), dim3(128), 0, st, params, params + S::PD, params + S::PWT);
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }

@@ -1,6 +1,7 @@
 // nep_kernels.hpp -- NEP evaluation kernels for gfx950, templated on the shape.
 //
-// One thread evaluates one atom slot; every wavefront holds one species (see
+// One thread evaluates one atom slot (one wavefront in small batches, see
+// nep_wave.hip); every wavefront holds one species (see
 // nbr.hip), so species-pair coefficients c[Z_i][.] and the network weights of
 // Z_i are read through the scalar unit.  Coefficients that depend on the
 // neighbour's species are read from LDS.  The kernels use a derived copy of
@@ -71,9 +72,23 @@ struct Launch {
   static int desc(hipStream_t st, const NepIO& io, const float* params, bool want_adjoint, int variant);
   static int force(hipStream_t st, const NepIO& io, const float* params, int variant);
   static int gather(hipStream_t st, const NepIO& io, int variant);
-  // Writes the derived coefficient table after the P parameters (the
-  // parameter buffer holds P + PCR + PCA floats).
+  // Writes the derived tables after the P parameters (the parameter buffer
+  // holds PALL floats).
   static int derive(hipStream_t st, float* params);
+};
+
+// Variant 0 of k_desc and k_force with one wavefront per atom, bit for bit the
+// same results (nep_wave.hip), for batches that fit kWaveSlots slots.
+// With one thread per atom these kernels take the time of one walk up to about
+// 65,000 atoms (one wavefront per SIMD); with one wavefront the time grows with
+// the atoms.  k_desc + k_force of the Ge-Sb-Te model, thread -> wavefront (us):
+// 3,686 atoms 56 + 70 -> 15 + 18, 9,100 62 + 75 -> 28 + 31, 18,400 61 + 79 ->
+// 49 + 56, 29,500 54 (k_desc) -> 61.
+constexpr int64_t kWaveSlots = 24576;
+template <class S>
+struct WaveLaunch {
+  static int desc(hipStream_t st, const NepIO& io, const float* params, bool want_adjoint);
+  static int force(hipStream_t st, const NepIO& io, const float* params);
 };
 
 }  // namespace nepmi
