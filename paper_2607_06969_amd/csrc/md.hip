@@ -56,41 +56,13 @@ __global__ void k_md_kick_drift(int64_t n_slots, MdConst mc, const int* __restri
   if (dx * dx + dy * dy + dz * dz > mc.half_skin2) atomicOr(&flags[kFlagRebuild], 1);
 }
 
-// Wrap r into the cell along its periodic directions in float64, and round it
-// to f; if the rounding lands outside the cell (a last-ulp case at a face),
-// wrap the rounded value once more.  Non-periodic directions are left alone.
-__device__ void wrap_periodic(const CfgDev& C, double r[3], float f[3]) {
-  for (int pass = 0; pass < 2; ++pass) {
-    double m[3];
-    for (int a = 0; a < 3; ++a) {
-      const double s = r[0] * C.Hinv[a] + r[1] * C.Hinv[3 + a] + r[2] * C.Hinv[6 + a];
-      m[a] = (C.periodic >> a) & 1 ? floor(s) : 0.0;
-    }
-    for (int a = 0; a < 3; ++a) r[a] -= m[0] * C.Hd[a] + m[1] * C.Hd[3 + a] + m[2] * C.Hd[6 + a];
-    for (int a = 0; a < 3; ++a) f[a] = (float)r[a];
-    // the float32 copy must also lie in the cell (as the staging kernel sees it)
-    bool inside = true;
-    for (int a = 0; a < 3; ++a) {
-      const double s = (double)f[0] * C.Hinv[a] + (double)f[1] * C.Hinv[3 + a] + (double)f[2] * C.Hinv[6 + a];
-      if ((C.periodic >> a) & 1 && floor(s) != 0.0) inside = false;
-    }
-    if (inside) break;
-    for (int a = 0; a < 3; ++a) r[a] = (double)f[a];
-  }
-}
-
-// Before a rebuild: state back to caller order, positions wrapped into the
-// cell in float64 so that the float32 copy needs no further wrapping.  Also
-// clears the n_clear key counts of the sort that follows (cnt may be null).
+// State back to caller order, positions wrapped into the cell in float64 so
+// that the float32 copy needs no further wrapping (the checkpoint).
 __global__ void k_md_unpermute(int64_t n_slots, const int* __restrict__ cfg_of, const int* __restrict__ orig,
                                const CfgDev* __restrict__ cfgs, const Dbl3* __restrict__ xd,
                                const float4* __restrict__ vel4, Dbl3* __restrict__ xd_user,
-                               float4* __restrict__ x_user, float4* __restrict__ v_user, int* __restrict__ cnt,
-                               int64_t n_clear, const int* __restrict__ gate) {
-  if (*gate == 0) return;
+                               float4* __restrict__ x_user, float4* __restrict__ v_user) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (cnt)
-    for (int64_t k = p; k < n_clear; k += (int64_t)gridDim.x * blockDim.x) cnt[k] = 0;
   if (p >= n_slots) return;
   const int c = cfg_of[p];
   if (c < 0) return;
@@ -201,9 +173,9 @@ struct nepmi_md {
   DevBuf species_user, xd_user, x_user, v_user, xd, vel4, ref4, F4;
   DevBuf fp, aR, Ei, frad, fA, amask, Wi, Ki, Eproc;
   DevBuf epot, ekin, vir, counters;
-  // checkpoint of the last checked step (caller order, wrapped positions), its
-  // device counters, and a device word holding 1 (an always-open gate)
-  DevBuf snap_xd, snap_x, snap_v, snap_cnt, one;
+  // checkpoint of the last checked step (caller order, wrapped positions) and
+  // its device counters
+  DevBuf snap_xd, snap_x, snap_v, snap_cnt;
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;     // the step
   hipGraphExec_t exec = nullptr;
@@ -295,18 +267,23 @@ struct nepmi_md {
     return NEPMI_OK;
   }
 
+  // Sort and lists; the sort takes the state back to caller order (wrapped)
+  // and moves it into the new slot order.
   int rebuild(hipStream_t st, const int* gate) {
-    const int64_t ns = nbr.n_slots;
-    hipLaunchKernelGGL(k_md_unpermute, dim3(nb256(ns)), dim3(256), 0, st, ns, nbr.cfg_of.ptr<int>(),
-                       nbr.orig.ptr<int>(), nbr.cfgs.ptr<CfgDev>(), xd.ptr<Dbl3>(), vel4.ptr<float4>(),
-                       xd_user.ptr<Dbl3>(), x_user.ptr<float4>(), v_user.ptr<float4>(), nbr.cnt.ptr<int>(),
-                       (int64_t)n_species * nbr.total_bins + 1, gate);
-    return after_unpermute(st, gate, true);
+    SlotSource src;
+    src.cfg_of = nbr.cfg_of.ptr<int>();
+    src.orig = nbr.orig.ptr<int>();
+    src.xd = reinterpret_cast<const double*>(xd.ptr<Dbl3>());
+    src.vel4 = vel4.ptr<float4>();
+    src.xd_user = reinterpret_cast<double*>(xd_user.ptr<Dbl3>());
+    src.x_user = x_user.ptr<float4>();
+    src.v_user = v_user.ptr<float4>();
+    return sort_and_lists(st, gate, &src);
   }
 
-  // Sort and lists from the caller-order state; the sort moves the state into
-  // the new slot order.  cnt_zeroed: the key counts are already clear.
-  int after_unpermute(hipStream_t st, const int* gate, bool cnt_zeroed) {
+  // The same from the caller-order state (src null: xd_user, x_user, v_user
+  // hold it already).
+  int sort_and_lists(hipStream_t st, const int* gate, const SlotSource* src = nullptr) {
     SlotCarry carry;
     carry.xd_user = reinterpret_cast<const double*>(xd_user.ptr<Dbl3>());
     carry.x_user = x_user.ptr<float4>();
@@ -315,8 +292,7 @@ struct nepmi_md {
     carry.vel4 = vel4.ptr<float4>();
     carry.ref4 = ref4.ptr<float4>();
     int rc;
-    if ((rc = nbr.launch_sort(st, x_user.ptr<float>(), 4, species_user.ptr<int32_t>(), n_species, gate, cnt_zeroed,
-                              &carry)))
+    if ((rc = nbr.launch_sort(st, x_user.ptr<float>(), 4, species_user.ptr<int32_t>(), n_species, gate, &carry, src)))
       return rc;
     return nbr.launch_lists(st, n_species, gate);
   }
@@ -382,8 +358,7 @@ struct nepmi_md {
     const int64_t ns = nbr.n_slots;
     hipLaunchKernelGGL(k_md_unpermute, dim3(nb256(ns)), dim3(256), 0, st, ns, nbr.cfg_of.ptr<int>(),
                        nbr.orig.ptr<int>(), nbr.cfgs.ptr<CfgDev>(), xd.ptr<Dbl3>(), vel4.ptr<float4>(),
-                       snap_xd.ptr<Dbl3>(), snap_x.ptr<float4>(), snap_v.ptr<float4>(), nullptr, (int64_t)0,
-                       one.ptr<int>());
+                       snap_xd.ptr<Dbl3>(), snap_x.ptr<float4>(), snap_v.ptr<float4>());
     NEPMI_HIP(hipGetLastError());
     NEPMI_HIP(hipMemcpyAsync(snap_cnt.p, counters.p, 16, hipMemcpyDeviceToDevice, st));
     return NEPMI_OK;
@@ -407,7 +382,7 @@ struct nepmi_md {
       NEPMI_HIP(hipMemcpyAsync(counters.p, snap_cnt.p, 16, hipMemcpyDeviceToDevice, st));
       fill_int(st, flags, kFlagCount, 0, nullptr);
       hipLaunchKernelGGL(k_set_int, dim3(1), dim3(64), 0, st, flags + kFlagRebuild, 1);
-      if ((rc = after_unpermute(st, flags + kFlagRebuild, false))) return rc;
+      if ((rc = sort_and_lists(st, flags + kFlagRebuild))) return rc;
       int hf[kFlagCount];
       if ((rc = nbr.check_flags(st, hf))) return rc;
       if (!hf[kFlagOverflow]) break;
@@ -489,9 +464,8 @@ int nepmi_md_create(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
       (rc = md->epot.ensure(8 * (size_t)n_cfg)) || (rc = md->ekin.ensure(8 * (size_t)n_cfg)) ||
       (rc = md->vir.ensure(72 * (size_t)n_cfg)) || (rc = md->counters.ensure(16)) ||
       (rc = md->snap_xd.ensure(24 * Na)) || (rc = md->snap_x.ensure(16 * Na)) || (rc = md->snap_v.ensure(16 * Na)) ||
-      (rc = md->snap_cnt.ensure(16)) || (rc = md->one.ensure(4)))
+      (rc = md->snap_cnt.ensure(16)))
     return fail(rc);
-  hipLaunchKernelGGL(k_set_int, dim3(1), dim3(64), 0, st, md->one.ptr<int>(), 1);
   if (hipMemcpyAsync(md->species_user.p, dev_species, 4 * (size_t)N, hipMemcpyDeviceToDevice, st) != hipSuccess)
     return fail(hip_fail(hipGetLastError(), "hipMemcpyAsync(species)"));
   hipLaunchKernelGGL(k_md_init, dim3(nb256(N > 0 ? N : 1)), dim3(256), 0, st, N, n_cfg, nb.atom_off_dev.ptr<int64_t>(),
@@ -502,7 +476,7 @@ int nepmi_md_create(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
   // first build, with capacity growth and a margin for the density
   // fluctuations of the run
   hipLaunchKernelGGL(k_set_int, dim3(1), dim3(64), 0, st, nb.flags.ptr<int>() + kFlagRebuild, 1);
-  if ((rc = md->after_unpermute(st, nb.flags.ptr<int>() + kFlagRebuild, false))) return fail(rc);
+  if ((rc = md->sort_and_lists(st, nb.flags.ptr<int>() + kFlagRebuild))) return fail(rc);
   int hf[kFlagCount];
   if ((rc = nb.check_flags(st, hf))) return fail(rc);
   const int wantR = hf[kFlagMaxR] + hf[kFlagMaxR] / 4 + 16, wantA = hf[kFlagMaxA] + hf[kFlagMaxA] / 4 + 16;

@@ -23,6 +23,13 @@
 
 namespace nepmi {
 
+constexpr int kScanBlock = 1024;
+constexpr int kMaxSortSpecies = 8;
+// Largest sort that one block does whole, and most keys that one block scans
+// (see k_sort_small, k_scan_one).
+constexpr int kSmallAtoms = 4096, kSmallKeys = 8192;
+constexpr int kOneScan = 1 << 15, kOneScanGated = 1 << 20;
+
 // ------------------------------------------------------------------ staging
 
 // Per caller-order atom: validate, wrap into the cell, find its bin and sort key.
@@ -37,35 +44,13 @@ __device__ __forceinline__ int bin_key(const CfgDev& C, int b0, int b1, int b2) 
   return C.bin_off + (t << 6) + (((b0 & 3) << 4) | ((b1 & 3) << 2) | (b2 & 3));
 }
 
-__global__ void k_stage(int64_t N, int n_cfg, const int64_t* __restrict__ atom_off, const CfgDev* __restrict__ cfgs,
-                        const float* __restrict__ pos, int pos_stride, const int32_t* __restrict__ species,
-                        int n_species, int total_bins, float4* __restrict__ pos_tmp, int* __restrict__ cfg_tmp,
-                        int* __restrict__ key, int* __restrict__ cnt, int* __restrict__ flags,
-                        const int* __restrict__ gate) {
-  if (gate && *gate == 0) return;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  // configuration of atom i: binary search in atom_off
-  int lo = 0, hi = n_cfg;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (atom_off[mid] <= i) lo = mid; else hi = mid;
-  }
-  const CfgDev& C = cfgs[lo];
-  const int z = species[i];
-  if (z < 0 || z >= n_species) {
-    atomicOr(&flags[kFlagBadSpecies], 1);
-    key[i] = -1;
-    return;
-  }
-  const float x = pos[i * pos_stride + 0], y = pos[i * pos_stride + 1], w = pos[i * pos_stride + 2];
-  if (!(isfinite(x) && isfinite(y) && isfinite(w))) {
-    atomicOr(&flags[kFlagNaN], 1);
-    key[i] = -1;
-    return;
-  }
+// Sort key of an atom at (x, y, w) of species z, and its position wrapped into
+// the cell.
+__device__ __forceinline__ int stage_atom(const CfgDev& C, int z, int total_bins, float x, float y, float w,
+                                          float (&o)[3]) {
   int b[3];
   double m[3];
+#pragma unroll
   for (int a = 0; a < 3; ++a) {
     const double s = (double)x * C.Hinv[a] + (double)y * C.Hinv[3 + a] + (double)w * C.Hinv[6 + a];
     // along a non-periodic direction the atom is not wrapped, and one outside
@@ -76,22 +61,156 @@ __global__ void k_stage(int64_t N, int n_cfg, const int64_t* __restrict__ atom_o
     const double t = (s - m[a]) * C.nb[a];
     b[a] = t < 0.0 ? 0 : (t >= (double)C.nb[a] ? C.nb[a] - 1 : (int)t);
   }
-  float o[3] = {x, y, w};
+  o[0] = x;
+  o[1] = y;
+  o[2] = w;
   if (m[0] != 0.0 || m[1] != 0.0 || m[2] != 0.0) {
     // wrap by whole lattice vectors (float64, then rounded once)
+#pragma unroll
     for (int a = 0; a < 3; ++a)
       o[a] = (float)((double)o[a] - m[0] * C.Hd[a] - m[1] * C.Hd[3 + a] - m[2] * C.Hd[6 + a]);
   }
-  const int k = z * total_bins + bin_key(C, b[0], b[1], b[2]);
-  key[i] = k;
-  pos_tmp[i] = make_float4(o[0], o[1], o[2], __int_as_float(z));
-  cfg_tmp[i] = lo;
-  atomicAdd(&cnt[k], 1);
+  return z * total_bins + bin_key(C, b[0], b[1], b[2]);
+}
+
+// Where the atoms to sort come from and what the sort works on.
+struct SortArgs {
+  int64_t N, n_slots;
+  int n_cfg, n_species, total_bins;
+  const int64_t* atom_off;
+  const CfgDev* cfgs;
+  const float* pos;          // caller order, pos_stride floats per atom (unused with src.xd)
+  int pos_stride;
+  const int32_t* species;    // caller order
+  SlotSource src;            // MD state in the present slot order (src.xd null: none)
+  SlotCarry carry;
+  // work
+  float4* pos_tmp;
+  int *cfg_tmp, *key, *cnt, *start, *cursor, *perm;
+  // results
+  float4* pos4;
+  int *base, *cfg_of, *orig, *slot_of, *cntR, *cntAV, *flags;
+};
+
+// An atom on its way to its slot.
+struct Staged {
+  int key;         // sort key, -1 if the atom is refused (the flags say why)
+  int i, c;        // caller index, configuration
+  float4 x;        // wrapped position and species
+  float4 xu, v;    // MD state: float32 position the build stages, velocity
+  double r[3];     // MD state: float64 position
+};
+
+// Stage caller atom i of configuration c at (x, y, w).
+__device__ __forceinline__ void stage_one(const SortArgs& a, Staged& s, float x, float y, float w) {
+  const int z = a.species[s.i];
+  s.key = -1;
+  if (z < 0 || z >= a.n_species) {
+    atomicOr(&a.flags[kFlagBadSpecies], 1);
+  } else if (!(isfinite(x) && isfinite(y) && isfinite(w))) {
+    atomicOr(&a.flags[kFlagNaN], 1);
+  } else {
+    float o[3];
+    s.key = stage_atom(a.cfgs[s.c], z, a.total_bins, x, y, w, o);
+    s.x = make_float4(o[0], o[1], o[2], __int_as_float(z));
+  }
+}
+
+// Configuration of caller atom i: the last c with off[c] <= i.
+template <class P>
+__device__ __forceinline__ int config_of(P off, int n_cfg, int64_t i) {
+  int lo = 0, hi = n_cfg;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (off[mid] <= i) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// Stage slot p of the MD state, its position wrapped into the cell in float64
+// (so that the float32 copy needs no further wrapping); false for padding.
+__device__ __forceinline__ bool stage_slot(const SortArgs& a, Staged& s, int64_t p) {
+  s.key = -1;
+  s.c = a.src.cfg_of[p];
+  if (s.c < 0) return false;
+  s.i = a.src.orig[p];
+  s.v = a.src.vel4[p];
+  float f[3];
+#pragma unroll
+  for (int x = 0; x < 3; ++x) s.r[x] = a.src.xd[3 * p + x];
+  wrap_periodic(a.cfgs[s.c], s.r, f);
+  s.xu = make_float4(f[0], f[1], f[2], 0.f);
+  stage_one(a, s, f[0], f[1], f[2]);
+  return true;
+}
+
+// Stage the atom of each thread: a caller atom, or a slot of the MD state, whose
+// state goes back to caller order.
+template <bool SLOTS>
+__global__ void k_stage(SortArgs a, const int* __restrict__ gate) {
+  if (gate && *gate == 0) return;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= (SLOTS ? a.n_slots : a.N)) return;
+  Staged s;
+  if constexpr (SLOTS) {
+    if (!stage_slot(a, s, t)) return;
+#pragma unroll
+    for (int x = 0; x < 3; ++x) a.src.xd_user[3 * (int64_t)s.i + x] = s.r[x];
+    a.src.x_user[s.i] = s.xu;
+    a.src.v_user[s.i] = s.v;
+  } else {
+    s.i = (int)t;
+    s.c = config_of(a.atom_off, a.n_cfg, t);
+    const float* x = a.pos + t * a.pos_stride;
+    stage_one(a, s, x[0], x[1], x[2]);
+  }
+  a.key[s.i] = s.key;
+  if (s.key < 0) return;
+  a.pos_tmp[s.i] = s.x;
+  a.cfg_tmp[s.i] = s.c;
+  atomicAdd(&a.cnt[s.key], 1);
+}
+
+// Put an atom into slot p.  With carry.xd set, the carried state moves into the
+// slot as well: the staging wraps again only in a last-ulp case at a cell face,
+// and that shift (zero otherwise) is carried into the float64 position.
+__device__ __forceinline__ void put_slot(const SortArgs& a, int64_t p, const Staged& s) {
+  a.pos4[p] = s.x;
+  a.cfg_of[p] = s.c;
+  a.orig[p] = s.i;
+  if (a.slot_of) a.slot_of[s.i] = (int)p;
+  if (a.carry.xd) {
+    double* o = a.carry.xd + 3 * p;
+    o[0] = s.r[0] + ((double)s.x.x - (double)s.xu.x);
+    o[1] = s.r[1] + ((double)s.x.y - (double)s.xu.y);
+    o[2] = s.r[2] + ((double)s.x.z - (double)s.xu.z);
+    a.carry.vel4[p] = s.v;
+    a.carry.ref4[p] = s.x;
+  }
+}
+
+// The carried state of caller atom i.
+__device__ __forceinline__ void load_carry(const SortArgs& a, Staged& s) {
+  if (!a.carry.xd) return;
+#pragma unroll
+  for (int x = 0; x < 3; ++x) s.r[x] = a.carry.xd_user[3 * (int64_t)s.i + x];
+  s.xu = a.carry.x_user[s.i];
+  s.v = a.carry.v_user[s.i];
+}
+
+// Padding slots get orig = -1, their group's species and empty lists (the list
+// build visits atoms only).
+__device__ __forceinline__ void pad_slot(const SortArgs& a, int64_t p, int z) {
+  if (a.carry.xd) a.carry.vel4[p] = make_float4(0.f, 0.f, 0.f, 0.f);
+  a.pos4[p] = make_float4(0.f, 0.f, 0.f, __int_as_float(z));
+  a.cfg_of[p] = -1;
+  a.orig[p] = -1;
+  a.cntR[p] = 0;
+  a.cntAV[p] = 0;
 }
 
 // ------------------------------------------------------------ exclusive scan
 
-constexpr int kScanBlock = 1024;
 constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanBlock * kScanItems;
 
@@ -173,106 +292,260 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_sums(int* __restrict__ tile
   species_base[n_species] = acc;
 }
 
-// Global prefixes, also copied into the scatter cursors.
+// Global prefixes, also copied into the scatter cursors; the counts are cleared
+// for the next sort.
 __global__ void k_scan_add(int* __restrict__ out, int M, const int* __restrict__ tile_sums,
-                           int* __restrict__ cursor, const int* __restrict__ gate) {
+                           int* __restrict__ cursor, int* __restrict__ cnt, const int* __restrict__ gate) {
   if (gate && *gate == 0) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < M) {
     const int v = out[i] + tile_sums[i / kScanTile];
     out[i] = v;
     cursor[i] = v;
+    cnt[i] = 0;
+  }
+}
+
+// Inclusive scan over a block of kScanBlock threads (wavefront scans, then the
+// wavefront totals); sh holds one int per wavefront.  Ends with a barrier.
+__device__ __forceinline__ int block_inclusive(int v, int* sh, int& total) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(v, o, 64);
+    if (lane >= o) v += u;
+  }
+  if (lane == 63) sh[wv] = v;
+  __syncthreads();
+  int before = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < kScanBlock / 64; ++w) {
+    before += w < wv ? sh[w] : 0;
+    total += sh[w];
+  }
+  __syncthreads();
+  return v + before;
+}
+
+// Species bases from the number of atoms before each species: base[z] = first
+// slot of species z, each group padded to the wavefront size.
+__device__ __forceinline__ void species_bases(const SortArgs& a, const int* lo, int total) {
+  int acc = 0;
+  for (int z = 0; z < a.n_species; ++z) {
+    const int n = (z + 1 < a.n_species ? lo[z + 1] : total) - lo[z];
+    a.base[z] = acc;
+    acc += (n + kWave - 1) / kWave * kWave;
+  }
+  a.base[a.n_species] = acc;
+}
+
+// The whole scan by one block: prefixes, cursors, cleared counts, species
+// bases.  One kernel instead of three for the small sorts, where a launch costs
+// more than the scan, and for the gated sorts of MD, where every kernel costs
+// 4.5 us in every step and the sort runs once in some 40 (255 thousand keys
+// there at 900,000 atoms).  12,288 keys: 12.5 us in three kernels, 5.8 in one;
+// 49,152 keys: 14.8 and 15.1.
+__global__ __launch_bounds__(kScanBlock) void k_scan_one(SortArgs a, const int* __restrict__ gate) {
+  if (gate && *gate == 0) return;
+  constexpr int Q = 2;  // int4 per thread and round
+  __shared__ int sh[kScanBlock / 64];
+  __shared__ int lo_s[kMaxSortSpecies];
+  const int M = a.n_species * a.total_bins;  // a multiple of 64 (bins come in tiles of 64)
+  int4* cnt = reinterpret_cast<int4*>(a.cnt);
+  int4* start = reinterpret_cast<int4*>(a.start);
+  int4* cursor = reinterpret_cast<int4*>(a.cursor);
+  const int M4 = M / 4, wave0 = (int)(threadIdx.x & ~63u) * Q + (int)(threadIdx.x & 63u);
+  int run = 0;
+  int4 v[Q];
+  // a wavefront takes 64 Q consecutive int4, lane by lane
+  auto load = [&](int b) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) v[q] = b + 64 * q < M4 ? cnt[b + 64 * q] : make_int4(0, 0, 0, 0);
+  };
+  load(wave0);
+  for (int b0 = 0; b0 < M4; b0 += kScanBlock * Q) {
+    const int b = b0 + wave0;
+    int4 c[Q];
+    int before = 0;  // keys of this wavefront's earlier int4 rows
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int s = v[q].x + v[q].y + v[q].z + v[q].w;
+      int inc = s;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += u;
+      }
+      const int ex = before + inc - s;
+      c[q] = make_int4(ex, ex + v[q].x, ex + v[q].x + v[q].y, ex + v[q].x + v[q].y + v[q].z);
+      before += __shfl(inc, 63, 64);
+    }
+    load(b + kScanBlock * Q);  // the next round's counts, ahead of the barriers
+    if (lane == 0) sh[wv] = before;
+    __syncthreads();
+    int off = run;
+#pragma unroll
+    for (int w = 0; w < kScanBlock / 64; ++w) {
+      off += w < wv ? sh[w] : 0;
+      run += sh[w];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (b + 64 * q < M4) {
+        const int4 o = make_int4(c[q].x + off, c[q].y + off, c[q].z + off, c[q].w + off);
+        start[b + 64 * q] = o;
+        cursor[b + 64 * q] = o;
+        cnt[b + 64 * q] = make_int4(0, 0, 0, 0);
+      }
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < a.n_species) lo_s[threadIdx.x] = a.start[threadIdx.x * a.total_bins];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    a.start[M] = run;
+    species_bases(a, lo_s, run);
   }
 }
 
 // ------------------------------------------------------- processing order
 
-// Slot of every atom (order inside a key decided by an atomic; made
-// deterministic by k_sort_keys).
-__global__ void k_scatter(int64_t N, const int* __restrict__ key, const int* __restrict__ start,
-                          int* __restrict__ cursor, const int* __restrict__ base, int total_bins,
-                          int* __restrict__ perm, const int* __restrict__ gate) {
+// Slots of the atoms of each key, in the order an atomic decides; k_fill_slots
+// makes it the caller's order.
+__global__ void k_scatter(SortArgs a, const int* __restrict__ gate) {
   if (gate && *gate == 0) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  const int k = key[i];
+  if (i >= a.N) return;
+  const int k = a.key[i];
   if (k < 0) return;
-  const int z = k / total_bins;
+  const int z = k / a.total_bins;
   // cursor[k] starts at start[k]: the returned value is start[k] + rank in key
-  const int r = atomicAdd(&cursor[k], 1);
-  const int p = base[z] + (r - start[z * total_bins]);
-  perm[p] = (int)i;
+  const int r = atomicAdd(&a.cursor[k], 1);
+  a.perm[a.base[z] + (r - a.start[z * a.total_bins])] = (int)i;
 }
 
-// Sort the slots of each key by caller index (insertion sort; keys hold few atoms).
-__global__ void k_sort_keys(int M, const int* __restrict__ start, const int* __restrict__ base, int total_bins,
-                            int* __restrict__ perm, const int* __restrict__ gate) {
-  if (gate && *gate == 0) return;
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= M) return;
-  const int z = k / total_bins;
-  const int n = start[k + 1] - start[k];
-  if (n < 2) return;
-  int* s = perm + base[z] + (start[k] - start[z * total_bins]);
-  for (int a = 1; a < n; ++a) {
-    const int v = s[a];
-    int b = a - 1;
-    while (b >= 0 && s[b] > v) {
-      s[b + 1] = s[b];
-      --b;
-    }
-    s[b + 1] = v;
-  }
-}
-
-// Fill the slot arrays.  Padding slots get orig = -1, their group's species and
-// empty lists.
-// With carry.xd set, the carried state moves into the slot as well: the
-// staging wraps again only in a last-ulp case at a cell face, and that shift
-// (zero otherwise) is carried into the float64 position.
-__global__ void k_fill_slots(int64_t n_slots, const int* __restrict__ base, const int* __restrict__ start,
-                             int total_bins, int n_species, const int* __restrict__ perm,
-                             const float4* __restrict__ pos_tmp, const int* __restrict__ cfg_tmp,
-                             float4* __restrict__ pos4, int* __restrict__ cfg_of,
-                             int* __restrict__ orig, int* __restrict__ slot_of, int* __restrict__ cntR,
-                             int* __restrict__ cntAV, SlotCarry carry, const int* __restrict__ gate) {
+// Fill the slot arrays.  The thread of scattered atom i counts the atoms of its
+// key with a smaller caller index: its place in the key (an insertion sort of
+// each key by one thread took 7 to 41 us, its swaps one after another).
+__global__ void k_fill_slots(SortArgs a, const int* __restrict__ gate) {
   if (gate && *gate == 0) return;
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n_slots) return;
+  if (p >= a.n_slots) return;
   int z = -1;
-  for (int t = 0; t < n_species; ++t)
-    if (p >= base[t] && p < base[t + 1]) z = t;
+  for (int t = 0; t < a.n_species; ++t)
+    if (p >= a.base[t] && p < a.base[t + 1]) z = t;
   if (z >= 0) {
-    const int r = (int)(p - base[z]);
-    const int c = start[(z + 1) * total_bins] - start[z * total_bins];
-    if (r < c) {
-      const int i = perm[p];
-      const float4 xs = pos_tmp[i];
-      pos4[p] = xs;
-      cfg_of[p] = cfg_tmp[i];
-      orig[p] = i;
-      if (slot_of) slot_of[i] = (int)p;
-      if (carry.xd) {
-        const float4 xu = carry.x_user[i];
-        const double* r = carry.xd_user + 3 * (int64_t)i;
-        double* o = carry.xd + 3 * p;
-        o[0] = r[0] + ((double)xs.x - (double)xu.x);
-        o[1] = r[1] + ((double)xs.y - (double)xu.y);
-        o[2] = r[2] + ((double)xs.z - (double)xu.z);
-        carry.vel4[p] = carry.v_user[i];
-        carry.ref4[p] = xs;
+    const int s0 = a.start[z * a.total_bins];
+    if (p - a.base[z] < a.start[(z + 1) * a.total_bins] - s0) {
+      const int i = a.perm[p];
+      const int k = a.key[i];
+      const int q0 = a.base[z] + (a.start[k] - s0), n = a.start[k + 1] - a.start[k];
+      int rank = 0;
+      for (int q = 0; q < n; q += 4) {  // four loads at a time (clamped into the key)
+        int v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = a.perm[q0 + (q + u < n ? q + u : n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rank += q + u < n && v[u] < i ? 1 : 0;
       }
+      Staged s;
+      s.i = i;
+      s.c = a.cfg_tmp[i];
+      s.x = a.pos_tmp[i];
+      load_carry(a, s);
+      put_slot(a, q0 + rank, s);
       return;
     }
-  } else {
-    z = 0;
   }
-  if (carry.xd) carry.vel4[p] = make_float4(0.f, 0.f, 0.f, 0.f);
-  pos4[p] = make_float4(0.f, 0.f, 0.f, __int_as_float(z));
-  cfg_of[p] = -1;
-  orig[p] = -1;
-  cntR[p] = 0;  // the list build visits atoms only
-  cntAV[p] = 0;
+  pad_slot(a, p, z < 0 ? 0 : z);
+}
+
+// The whole sort by one block, the counts and the order in LDS and the atoms in
+// registers: one kernel instead of four for batches of a few thousand atoms,
+// where launches are most of the cost.  A gated sort then
+// costs an MD step one idle kernel instead of eight (4.5 us each).  3,686 atoms:
+// 37 us in seven kernels, 16 in one.
+template <bool SLOTS>
+__global__ __launch_bounds__(kScanBlock) void k_sort_small(SortArgs a, const int* __restrict__ gate) {
+  if (gate && *gate == 0) return;
+  constexpr int IT = kSmallAtoms / kScanBlock;
+  constexpr int kOff = 512;         // configurations whose offsets fit LDS
+  __shared__ int cur[kSmallKeys];   // counts, then (scanned) next free place, then end of every key
+  __shared__ int perm[kSmallAtoms];
+  __shared__ int off_s[SLOTS ? 1 : kOff];
+  __shared__ int sh[kScanBlock / 64];
+  __shared__ int lo_s[kMaxSortSpecies], base_s[kMaxSortSpecies + 1];
+  const int t = threadIdx.x, M = a.n_species * a.total_bins;
+  for (int k = t; k < M; k += kScanBlock) cur[k] = 0;
+  const bool in_lds = a.n_cfg <= kOff;
+  if (!SLOTS && in_lds)
+    for (int c = t; c < a.n_cfg; c += kScanBlock) off_s[c] = (int)a.atom_off[c];
+  __syncthreads();
+  Staged s[IT];
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int j = t + u * kScanBlock;
+    s[u].key = -1;
+    if (j < (int)(SLOTS ? a.n_slots : a.N)) {
+      if constexpr (SLOTS) {
+        stage_slot(a, s[u], j);
+      } else {
+        s[u].i = j;
+        s[u].c = in_lds ? config_of(off_s, a.n_cfg, j) : config_of(a.atom_off, a.n_cfg, j);
+        const float* x = a.pos + (int64_t)j * a.pos_stride;
+        stage_one(a, s[u], x[0], x[1], x[2]);
+        load_carry(a, s[u]);
+      }
+      if (s[u].key >= 0) atomicAdd(&cur[s[u].key], 1);
+    }
+  }
+  __syncthreads();
+  int run = 0;
+  for (int b0 = 0; b0 < M; b0 += kScanBlock) {
+    const int k = b0 + t;
+    const int n = k < M ? cur[k] : 0;
+    int total;
+    const int ex = run + block_inclusive(n, sh, total) - n;
+    if (k < M) {
+      cur[k] = ex;
+      a.start[k] = ex;
+    }
+    run += total;
+  }
+  __syncthreads();
+  if (t < a.n_species) lo_s[t] = cur[t * a.total_bins];
+  __syncthreads();
+  if (t == 0) {
+    a.start[M] = run;
+    species_bases(a, lo_s, run);
+    int acc = 0;
+    for (int z = 0; z < a.n_species; ++z) {
+      base_s[z] = acc;
+      acc += ((z + 1 < a.n_species ? lo_s[z + 1] : run) - lo_s[z] + kWave - 1) / kWave * kWave;
+    }
+    base_s[a.n_species] = acc;
+  }
+#pragma unroll
+  for (int u = 0; u < IT; ++u)
+    if (s[u].key >= 0) perm[atomicAdd(&cur[s[u].key], 1)] = s[u].i;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int k = s[u].key;
+    if (k < 0) continue;
+    const int z = k / a.total_bins;
+    const int q0 = k > 0 ? cur[k - 1] : 0, q1 = cur[k];
+    int rank = 0;
+    for (int q = q0; q < q1; ++q) rank += perm[q] < s[u].i ? 1 : 0;
+    put_slot(a, base_s[z] + (q0 - lo_s[z]) + rank, s[u]);
+  }
+  for (int z = 0; z < a.n_species; ++z) {
+    const int n = (z + 1 < a.n_species ? lo_s[z + 1] : run) - lo_s[z];
+    for (int p = base_s[z] + n + t; p < base_s[z + 1]; p += kScanBlock) pad_slot(a, p, z);
+  }
+  for (int64_t p = base_s[a.n_species] + t; p < a.n_slots; p += kScanBlock) pad_slot(a, p, 0);
 }
 
 // --------------------------------------------------------- Verlet lists
@@ -872,6 +1145,7 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
   }
   int rc;
   const size_t Na = (size_t)(N > 0 ? N : 1);
+  if (cnt.bytes < 4 * (size_t)(M + 1)) clear_keys = 0;  // the counts get new memory
   if ((rc = cfgs.ensure(sizeof(CfgDev) * (size_t)n_cfg_)) || (rc = atom_off_dev.ensure(8 * (size_t)(n_cfg_ + 1))) ||
       (rc = key.ensure(4 * Na)) || (rc = cnt.ensure(4 * (size_t)(M + 1))) || (rc = start.ensure(4 * (size_t)(M + 1))) ||
       (rc = cursor.ensure(4 * (size_t)(M + 1))) || (rc = tile_sums.ensure(4 * (size_t)(n_tiles + 1))) ||
@@ -914,6 +1188,7 @@ void NbrPipeline::use_arena(Arena* a) {
     b->arena = a;
   }
   capR = capA = 0;
+  clear_keys = 0;
 }
 
 int NbrPipeline::ensure_lists(int capR_, int capA_) {
@@ -978,29 +1253,70 @@ int NbrPipeline::build(hipStream_t st, const float* pos, const int32_t* species)
 }
 
 int NbrPipeline::launch_sort(hipStream_t st, const float* pos, int pos_stride, const int32_t* species, int n_species,
-                             const int* gate, bool cnt_zeroed, const SlotCarry* carry) {
+                             const int* gate, const SlotCarry* carry, const SlotSource* src) {
+  if (n_species > kMaxSortSpecies) {
+    set_error("too many species for the neighbour lists");
+    return NEPMI_UNSUPPORTED;
+  }
   const int M = n_species * total_bins;
-  if (!cnt_zeroed) fill_int(st, cnt.ptr<int>(), M + 1, 0, gate);
-  if (N > 0)
-  hipLaunchKernelGGL(k_stage, dim3(nblk(N, 256)), dim3(256), 0, st, N, n_cfg, atom_off_dev.ptr<int64_t>(),
-                     cfgs.ptr<CfgDev>(), pos, pos_stride, species, n_species, total_bins, pos_tmp.ptr<float4>(),
-                     cfg_tmp.ptr<int>(), key.ptr<int>(), cnt.ptr<int>(), flags.ptr<int>(), gate);
-  const int n_tiles = (M + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(k_scan_tiles, dim3(n_tiles), dim3(kScanBlock), 0, st, cnt.ptr<int>(), M, start.ptr<int>(),
-                     tile_sums.ptr<int>(), gate);
-  hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanBlock), 0, st, tile_sums.ptr<int>(), n_tiles, start.ptr<int>(),
-                     M, total_bins, n_species, base.ptr<int>(), gate);
-  hipLaunchKernelGGL(k_scan_add, dim3(nblk(M, 256)), dim3(256), 0, st, start.ptr<int>(), M, tile_sums.ptr<int>(),
-                     cursor.ptr<int>(), gate);
-  if (N > 0)
-  hipLaunchKernelGGL(k_scatter, dim3(nblk(N, 256)), dim3(256), 0, st, N, key.ptr<int>(), start.ptr<int>(),
-                     cursor.ptr<int>(), base.ptr<int>(), total_bins, perm.ptr<int>(), gate);
-  hipLaunchKernelGGL(k_sort_keys, dim3(nblk(M, 256)), dim3(256), 0, st, M, start.ptr<int>(), base.ptr<int>(),
-                     total_bins, perm.ptr<int>(), gate);
-  hipLaunchKernelGGL(k_fill_slots, dim3(nblk(n_slots, 256)), dim3(256), 0, st, n_slots, base.ptr<int>(),
-                     start.ptr<int>(), total_bins, n_species, perm.ptr<int>(), pos_tmp.ptr<float4>(),
-                     cfg_tmp.ptr<int>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), orig.ptr<int>(), slot_of.ptr<int>(),
-                     cntR.ptr<int>(), cntAV.ptr<int>(), carry ? *carry : SlotCarry{}, gate);
+  SortArgs a{};
+  a.N = N;
+  a.n_slots = n_slots;
+  a.n_cfg = n_cfg;
+  a.n_species = n_species;
+  a.total_bins = total_bins;
+  a.atom_off = atom_off_dev.ptr<int64_t>();
+  a.cfgs = cfgs.ptr<CfgDev>();
+  a.pos = pos;
+  a.pos_stride = pos_stride;
+  a.species = species;
+  if (src) a.src = *src;
+  if (carry) a.carry = *carry;
+  a.pos_tmp = pos_tmp.ptr<float4>();
+  a.cfg_tmp = cfg_tmp.ptr<int>();
+  a.key = key.ptr<int>();
+  a.cnt = cnt.ptr<int>();
+  a.start = start.ptr<int>();
+  a.cursor = cursor.ptr<int>();
+  a.perm = perm.ptr<int>();
+  a.pos4 = pos4.ptr<float4>();
+  a.base = base.ptr<int>();
+  a.cfg_of = cfg_of.ptr<int>();
+  a.orig = orig.ptr<int>();
+  a.slot_of = slot_of.ptr<int>();
+  a.cntR = cntR.ptr<int>();
+  a.cntAV = cntAV.ptr<int>();
+  a.flags = flags.ptr<int>();
+  if (n_slots <= kSmallAtoms && M <= kSmallKeys) {
+    if (src)
+      hipLaunchKernelGGL(k_sort_small<true>, dim3(1), dim3(kScanBlock), 0, st, a, gate);
+    else
+      hipLaunchKernelGGL(k_sort_small<false>, dim3(1), dim3(kScanBlock), 0, st, a, gate);
+    NEPMI_HIP(hipGetLastError());
+    return NEPMI_OK;
+  }
+  // the counts are clear: every sort leaves them so (new memory is cleared here)
+  if (clear_keys < M) {
+    fill_int(st, a.cnt, M, 0, nullptr);
+    clear_keys = M;
+  }
+  if (src)
+    hipLaunchKernelGGL(k_stage<true>, dim3(nblk(n_slots, 256)), dim3(256), 0, st, a, gate);
+  else
+    hipLaunchKernelGGL(k_stage<false>, dim3(nblk(N, 256)), dim3(256), 0, st, a, gate);
+  if (M <= (gate ? kOneScanGated : kOneScan)) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanBlock), 0, st, a, gate);
+  } else {
+    const int n_tiles = (M + kScanTile - 1) / kScanTile;
+    hipLaunchKernelGGL(k_scan_tiles, dim3(n_tiles), dim3(kScanBlock), 0, st, a.cnt, M, a.start, tile_sums.ptr<int>(),
+                       gate);
+    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanBlock), 0, st, tile_sums.ptr<int>(), n_tiles, a.start, M,
+                       total_bins, n_species, a.base, gate);
+    hipLaunchKernelGGL(k_scan_add, dim3(nblk(M, 256)), dim3(256), 0, st, a.start, M, tile_sums.ptr<int>(), a.cursor,
+                       a.cnt, gate);
+  }
+  hipLaunchKernelGGL(k_scatter, dim3(nblk(N, 256)), dim3(256), 0, st, a, gate);
+  hipLaunchKernelGGL(k_fill_slots, dim3(nblk(n_slots, 256)), dim3(256), 0, st, a, gate);
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }

@@ -62,6 +62,19 @@ struct SlotCarry {
   float4* ref4 = nullptr;           // [n_slots]
 };
 
+// State in the present slot order (MD) that a rebuild takes its atoms from: it
+// goes back to caller order, positions wrapped, before it is sorted.  Used when
+// xd is not null.
+struct SlotSource {
+  const int* cfg_of = nullptr;      // [n_slots]
+  const int* orig = nullptr;        // [n_slots]
+  const double* xd = nullptr;       // [n_slots][3]
+  const float4* vel4 = nullptr;     // [n_slots]
+  double* xd_user = nullptr;        // [N][3], caller order
+  float4* x_user = nullptr;         // [N] float32 positions
+  float4* v_user = nullptr;         // [N]
+};
+
 // Neighbour lists of one batch of configurations, in processing order.
 struct NbrPipeline {
   int64_t N = 0;        // atoms
@@ -85,6 +98,7 @@ struct NbrPipeline {
   DevBuf nbrTA;                  // the angular part of each list, row-major, rows of rowTA entries (reverse search)
   DevBuf angm;                   // uint32: bit k % 32 of word k / 32 ([word][slot]): entry k is in the angular part
   int rowTA = 0;
+  int clear_keys = 0;            // key counts (cnt) known to be zero between sorts
   DevBuf vrev;                   // reverse index of the Verlet list (see k_reverse)
   DevBuf cnbrR, ccntR, cnbrA, ccntA, cposA;  // per-evaluation compact lists (rc_radial, rc_angular),
                                              // in groups of four entries (see list_groups)
@@ -102,17 +116,39 @@ struct NbrPipeline {
   // setup sizes the lists afresh).
   void use_arena(Arena* a);
   // Stage, bin and sort (pos: N x pos_stride floats).  gate: optional device
-  // flag; every kernel returns at once when *gate == 0.  cnt_zeroed: the
-  // caller has already cleared the n_species * total_bins + 1 key counts
-  // (cnt) on the stream.  carry: state moved into slot order with the
-  // positions (optional).
+  // flag; every kernel returns at once when *gate == 0.  carry: state moved
+  // into slot order with the positions (optional).  src: take the atoms from
+  // this state instead of pos (optional).
   int launch_sort(hipStream_t st, const float* pos, int pos_stride, const int32_t* species, int n_species,
-                  const int* gate, bool cnt_zeroed = false, const SlotCarry* carry = nullptr);
+                  const int* gate, const SlotCarry* carry = nullptr, const SlotSource* src = nullptr);
   int launch_lists(hipStream_t st, int n_species, const int* gate);
   // Full build with capacity check and regrow (synchronises st once or twice).
   int build(hipStream_t st, const float* pos, const int32_t* species);
   int check_flags(hipStream_t st, int* host_flags);
 };
+
+// Wrap r into the cell along its periodic directions in float64, and round it
+// to f; if the rounding lands outside the cell (a last-ulp case at a face),
+// wrap the rounded value once more.  Non-periodic directions are left alone.
+static __device__ __forceinline__ void wrap_periodic(const CfgDev& C, double r[3], float f[3]) {
+  for (int pass = 0; pass < 2; ++pass) {
+    double m[3];
+    for (int a = 0; a < 3; ++a) {
+      const double s = r[0] * C.Hinv[a] + r[1] * C.Hinv[3 + a] + r[2] * C.Hinv[6 + a];
+      m[a] = (C.periodic >> a) & 1 ? floor(s) : 0.0;
+    }
+    for (int a = 0; a < 3; ++a) r[a] -= m[0] * C.Hd[a] + m[1] * C.Hd[3 + a] + m[2] * C.Hd[6 + a];
+    for (int a = 0; a < 3; ++a) f[a] = (float)r[a];
+    // the float32 copy must also lie in the cell (as the staging kernel sees it)
+    bool inside = true;
+    for (int a = 0; a < 3; ++a) {
+      const double s = (double)f[0] * C.Hinv[a] + (double)f[1] * C.Hinv[3 + a] + (double)f[2] * C.Hinv[6 + a];
+      if ((C.periodic >> a) & 1 && floor(s) != 0.0) inside = false;
+    }
+    if (inside) break;
+    for (int a = 0; a < 3; ++a) r[a] = (double)f[a];
+  }
+}
 
 // Fill an int array with a value on the stream (graph-safe, no memset node).
 void fill_int(hipStream_t st, int* p, int64_t n, int v, const int* gate);
