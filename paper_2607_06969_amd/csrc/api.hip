@@ -69,22 +69,37 @@ using namespace nepmi;
 
 namespace nepmi {
 
-int prepare_eval(EvalWork& w, const Ops* ops, const nepmi_hparams& hp, int n_cfg, const int64_t* atom_off,
-                 const double* cells, const int32_t* pbc, const float* pos, const int32_t* species, hipStream_t st, double skin) {
-  int rc;
-  // the list build's capacity check synchronises the stream once, which also
-  // completes the uploads of both setups
-  if ((rc = w.nbr.setup(n_cfg, atom_off, cells, pbc, ops->T, hp.rc_radial, hp.rc_angular, skin, st)) ||
-      (rc = w.red.setup(n_cfg, atom_off, st)) || (rc = w.nbr.build(st, pos, species)))
-    return rc;
+static int eval_buffers(EvalWork& w, const Ops* ops) {
   const NbrPipeline& nb = w.nbr;
   const size_t ns = (size_t)nb.n_slots, N = (size_t)(nb.N > 0 ? nb.N : 1);
+  int rc;
   if ((rc = w.fp.ensure(4 * ns * (size_t)ops->NANG)) || (rc = w.aR.ensure(4 * ns * (size_t)(ops->T * ops->BR))) ||
       (rc = w.Ei.ensure(4 * N)) || (rc = w.frad.ensure(16 * ns)) ||
       (rc = w.amask.ensure(8 * ns * (size_t)((nb.capA + 63) / 64))) || (rc = w.fA.ensure(16 * ns * (size_t)nb.capA)) ||
       (rc = w.Wi.ensure(36 * N)) || (rc = w.Eproc.ensure(4 * ns)))
     return rc;
   return NEPMI_OK;
+}
+
+int prepare_start(EvalWork& w, const Ops* ops, const nepmi_hparams& hp, int n_cfg, const int64_t* atom_off,
+                  const double* cells, const int32_t* pbc, const float* pos, const int32_t* species, hipStream_t st,
+                  double skin) {
+  int rc;
+  // the flags of an earlier build whose call ended in an error: its upload may
+  // still read the pinned tables
+  if (w.nbr.waiting) {
+    NEPMI_HIP(hipDeviceSynchronize());
+    w.nbr.waiting = false;
+  }
+  if ((rc = w.nbr.setup(n_cfg, atom_off, cells, pbc, ops->T, hp.rc_radial, hp.rc_angular, skin)) ||
+      (rc = w.red.setup(n_cfg, atom_off, w.nbr.up)) || (rc = eval_buffers(w, ops)))
+    return rc;
+  return w.nbr.build_start(st, pos, species);
+}
+
+int prepare_end(EvalWork& w, const Ops* ops, hipStream_t st, bool& again) {
+  const int rc = w.nbr.build_end(st, again);
+  return rc || !again ? rc : eval_buffers(w, ops);
 }
 
 NepIO eval_io(EvalWork& w, const nepmi_hparams& hp, float* Fuser, float4* Fproc, float* qout) {
@@ -128,46 +143,60 @@ NepIO eval_io(EvalWork& w, const nepmi_hparams& hp, float* Fuser, float4* Fproc,
 }
 
 // E, F, V of a prepared batch: descriptors + network, pair forces, gather,
-// float64 sums, optional per-atom copies.
+// float64 sums, optional per-atom values.
 int run_eval(EvalWork& w, const nepmi_model* m, float* dev_forces, double* dev_energy, double* dev_virial,
              float* dev_atom_energy, float* dev_atom_virial, hipStream_t st) {
   NepIO io = eval_io(w, m->hp, dev_forces, nullptr, nullptr);
+  // the per-atom values go straight to the caller if asked for
+  if (dev_atom_energy) io.Ei = dev_atom_energy;
+  if (dev_atom_virial) io.Wi = dev_atom_virial;
   const float* P = m->params.ptr<float>();
   int rc;
   if ((rc = m->ops->desc(st, io, P, true, m->vdesc)) || (rc = m->ops->force(st, io, P, m->vforce)) ||
       (rc = m->ops->gather(st, io, m->vgather)))
     return rc;
-  if ((rc = w.red.run(st, io.Ei, io.Wi, nullptr, dev_energy, dev_virial, nullptr))) return rc;
-  const size_t N = (size_t)w.nbr.N;
-  if (dev_atom_energy && N) NEPMI_HIP(hipMemcpyAsync(dev_atom_energy, io.Ei, 4 * N, hipMemcpyDeviceToDevice, st));
-  if (dev_atom_virial && N) NEPMI_HIP(hipMemcpyAsync(dev_atom_virial, io.Wi, 36 * N, hipMemcpyDeviceToDevice, st));
-  return NEPMI_OK;
+  return w.red.run(st, io.Ei, io.Wi, nullptr, dev_energy, dev_virial, nullptr);
 }
 
 }  // namespace nepmi
 
-int nepmi_model::prepare(int n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc, const float* pos,
-                         const int32_t* species, hipStream_t st, double skin, bool may_reuse) {
-  // periodicity flags as given (null: every direction periodic)
+// periodicity flags as given (null: every direction periodic)
+static std::vector<int32_t> pbc_flags(int n_cfg, const int32_t* pbc) {
   std::vector<int32_t> per(3 * (size_t)(n_cfg > 0 ? n_cfg : 0), 1);
   if (pbc) per.assign(pbc, pbc + per.size());
-  if (n_cfg >= 1 && atom_off && cells && reuse_lists && may_reuse && last.valid && last.pos == pos &&
-      last.species == species && last.skin == skin && last.off.size() == (size_t)n_cfg + 1 &&
-      std::equal(last.off.begin(), last.off.end(), atom_off) &&
-      std::equal(last.cells.begin(), last.cells.end(), cells) && last.pbc == per)
-    return NEPMI_OK;
+  return per;
+}
+
+bool nepmi_model::kept(int n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc, const float* pos,
+                       const int32_t* species, double skin) const {
+  return n_cfg >= 1 && atom_off && cells && reuse_lists && last.valid && last.pos == pos && last.species == species &&
+         last.skin == skin && last.off.size() == (size_t)n_cfg + 1 &&
+         std::equal(last.off.begin(), last.off.end(), atom_off) &&
+         std::equal(last.cells.begin(), last.cells.end(), cells) && last.pbc == pbc_flags(n_cfg, pbc);
+}
+
+void nepmi_model::keep(int n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc, const float* pos,
+                       const int32_t* species, double skin) {
+  if (!reuse_lists) return;
+  last.valid = true;
+  last.pos = pos;
+  last.species = species;
+  last.skin = skin;
+  last.off.assign(atom_off, atom_off + n_cfg + 1);
+  last.cells.assign(cells, cells + 9 * (size_t)n_cfg);
+  last.pbc = pbc_flags(n_cfg, pbc);
+}
+
+int nepmi_model::prepare(int n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc, const float* pos,
+                         const int32_t* species, hipStream_t st, double skin, bool may_reuse) {
+  if (may_reuse && kept(n_cfg, atom_off, cells, pbc, pos, species, skin)) return NEPMI_OK;
   last.valid = false;
   int rc;
-  if ((rc = prepare_eval(*this, ops, hp, n_cfg, atom_off, cells, pbc, pos, species, st, skin))) return rc;
-  if (may_reuse) {
-    last.valid = true;
-    last.pos = pos;
-    last.species = species;
-    last.skin = skin;
-    last.off.assign(atom_off, atom_off + n_cfg + 1);
-    last.cells.assign(cells, cells + 9 * (size_t)n_cfg);
-    last.pbc = per;
-  }
+  bool again = false;
+  if ((rc = prepare_start(*this, ops, hp, n_cfg, atom_off, cells, pbc, pos, species, st, skin)) ||
+      (rc = prepare_end(*this, ops, st, again)))
+    return rc;
+  if (may_reuse) keep(n_cfg, atom_off, cells, pbc, pos, species, skin);
   return NEPMI_OK;
 }
 
@@ -250,9 +279,9 @@ int nepmi_compute(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, const 
     return NEPMI_INVALID_ARG;
   }
   hipStream_t st = (hipStream_t)stream;
-  int rc = m->prepare(n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st);
-  if (rc) return rc;
-  return run_eval(*m, m, dev_forces, dev_energy, dev_virial, dev_atom_energy, dev_atom_virial, st);
+  return m->with_lists(n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st, [&]() -> int {
+    return run_eval(*m, m, dev_forces, dev_energy, dev_virial, dev_atom_energy, dev_atom_virial, st);
+  });
 }
 
 int nepmi_descriptors(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc,
@@ -262,10 +291,9 @@ int nepmi_descriptors(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, co
     return NEPMI_INVALID_ARG;
   }
   hipStream_t st = (hipStream_t)stream;
-  int rc = m->prepare(n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st);
-  if (rc) return rc;
-  NepIO io = m->io(nullptr, nullptr, dev_q);
-  return m->ops->desc(st, io, m->params.ptr<float>(), false, m->vdesc);
+  return m->with_lists(n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st, [&]() -> int {
+    return m->ops->desc(st, m->io(nullptr, nullptr, dev_q), m->params.ptr<float>(), false, m->vdesc);
+  });
 }
 
 }  // extern "C"

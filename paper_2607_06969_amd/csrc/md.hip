@@ -450,9 +450,9 @@ int nepmi_md_create(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
   md->mc.dt = (float)dt_fs;
   md->mc.half_skin2 = (float)(0.25 * skin * skin);
   NbrPipeline& nb = md->nbr;
-  if ((rc = nb.setup(n_cfg, atom_off, cells, pbc, md->n_species, m->hp.rc_radial, m->hp.rc_angular, skin, st)))
+  if ((rc = nb.setup(n_cfg, atom_off, cells, pbc, md->n_species, m->hp.rc_radial, m->hp.rc_angular, skin)))
     return fail(rc);
-  if ((rc = md->red.setup(n_cfg, atom_off, st))) return fail(rc);
+  if ((rc = md->red.setup(n_cfg, atom_off, nb.up))) return fail(rc);
   const int64_t N = nb.N, ns = nb.n_slots;
   const size_t Na = (size_t)(N > 0 ? N : 1);
   if ((rc = md->species_user.ensure(4 * Na)) || (rc = md->xd_user.ensure(24 * Na)) ||
@@ -466,12 +466,12 @@ int nepmi_md_create(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
       (rc = md->snap_xd.ensure(24 * Na)) || (rc = md->snap_x.ensure(16 * Na)) || (rc = md->snap_v.ensure(16 * Na)) ||
       (rc = md->snap_cnt.ensure(16)))
     return fail(rc);
+  if ((rc = nb.up.run(st, nb.flags.ptr<int>(), kFlagCount))) return fail(rc);
   if (hipMemcpyAsync(md->species_user.p, dev_species, 4 * (size_t)N, hipMemcpyDeviceToDevice, st) != hipSuccess)
     return fail(hip_fail(hipGetLastError(), "hipMemcpyAsync(species)"));
   hipLaunchKernelGGL(k_md_init, dim3(nb256(N > 0 ? N : 1)), dim3(256), 0, st, N, n_cfg, nb.atom_off_dev.ptr<int64_t>(),
                      nb.cfgs.ptr<CfgDev>(), dev_pos, dev_vel, md->xd_user.ptr<Dbl3>(), md->x_user.ptr<float4>(),
                      md->v_user.ptr<float4>());
-  fill_int(st, nb.flags.ptr<int>(), kFlagCount, 0, nullptr);
   fill_int(st, md->counters.ptr<int>(), 4, 0, nullptr);
   // first build, with capacity growth and a margin for the density
   // fluctuations of the run

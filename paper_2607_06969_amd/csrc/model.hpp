@@ -58,9 +58,15 @@ struct EvalWork {
 };
 
 // Neighbour lists (pairs within the cutoffs + skin), work buffers and
-// reduction plan of a batch in `w`.
-int prepare_eval(EvalWork& w, const Ops* ops, const nepmi_hparams& hp, int n_cfg, const int64_t* atom_off,
-                 const double* cells, const int32_t* pbc, const float* pos, const int32_t* species, hipStream_t st, double skin);
+// reduction plan of a batch in `w`: launched by prepare_start; prepare_end
+// waits for the lists' flags and reports what is wrong with the input.  Work
+// on the lists can be launched between the two: it stays within its buffers
+// whatever the flags say, and has to be launched again if prepare_end says so
+// (the lists were too short and have been rebuilt).
+int prepare_start(EvalWork& w, const Ops* ops, const nepmi_hparams& hp, int n_cfg, const int64_t* atom_off,
+                  const double* cells, const int32_t* pbc, const float* pos, const int32_t* species, hipStream_t st,
+                  double skin);
+int prepare_end(EvalWork& w, const Ops* ops, hipStream_t st, bool& again);
 // Kernel arguments of an evaluation on `w` (optional caller-order forces,
 // slot-order forces and descriptors).
 NepIO eval_io(EvalWork& w, const nepmi_hparams& hp, float* Fuser, float4* Fproc, float* qout);
@@ -80,9 +86,31 @@ struct nepmi_model : nepmi::EvalWork {
   // Prepare the batch: neighbour lists (pairs within the cutoffs + skin),
   // work buffers and reduction plan.  With reuse_lists set and may_reuse, a
   // batch identical to the previous one (same sizes, cells and device
-  // pointers) keeps what the previous call prepared.
+  // pointers) keeps what the previous call prepared.  launch() launches the
+  // work on them, before the lists' flags are waited for (a launch after the
+  // wait would leave the GPU idle for a round trip to the host), and once more
+  // if the lists had to be rebuilt.
+  template <class L>
+  int with_lists(int n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc, const float* pos,
+                 const int32_t* species, hipStream_t st, L&& launch) {
+    if (kept(n_cfg, atom_off, cells, pbc, pos, species, 0.0)) return launch();
+    last.valid = false;
+    int rc;
+    bool again = false;
+    if ((rc = nepmi::prepare_start(*this, ops, hp, n_cfg, atom_off, cells, pbc, pos, species, st, 0.0)) ||
+        (rc = launch()) || (rc = nepmi::prepare_end(*this, ops, st, again)) || (again && (rc = launch())))
+      return rc;
+    keep(n_cfg, atom_off, cells, pbc, pos, species, 0.0);
+    return NEPMI_OK;
+  }
+  // The same with the lists complete on return and no work launched.
   int prepare(int n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc, const float* pos, const int32_t* species,
               hipStream_t st, double skin = 0.0, bool may_reuse = true);
+  // Whether the batch is the one whose lists are kept; remember the batch.
+  bool kept(int n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc, const float* pos,
+            const int32_t* species, double skin) const;
+  void keep(int n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc, const float* pos,
+            const int32_t* species, double skin);
   bool reuse_lists = false;
   struct {
     bool valid = false;

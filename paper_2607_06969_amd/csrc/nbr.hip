@@ -20,6 +20,7 @@
 #include "nbr.hpp"
 
 #include <algorithm>
+#include <cstring>
 
 namespace nepmi {
 
@@ -1050,8 +1051,80 @@ static void cell_geometry(const double* H, double w[3], double Hi[9], double& de
   }
 }
 
+int PinBuf::ensure(size_t n) {
+  if (n <= bytes && p) return NEPMI_OK;
+  if (p) (void)hipHostFree(p);
+  p = nullptr;
+  bytes = 0;
+  const size_t want = n < 4096 ? 4096 : n + n / 2;
+  NEPMI_HIP(hipHostMalloc(&p, want, hipHostMallocDefault));
+  bytes = want;
+  return NEPMI_OK;
+}
+
+PinBuf::~PinBuf() {
+  if (p) (void)hipHostFree(p);
+}
+
+struct UploadArgs {
+  struct {
+    const uint4* src;
+    uint4* dst;
+    int64_t n;
+  } seg[Uploader::kMost];
+  int n_seg;
+  int* clear;
+  int n_clear;
+};
+
+__global__ void k_upload(UploadArgs a) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  if (t < a.n_clear) a.clear[t] = 0;
+#pragma unroll
+  for (int s = 0; s < Uploader::kMost; ++s)
+    if (s < a.n_seg)
+      for (int64_t i = t; i < a.seg[s].n; i += step) a.seg[s].dst[i] = a.seg[s].src[i];
+}
+
+int Uploader::add(const void* src, size_t bytes, DevBuf& dst) {
+  if (tables.size() >= (size_t)kMost) {
+    set_error("too many tables in one upload");
+    return NEPMI_INVALID_ARG;
+  }
+  const int rc = dst.ensure((bytes + 15) / 16 * 16);
+  if (rc) return rc;
+  tables.push_back({src, &dst, bytes});
+  return NEPMI_OK;
+}
+
+int Uploader::run(hipStream_t st, int* clear, int n_clear) {
+  size_t total = 0;
+  for (const Table& t : tables) total += (t.bytes + 15) / 16 * 16;
+  const int rc = pin.ensure(total);
+  if (rc) return rc;
+  UploadArgs a{};
+  char* h = static_cast<char*>(pin.p);
+  for (const Table& t : tables) {
+    const size_t n = (t.bytes + 15) / 16;
+    memcpy(h, t.src, t.bytes);
+    a.seg[a.n_seg].src = reinterpret_cast<const uint4*>(h);
+    a.seg[a.n_seg].dst = t.dst->ptr<uint4>();
+    a.seg[a.n_seg].n = (int64_t)n;
+    ++a.n_seg;
+    h += 16 * n;
+  }
+  tables.clear();
+  a.clear = clear;
+  a.n_clear = n_clear;
+  const int64_t want = (int64_t)(total / 16 + 255) / 256;
+  const unsigned blocks = (unsigned)(want < 1 ? 1 : (want > 256 ? 256 : want));
+  hipLaunchKernelGGL(k_upload, dim3(blocks), dim3(256), 0, st, a);
+  NEPMI_HIP(hipGetLastError());
+  return NEPMI_OK;
+}
+
 int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells, const int32_t* pbc, int n_species_,
-                       double rcR, double rcA, double skin_, hipStream_t st) {
+                       double rcR, double rcA, double skin_) {
   if (n_cfg_ < 1 || !atom_off || !cells) {
     set_error("n_cfg must be >= 1 and atom_off, cells non-null");
     return NEPMI_INVALID_ARG;
@@ -1146,7 +1219,10 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
   int rc;
   const size_t Na = (size_t)(N > 0 ? N : 1);
   if (cnt.bytes < 4 * (size_t)(M + 1)) clear_keys = 0;  // the counts get new memory
-  if ((rc = cfgs.ensure(sizeof(CfgDev) * (size_t)n_cfg_)) || (rc = atom_off_dev.ensure(8 * (size_t)(n_cfg_ + 1))) ||
+  // uploaded from the members
+  up.tables.clear();
+  if ((rc = up.add(host_cfgs.data(), sizeof(CfgDev) * (size_t)n_cfg_, cfgs)) ||
+      (rc = up.add(host_off.data(), 8 * (size_t)(n_cfg_ + 1), atom_off_dev)) ||
       (rc = key.ensure(4 * Na)) || (rc = cnt.ensure(4 * (size_t)(M + 1))) || (rc = start.ensure(4 * (size_t)(M + 1))) ||
       (rc = cursor.ensure(4 * (size_t)(M + 1))) || (rc = tile_sums.ensure(4 * (size_t)(n_tiles + 1))) ||
       (rc = base.ensure(4 * (size_t)(n_species_ + 1))) || (rc = perm.ensure(4 * (size_t)n_slots)) ||
@@ -1158,10 +1234,6 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
       (rc = ccntA.ensure(4 * (size_t)n_slots)) ||
       (rc = flags.ensure(4 * kFlagCount)))
     return rc;
-  // uploaded from the members, which outlive the asynchronous copies (the
-  // caller synchronises the stream before the next setup)
-  NEPMI_HIP(hipMemcpyAsync(cfgs.p, host_cfgs.data(), sizeof(CfgDev) * (size_t)n_cfg_, hipMemcpyHostToDevice, st));
-  NEPMI_HIP(hipMemcpyAsync(atom_off_dev.p, host_off.data(), 8 * (size_t)(n_cfg_ + 1), hipMemcpyHostToDevice, st));
   if (capR == 0) {
     // initial capacity from the densest configuration
     double dmax = 0.0;
@@ -1215,9 +1287,8 @@ int NbrPipeline::ensure_lists(int capR_, int capA_) {
   return NEPMI_OK;
 }
 
-int NbrPipeline::check_flags(hipStream_t st, int* hf) {
-  NEPMI_HIP(hipMemcpyAsync(hf, flags.p, sizeof(int) * kFlagCount, hipMemcpyDeviceToHost, st));
-  NEPMI_HIP(hipStreamSynchronize(st));
+// What the flags say of the input.
+static int flag_errors(const int* hf) {
   if (hf[kFlagNaN]) {
     set_error("non-finite position");
     return NEPMI_NAN_DETECTED;
@@ -1229,14 +1300,71 @@ int NbrPipeline::check_flags(hipStream_t st, int* hf) {
   return NEPMI_OK;
 }
 
-int NbrPipeline::build(hipStream_t st, const float* pos, const int32_t* species) {
-  fill_int(st, flags.ptr<int>(), kFlagCount, 0, nullptr);
-  int rc = launch_sort(st, pos, 3, species, n_species, nullptr);
+int NbrPipeline::check_flags(hipStream_t st, int* hf) {
+  NEPMI_HIP(hipMemcpyAsync(hf, flags.p, sizeof(int) * kFlagCount, hipMemcpyDeviceToHost, st));
+  NEPMI_HIP(hipStreamSynchronize(st));
+  return flag_errors(hf);
+}
+
+// The flags into pinned host memory, then the number of the build.
+__global__ void k_mail_flags(const int* __restrict__ flags, int* __restrict__ mail, int number) {
+  if (threadIdx.x < kFlagCount) mail[threadIdx.x] = flags[threadIdx.x];
+  __threadfence_system();
+  __builtin_amdgcn_wave_barrier();
+  if (threadIdx.x == 0) __hip_atomic_store(&mail[kFlagCount], number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+static void mail_flags(hipStream_t st, const int* flags, int* mail, int number) {
+  hipLaunchKernelGGL(k_mail_flags, dim3(1), dim3(kWave), 0, st, flags, mail, number);
+}
+
+int NbrPipeline::build_start(hipStream_t st, const float* pos, const int32_t* species) {
+  int rc = mail.ensure(sizeof(int) * (kFlagCount + 1));
   if (rc) return rc;
+  if (builds == 0) static_cast<int*>(mail.p)[kFlagCount] = 0;
+  waiting = true;
+  builds = builds == INT32_MAX ? 1 : builds + 1;
+  if ((rc = up.run(st, flags.ptr<int>(), kFlagCount)) || (rc = launch_sort(st, pos, 3, species, n_species, nullptr)) ||
+      (rc = launch_lists(st, n_species, nullptr)))
+    return rc;
+  mail_flags(st, flags.ptr<int>(), static_cast<int*>(mail.p), builds);
+  NEPMI_HIP(hipGetLastError());
+  return NEPMI_OK;
+}
+
+// Wait until the stream has delivered the flags of build `number`.  The host
+// watches the pinned word (a synchronisation of the stream would also wait for
+// the work launched behind the lists); every so often it asks the stream, which
+// ends the wait if the stream has failed or finished.
+static int await_mail(hipStream_t st, const int* mail, int number) {
+  for (unsigned n = 1; __atomic_load_n(&mail[kFlagCount], __ATOMIC_ACQUIRE) != number; ++n) {
+    if (n % 16384) {
+      __builtin_ia32_pause();
+      continue;
+    }
+    const hipError_t e = hipStreamQuery(st);
+    if (e == hipErrorNotReady) {
+      (void)hipGetLastError();
+      continue;
+    }
+    if (e != hipSuccess) return hip_fail(e, "hipStreamQuery (neighbour lists)");
+    if (__atomic_load_n(&mail[kFlagCount], __ATOMIC_ACQUIRE) == number) break;
+    set_error("the neighbour build ended without its flags");
+    return NEPMI_HIP_ERROR;
+  }
+  return NEPMI_OK;
+}
+
+int NbrPipeline::build_end(hipStream_t st, bool& regrown) {
+  regrown = false;
+  int* m = static_cast<int*>(mail.p);
   for (int attempt = 0; attempt < 2; ++attempt) {
-    if ((rc = launch_lists(st, n_species, nullptr))) return rc;
+    int rc = await_mail(st, m, builds);
+    if (rc) return rc;
+    waiting = false;
     int hf[kFlagCount];
-    if ((rc = check_flags(st, hf))) return rc;
+    memcpy(hf, m, sizeof hf);
+    if ((rc = flag_errors(hf))) return rc;
     if (!hf[kFlagOverflow]) {
       if (hf[kFlagAsym]) {
         set_error("neighbour list is not symmetric");
@@ -1244,9 +1372,16 @@ int NbrPipeline::build(hipStream_t st, const float* pos, const int32_t* species)
       }
       return NEPMI_OK;
     }
+    if (attempt) break;
     // grow to the largest list seen plus a margin and rebuild the lists
+    regrown = true;
     if ((rc = ensure_lists(hf[kFlagMaxR] + 8, hf[kFlagMaxA] + 8))) return rc;
     fill_int(st, flags.ptr<int>(), kFlagCount, 0, nullptr);
+    if ((rc = launch_lists(st, n_species, nullptr))) return rc;
+    builds = builds == INT32_MAX ? 1 : builds + 1;
+    waiting = true;
+    mail_flags(st, flags.ptr<int>(), m, builds);
+    NEPMI_HIP(hipGetLastError());
   }
   set_error("neighbour capacity overflow after regrow");
   return NEPMI_NEIGHBOR_OVERFLOW;

@@ -50,6 +50,36 @@ struct DevBuf {
   DevBuf& operator=(const DevBuf&) = delete;
 };
 
+// Pinned host memory that grows on demand.
+struct PinBuf {
+  void* p = nullptr;
+  size_t bytes = 0;
+  int ensure(size_t n);
+  ~PinBuf();
+  PinBuf() = default;
+  PinBuf(const PinBuf&) = delete;
+  PinBuf& operator=(const PinBuf&) = delete;
+};
+
+// Host tables on their way to device buffers: copied into pinned memory, then
+// moved by one kernel (a copy call for each table costs the host some 10 us and
+// the stream 5).  The pinned memory is free again once the stream has passed
+// the kernel; the owner waits for that before the next upload.
+struct Uploader {
+  static constexpr int kMost = 4;
+  struct Table {
+    const void* src;
+    DevBuf* dst;
+    size_t bytes;
+  };
+  PinBuf pin;
+  std::vector<Table> tables;
+  // dst receives the bytes (and is sized for them)
+  int add(const void* src, size_t bytes, DevBuf& dst);
+  // launch the upload of the added tables, clearing n_clear ints at clear
+  int run(hipStream_t st, int* clear, int n_clear);
+};
+
 // State that a rebuild moves from caller order into the new slot order along
 // with the positions (MD: float64 positions, velocities, and the positions the
 // new lists are built from, as the drift reference).  Used when xd is not null.
@@ -103,13 +133,17 @@ struct NbrPipeline {
   DevBuf cnbrR, ccntR, cnbrA, ccntA, cposA;  // per-evaluation compact lists (rc_radial, rc_angular),
                                              // in groups of four entries (see list_groups)
   DevBuf flags;
+  Uploader up;
+  PinBuf mail;          // the flags as the host reads them, then the number of the build they belong to
+  int builds = 0;       // number of the last build started
+  bool waiting = false; // its flags have not been read yet
 
   // Host-side setup of a batch: validates the cells, computes bins, sizes
-  // buffers and uploads the configuration table.  pbc: host int32[3 n_cfg]
-  // (1 periodic, 0 not, per lattice vector) or null (all periodic).  Returns
-  // NEPMI_* codes.
+  // buffers and adds the configuration tables to `up`.  pbc: host int32[3
+  // n_cfg] (1 periodic, 0 not, per lattice vector) or null (all periodic).
+  // Returns NEPMI_* codes.
   int setup(int n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc, int n_species, double rcR,
-            double rcA, double skin, hipStream_t st);
+            double rcA, double skin);
   // Sizes the lists for capR x capA entries per slot.
   int ensure_lists(int capR_, int capA_);
   // Take every buffer from `a` from now on (releases what is held; the next
@@ -122,8 +156,13 @@ struct NbrPipeline {
   int launch_sort(hipStream_t st, const float* pos, int pos_stride, const int32_t* species, int n_species,
                   const int* gate, const SlotCarry* carry = nullptr, const SlotSource* src = nullptr);
   int launch_lists(hipStream_t st, int n_species, const int* gate);
-  // Full build with capacity check and regrow (synchronises st once or twice).
-  int build(hipStream_t st, const float* pos, const int32_t* species);
+  // Full build, in two parts so that work on the lists can be launched between
+  // them: build_start launches the upload, sort and lists; build_end waits for
+  // the flags, reports what the build found wrong, and builds lists that were
+  // too short again with a larger capacity (regrown: work launched on the first
+  // ones, which kept within the capacity, is void).
+  int build_start(hipStream_t st, const float* pos, const int32_t* species);
+  int build_end(hipStream_t st, bool& regrown);
   int check_flags(hipStream_t st, int* host_flags);
 };
 

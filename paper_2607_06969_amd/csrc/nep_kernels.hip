@@ -267,6 +267,9 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     // with a reverse position) is in the compact angular list
     uint64_t mword = 0;
     int ka = 0;  // position in the angular part of the list
+    // words the mask holds (a list cut off at its capacity, which is rebuilt
+    // before its results are used, may have more angular entries)
+    const int kaMax = (capA + 63) / 64 * 64;
     walk_groups<true>(reinterpret_cast<const uint4*>(nbrR), n_slots, p, n, pos4, NoPre{},
                       [&](int, uint32_t e, float4 xq, uint32_t rvk, int) {
       const PairVec v = pair_vec(e, xq, xi, Hc, itab);
@@ -306,13 +309,13 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
         }
       }
       if (in_ang_part && (++ka & 63) == 0) {
-        *mw = mword;
+        if (ka <= kaMax) *mw = mword;
         mw += n_slots;
         mword = 0;
       }
     }, reinterpret_cast<const uint4*>(vrev));
     // the last, partly filled mask word and groups
-    if (ka & 63) *mw = mword;
+    if ((ka & 63) && ka < kaMax) *mw = mword;
     if (nR & 3) *wr = front4(gr, nR & 3);
     if (nA & 3) {
       *wa = front4(ga, nA & 3);

@@ -134,6 +134,9 @@ __global__ __launch_bounds__(kWave) void k_desc_wave(NepIO io, const float* __re
   load_cell(io.cfgs, c, Hc);
   const float rcR_inv = 1.0f / io.cut.rcR, rcA_inv = 1.0f / io.cut.rcA;
   const int n = io.cntR[p];
+  // entries the mask's words hold (a list cut off at its capacity, which is
+  // rebuilt before its results are used, may have more)
+  const int kaMax = (io.capA + 63) / 64 * 64;
   lds_fence();
 
   // ---- filter the Verlet list into the pairs inside the two cutoffs, 64
@@ -194,7 +197,7 @@ __global__ __launch_bounds__(kWave) void k_desc_wave(NepIO io, const float* __re
     const int sh = ka0 & 63;
     mword |= bits << sh;
     if ((ka0 + np) >> 6 != ka0 >> 6) {
-      if (lane == 0) io.amask[(int64_t)(ka0 >> 6) * ns + p] = mword;
+      if (lane == 0 && ka0 < kaMax) io.amask[(int64_t)(ka0 >> 6) * ns + p] = mword;
       mword = sh ? bits >> (64 - sh) : 0;
     }
     ka0 += np;
@@ -247,7 +250,7 @@ __global__ __launch_bounds__(kWave) void k_desc_wave(NepIO io, const float* __re
   }
   // the last, partly filled mask word and groups (they repeat the last entry)
   if (lane == 0) {
-    if (ka0 & 63) io.amask[(int64_t)(ka0 >> 6) * ns + p] = mword;
+    if ((ka0 & 63) && ka0 < kaMax) io.amask[(int64_t)(ka0 >> 6) * ns + p] = mword;
     io.ccR[p] = nR;
     io.ccA[p] = nA;
   }

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kRedBlock) void k_reduce_final(int n_cfg, const int
   if (v == 10 && Kout) Kout[c] = acc[0];
 }
 
-int Reducer::setup(int n_cfg_, const int64_t* atom_off, hipStream_t st) {
+int Reducer::setup(int n_cfg_, const int64_t* atom_off, Uploader& up) {
   std::vector<RedItem>& items = host_items;
   std::vector<int>& start = host_start;
   items.clear();
@@ -103,11 +103,10 @@ int Reducer::setup(int n_cfg_, const int64_t* atom_off, hipStream_t st) {
   n_cfg = n_cfg_;
   n_items = (int)items.size();
   int rc;
-  if ((rc = items_dev.ensure(sizeof(RedItem) * items.size())) || (rc = start_dev.ensure(4 * start.size())) ||
+  if ((rc = up.add(items.data(), sizeof(RedItem) * items.size(), items_dev)) ||
+      (rc = up.add(start.data(), 4 * start.size(), start_dev)) ||
       (rc = part.ensure(sizeof(double) * kRedValues * items.size())))
     return rc;
-  NEPMI_HIP(hipMemcpyAsync(items_dev.p, items.data(), sizeof(RedItem) * items.size(), hipMemcpyHostToDevice, st));
-  NEPMI_HIP(hipMemcpyAsync(start_dev.p, start.data(), 4 * start.size(), hipMemcpyHostToDevice, st));
   return NEPMI_OK;
 }
 

@@ -232,11 +232,13 @@ int nepmi_backward_params(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off
     return NEPMI_INVALID_ARG;
   }
   hipStream_t st = (hipStream_t)stream;
-  int rc;
-  if ((rc = m->prepare(n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st)) || (rc = ensure_train(m))) return rc;
-  // the descriptor kernel writes the per-evaluation compact pair lists
-  if ((rc = m->ops->desc(st, m->io(nullptr, nullptr, nullptr), m->params.ptr<float>(), false, m->vdesc))) return rc;
-  return run_backward(m, st, dev_ebar, dev_lambda, dev_mu, dev_grad);
+  return m->with_lists(n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st, [&]() -> int {
+    int rc;
+    if ((rc = ensure_train(m))) return rc;
+    // the descriptor kernel writes the per-evaluation compact pair lists
+    if ((rc = m->ops->desc(st, m->io(nullptr, nullptr, nullptr), m->params.ptr<float>(), false, m->vdesc))) return rc;
+    return run_backward(m, st, dev_ebar, dev_lambda, dev_mu, dev_grad);
+  });
 }
 
 int nepmi_loss_grad(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc,
@@ -249,41 +251,43 @@ int nepmi_loss_grad(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
     return NEPMI_INVALID_ARG;
   }
   hipStream_t st = (hipStream_t)stream;
-  int rc;
-  if ((rc = m->prepare(n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st)) || (rc = ensure_train(m))) return rc;
-  TrainBufs& t = m->tr;
-  // forward: E, F, V
-  NepIO io = m->io(t.F.ptr<float>(), nullptr, nullptr);
-  const float* P = m->params.ptr<float>();
-  if ((rc = m->ops->desc(st, io, P, true, m->vdesc)) || (rc = m->ops->force(st, io, P, m->vforce)) || (rc = m->ops->gather(st, io, m->vgather)) ||
-      (rc = m->red.run(st, io.Ei, io.Wi, nullptr, t.E.ptr<double>(), t.V.ptr<double>(), nullptr)))
-    return rc;
-  // loss and seeds
-  TrainSeedArgs a;
-  a.items = m->red.items_dev.ptr<RedItem>();
-  a.n_items = m->red.n_items;
-  a.item_start = m->red.start_dev.ptr<int>();
-  a.n_cfg = n_cfg;
-  a.form = loss_form;
-  a.w[0] = weights[0];
-  a.w[1] = weights[1];
-  a.w[2] = weights[2];
-  a.inv_3ntot = m->nbr.N > 0 ? 1.0 / (3.0 * (double)m->nbr.N) : 0.0;
-  a.off = m->nbr.atom_off_dev.ptr<int64_t>();
-  a.F = t.F.ptr<float>();
-  a.Fref = dev_F_ref;
-  a.E = t.E.ptr<double>();
-  a.Eref = dev_E_ref;
-  a.V = t.V.ptr<double>();
-  a.Vref = dev_V_ref;
-  a.lam = t.lam.ptr<float>();
-  a.ebar = t.ebar.ptr<double>();
-  a.mu = t.mu.ptr<double>();
-  a.partF = t.partF.ptr<double>();
-  a.loss = dev_loss;
-  if ((rc = m->ops->seeds(st, a))) return rc;
-  if (!dev_grad) return NEPMI_OK;
-  return run_backward(m, st, t.ebar.ptr<double>(), t.lam.ptr<float>(), t.mu.ptr<double>(), dev_grad);
+  return m->with_lists(n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st, [&]() -> int {
+    int rc;
+    if ((rc = ensure_train(m))) return rc;
+    TrainBufs& t = m->tr;
+    // forward: E, F, V
+    NepIO io = m->io(t.F.ptr<float>(), nullptr, nullptr);
+    const float* P = m->params.ptr<float>();
+    if ((rc = m->ops->desc(st, io, P, true, m->vdesc)) || (rc = m->ops->force(st, io, P, m->vforce)) || (rc = m->ops->gather(st, io, m->vgather)) ||
+        (rc = m->red.run(st, io.Ei, io.Wi, nullptr, t.E.ptr<double>(), t.V.ptr<double>(), nullptr)))
+      return rc;
+    // loss and seeds
+    TrainSeedArgs a;
+    a.items = m->red.items_dev.ptr<RedItem>();
+    a.n_items = m->red.n_items;
+    a.item_start = m->red.start_dev.ptr<int>();
+    a.n_cfg = n_cfg;
+    a.form = loss_form;
+    a.w[0] = weights[0];
+    a.w[1] = weights[1];
+    a.w[2] = weights[2];
+    a.inv_3ntot = m->nbr.N > 0 ? 1.0 / (3.0 * (double)m->nbr.N) : 0.0;
+    a.off = m->nbr.atom_off_dev.ptr<int64_t>();
+    a.F = t.F.ptr<float>();
+    a.Fref = dev_F_ref;
+    a.E = t.E.ptr<double>();
+    a.Eref = dev_E_ref;
+    a.V = t.V.ptr<double>();
+    a.Vref = dev_V_ref;
+    a.lam = t.lam.ptr<float>();
+    a.ebar = t.ebar.ptr<double>();
+    a.mu = t.mu.ptr<double>();
+    a.partF = t.partF.ptr<double>();
+    a.loss = dev_loss;
+    if ((rc = m->ops->seeds(st, a))) return rc;
+    if (!dev_grad) return NEPMI_OK;
+    return run_backward(m, st, t.ebar.ptr<double>(), t.lam.ptr<float>(), t.mu.ptr<double>(), dev_grad);
+  });
 }
 
 }  // extern "C"
