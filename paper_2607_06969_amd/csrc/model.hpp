@@ -31,7 +31,7 @@ const Ops* find_ops(const nepmi_hparams& hp);
 // Training-only buffers (see train.hip).
 struct TrainBufs {
   DevBuf F, E, V, lam, ebar, mu, partF, lam4;
-  DevBuf Sst, Sdt, q, qd, Pb, Pdn, abar, zneg, gw1, eat, qbR, FpR, GA, part, grad64, gradf, FpA, qbA;
+  DevBuf Sst, Sdt, q, qd, Pb, Pdn, abar, zneg, gw1, eat, qbR, FpR, GA, part, grad64, FpA, qbA;
 };
 
 // Buffers of the float64 variant (see train.hip).

@@ -16,95 +16,11 @@
 //   k_outer2 / k_colsum4 per-species sums over atoms (fixed order, float64)
 #include <cstdlib>
 
-#include "train.hpp"
+#include "train_device.hpp"
 
 namespace nepmi {
 
 constexpr int kTB = 256;
-
-// Symmetric 3x3 as (xx, yy, zz, xy, xz, yz); full-matrix gradient convention
-// dE = sum_ab M_ab dA_ab.  A_n from S_n2m (l = 2 content of S).
-template <class R>
-__device__ __forceinline__ void sym_from_s2(const R* s2, R (&A)[6]) {
-  const R azz = s2[0] * (R(1.0) / (R(3.0) * ShC<R>::k20));
-  const R dif = s2[3] * (R(1.0) / ShC<R>::k22);
-  A[0] = R(0.5) * (dif - azz);
-  A[1] = -R(0.5) * (dif + azz);
-  A[2] = azz;
-  A[3] = s2[4] * (R(1.0) / ShC<R>::k21);
-  A[4] = s2[1] * (R(1.0) / ShC<R>::k21);
-  A[5] = s2[2] * (R(1.0) / ShC<R>::k21);
-}
-
-template <class R>
-__device__ __forceinline__ void sym_mul_sym(const R (&A)[6], const R (&B)[6], R (&C)[9]) {
-  // C = A B (general 3x3, row-major)
-  const R a[9] = {A[0], A[3], A[4], A[3], A[1], A[5], A[4], A[5], A[2]};
-  const R b[9] = {B[0], B[3], B[4], B[3], B[1], B[5], B[4], B[5], B[2]};
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) C[3 * i + j] = a[3 * i] * b[j] + a[3 * i + 1] * b[3 + j] + a[3 * i + 2] * b[6 + j];
-}
-
-// sum_ab M_ab N_ab for symmetric M, N
-template <class R>
-__device__ __forceinline__ R sym_dot(const R (&M)[6], const R (&N)[6]) {
-  return M[0] * N[0] + M[1] * N[1] + M[2] * N[2] + R(2.0) * (M[3] * N[3] + M[4] * N[4] + M[5] * N[5]);
-}
-
-// Gradient with respect to S_n2m of a function whose gradient w.r.t. A is M.
-template <class R>
-__device__ __forceinline__ void chain_s2(const R (&M)[6], R (&g)[5]) {
-  g[0] = (M[2] - R(0.5) * (M[0] + M[1])) * (R(1.0) / (R(3.0) * ShC<R>::k20));
-  g[1] = R(2.0) * M[4] * (R(1.0) / ShC<R>::k21);
-  g[2] = R(2.0) * M[5] * (R(1.0) / ShC<R>::k21);
-  g[3] = R(0.5) * (M[0] - M[1]) * (R(1.0) / ShC<R>::k22);
-  g[4] = R(2.0) * M[3] * (R(1.0) / ShC<R>::k21);
-}
-
-template <class R>
-__device__ __forceinline__ void sym_sq6(const R (&A)[6], R (&B)[6]) {
-  const R xx = A[0], yy = A[1], zz = A[2], xy = A[3], xz = A[4], yz = A[5];
-  B[0] = xx * xx + xy * xy + xz * xz;
-  B[1] = xy * xy + yy * yy + yz * yz;
-  B[2] = xz * xz + yz * yz + zz * zz;
-  B[3] = xx * xy + xy * yy + xz * yz;
-  B[4] = xx * xz + xy * yz + xz * zz;
-  B[5] = xy * xz + yy * yz + yz * zz;
-}
-
-template <class R>
-__device__ __forceinline__ void load_cell9(const CfgDev* __restrict__ cfgs, int c, R (&H)[9]) {
-#pragma unroll
-  for (int x = 0; x < 9; ++x) H[x] = c >= 0 ? cell_rows(cfgs[c], R())[x] : R(0);
-}
-
-template <class R>
-struct PV {
-  R rx, ry, rz, d2;
-  int q, zj;
-};
-
-// Pair vector of list entry e whose neighbour position xq is already loaded.
-template <class R>
-__device__ __forceinline__ PV<R> pvec_at(uint32_t e, Vec4<R> xq, Vec4<R> xi, const R (&H)[9]) {
-  PV<R> v;
-  v.q = (int)(e & kNbrMask);
-  R sx, sy, sz;
-  image_shift(H, e >> kNbrShift, sx, sy, sz);
-  v.rx = (xq.x - xi.x) + sx;
-  v.ry = (xq.y - xi.y) + sy;
-  v.rz = (xq.z - xi.z) + sz;
-  v.d2 = pair_d2(v.rx, v.ry, v.rz);
-  v.zj = species_of(xq);
-  return v;
-}
-
-template <class R>
-__device__ __forceinline__ PV<R> pvec(const Vec4<R>* __restrict__ pos4, uint32_t e, Vec4<R> xi, const R (&H)[9]) {
-  return pvec_at(e, pos4[e & kNbrMask], xi, H);
-}
 
 // The pair lists walked here (compact lists of the forward in float32, the
 // Verlet list in float64) are stored in groups of four entries (walk_groups).
@@ -226,13 +142,20 @@ __global__ __launch_bounds__(kTB) void k_train_atom(TrainIOT<R> io, CutoffsT<R> 
     // padding: zero every per-slot output that is summed over species ranges
     if constexpr (kTangent) {
       if (blockIdx.y != 0) return;
-      for (int d = 0; d < D; ++d) io.q[d * ns + p] = io.qd[d * ns + p] = R(0);
-      for (int k = 0; k < T * BR; ++k) io.Pb[k * ns + p] = io.Pdn[k * ns + p] = R(0);
+      for (int d = 0; d < D; ++d) {
+        io.q[d * ns + p] = R(0);
+        if constexpr (!FWD) io.qd[d * ns + p] = R(0);
+      }
+      if constexpr (!FWD)
+        for (int k = 0; k < T * BR; ++k) io.Pb[k * ns + p] = io.Pdn[k * ns + p] = R(0);
     }
     if constexpr (kNet) {
-      for (int h = 0; h < H; ++h) io.abar[h * ns + p] = io.zneg[h * ns + p] = io.gw1[h * ns + p] = R(0);
-      for (int n = 0; n < NR; ++n) io.qbR[n * ns + p] = io.FpR[n * ns + p] = R(0);
-      io.eat[p] = R(0);
+      for (int n = 0; n < NR; ++n) io.FpR[n * ns + p] = R(0);
+      if constexpr (!FWD) {
+        for (int h = 0; h < H; ++h) io.abar[h * ns + p] = io.zneg[h * ns + p] = io.gw1[h * ns + p] = R(0);
+        for (int n = 0; n < NR; ++n) io.qbR[n * ns + p] = R(0);
+        io.eat[p] = R(0);
+      }
     }
     return;
   }
@@ -1583,6 +1506,7 @@ int TrainLaunch<S>::backward(hipStream_t st, TrainIO io, const Cutoffs& cut, con
   const int64_t ns = io.ns;
   hipLaunchKernelGGL(k_lam_slots<float>, dim3(blocks(ns, 256)), dim3(256), 0, st, ns, io.orig, lam,
                      const_cast<float4*>(io.lam4));
+  if (ns <= kTrainWaveSlots) return TrainWave<S, float>::run(st, io, cut, params, base, part, grad);
   constexpr int NC = S::NA >= 4 ? 2 : 1;
   hipLaunchKernelGGL((k_train_atom<S, NC, float, 1>), dim3(blocks(ns, kTB), 1 + S::NA / NC), dim3(kTB), 0, st, io, cut, params);
   hipLaunchKernelGGL(k_train_net<S>, dim3(blocks(ns, kTB)), dim3(kTB), 0, st, io, params);
@@ -1634,6 +1558,7 @@ int TrainLaunch<S>::backward64(hipStream_t st, TrainIOT<double> io, const Cutoff
                                const double* lam, const int* base, double* part, double* grad) {
   const int64_t ns = io.ns;
   hipLaunchKernelGGL(k_lam_slots<double>, dim3(blocks(ns, 256)), dim3(256), 0, st, ns, io.orig, lam, io.lam4);
+  if (ns <= kTrainWaveSlots64) return TrainWave<S, double>::run(st, io, cut, a.params, base, part, grad);
   constexpr int NC = S::NA >= 4 ? 2 : 1;
   hipLaunchKernelGGL((k_train_atom<S, NC, double, 1>), dim3(blocks(ns, kTB), 1 + S::NA / NC), dim3(kTB), 0, st, io, cut, a.params);
   hipLaunchKernelGGL((k_train_atom<S, NC, double, 2>), dim3(blocks(ns, kTB)), dim3(kTB), 0, st, io, cut, a.params);

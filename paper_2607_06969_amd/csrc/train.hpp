@@ -101,6 +101,34 @@ struct TrainLaunch {
                         const double* lam, const int* base, double* part, double* grad);
 };
 
+// The parameter gradient in one pass over the atoms (train_wave.hip), for io with
+// pos4, cfg_of, cfgs, lam4, mu, ebar and the list nbrR, cntR (every pair within
+// the radial cutoff, more allowed).  part holds train_wave_part(...) doubles.
+//
+// It serves batches of up to kTrainWaveSlots slots in float32 and
+// kTrainWaveSlots64 in float64; larger ones take the passes of train.hip, which
+// hold an atom per lane and so keep more atoms in flight (lists and gradient, one
+// pass against passes, us.  float32, Ge-Sb-Te model: 677 atoms 38 and 162, 9,285
+// atoms 120 and 190, 19,800 atoms 213 and 250, 39,402 atoms 370 and 348; model of
+// Table 2: 19,800 atoms 250 and 259, 27,173 atoms 351 and 335.  float64: 2,555
+// atoms 172 and 408, 46,872 atoms 1035 and 1128, Table 2 1273 and 1318, 74,000
+// atoms 1910 and 1718).
+constexpr int64_t kTrainWaveSlots = 24576, kTrainWaveSlots64 = 49152;
+// Blocks: an atom per wavefront while the chip holds them all, then what it
+// holds in one round (float32) or two (float64).
+inline int train_wave_blocks(int64_t ns) {
+  const int64_t few = (ns + 3) / 4;
+  return (int)(few < 512 ? few : 512);
+}
+inline size_t train_wave_part(int64_t ns, int n_species, size_t entries) {
+  return (size_t)(train_wave_blocks(ns) + n_species) * entries;
+}
+template <class S, class R>
+struct TrainWave {
+  static int run(hipStream_t st, const TrainIOT<R>& io, const CutoffsT<R>& cut, const R* params, const int* base,
+                 double* part, R* grad);
+};
+
 // float64 helpers: stage positions in slot order, round positions to float32
 // (for the neighbour lists), fill a float64 array.
 int launch_stage64(hipStream_t st, const TrainIOT<double>& io, const F64Args& a, const float4* pos4f);

@@ -18,15 +18,18 @@ int ensure_train(nepmi_model* m) {
   int rc;
   if ((rc = t.F.ensure(12 * N)) || (rc = t.E.ensure(8 * nc)) || (rc = t.V.ensure(72 * nc)) ||
       (rc = t.lam.ensure(12 * N)) || (rc = t.ebar.ensure(8 * nc)) || (rc = t.mu.ensure(72 * nc)) ||
-      (rc = t.partF.ensure(8 * ni)) || (rc = t.lam4.ensure(16 * ns)) ||
-      (rc = t.Sst.ensure(4 * ns * o->NA * o->K)) || (rc = t.Sdt.ensure(4 * ns * o->NA * o->K)) ||
+      (rc = t.partF.ensure(8 * ni)) || (rc = t.lam4.ensure(16 * ns)))
+    return rc;
+  if ((int64_t)ns <= kTrainWaveSlots) return t.part.ensure(8 * train_wave_part((int64_t)ns, o->T, sumE));
+  // the passes' hand-over arrays
+  if ((rc = t.Sst.ensure(4 * ns * o->NA * o->K)) || (rc = t.Sdt.ensure(4 * ns * o->NA * o->K)) ||
       (rc = t.q.ensure(4 * ns * o->D)) || (rc = t.qd.ensure(4 * ns * o->D)) ||
       (rc = t.Pb.ensure(4 * ns * o->T * o->BR)) || (rc = t.Pdn.ensure(4 * ns * o->T * o->BR)) ||
       (rc = t.abar.ensure(4 * ns * o->H)) || (rc = t.zneg.ensure(4 * ns * o->H)) || (rc = t.gw1.ensure(4 * ns * o->H)) ||
       (rc = t.eat.ensure(4 * ns)) || (rc = t.qbR.ensure(4 * ns * o->NR)) || (rc = t.FpR.ensure(4 * ns * o->NR)) ||
       (rc = t.GA.ensure(4 * ns * o->T * o->NA * o->BA)) || (rc = t.part.ensure(8 * (size_t)o->T * kRBlocks * sumE)) ||
-      (rc = t.grad64.ensure(8 * (size_t)o->P)) || (rc = t.gradf.ensure(4 * (size_t)o->P)) ||
-      (rc = t.FpA.ensure(4 * ns * o->D)) || (rc = t.qbA.ensure(4 * ns * o->D)))
+      (rc = t.grad64.ensure(8 * (size_t)o->P)) || (rc = t.FpA.ensure(4 * ns * o->D)) ||
+      (rc = t.qbA.ensure(4 * ns * o->D)))
     return rc;
   return NEPMI_OK;
 }
@@ -39,8 +42,11 @@ TrainIO train_io(nepmi_model* m, const double* mu, const double* ebar) {
   io.cfg_of = m->nbr.cfg_of.ptr<int>();
   io.orig = m->nbr.orig.ptr<int>();
   io.cfgs = m->nbr.cfgs.ptr<CfgDev>();
-  io.nbrR = m->nbr.cnbrR.ptr<uint32_t>();  // compact lists written by the forward
-  io.cntR = m->nbr.ccntR.ptr<int>();
+  // the one-pass gradient takes the list itself, the passes the compact lists
+  // written by the forward
+  const bool whole = io.ns <= kTrainWaveSlots;
+  io.nbrR = whole ? m->nbr.nbrR.ptr<uint32_t>() : m->nbr.cnbrR.ptr<uint32_t>();
+  io.cntR = whole ? m->nbr.cntR.ptr<int>() : m->nbr.ccntR.ptr<int>();
   io.nbrA = m->nbr.cnbrA.ptr<uint32_t>();
   io.cntA = m->nbr.ccntA.ptr<int>();
   io.lam4 = t.lam4.ptr<float4>();
@@ -87,15 +93,18 @@ int ensure_f64(nepmi_model* m) {
   int rc;
   if ((rc = f.pos4.ensure(32 * ns)) || (rc = f.lam4.ensure(32 * ns)) || (rc = f.ebar1.ensure(8 * nc)) ||
       (rc = f.mu0.ensure(72 * nc)) || (rc = f.Ei.ensure(8 * N)) || (rc = f.Wi.ensure(72 * N)) ||
-      (rc = f.Sst.ensure(8 * ns * o->NA * o->K)) || (rc = f.Sdt.ensure(8 * ns * o->NA * o->K)) ||
-      (rc = f.q.ensure(8 * ns * o->D)) || (rc = f.qd.ensure(8 * ns * o->D)) ||
-      (rc = f.Pb.ensure(8 * ns * o->T * o->BR)) || (rc = f.Pdn.ensure(8 * ns * o->T * o->BR)) ||
-      (rc = f.abar.ensure(8 * ns * o->H)) || (rc = f.zneg.ensure(8 * ns * o->H)) || (rc = f.gw1.ensure(8 * ns * o->H)) ||
-      (rc = f.eat.ensure(8 * ns)) || (rc = f.qbR.ensure(8 * ns * o->NR)) || (rc = f.FpR.ensure(8 * ns * o->NR)) ||
-      (rc = f.GA.ensure(8 * ns * o->T * o->NA * o->BA)) || (rc = f.part.ensure(8 * (size_t)o->T * kRBlocks * sumE)) ||
-      (rc = f.FpA.ensure(8 * ns * o->D)) || (rc = f.qbA.ensure(8 * ns * o->D)) ||
+      (rc = f.Sst.ensure(8 * ns * o->NA * o->K)) || (rc = f.q.ensure(8 * ns * o->D)) ||
+      (rc = f.zneg.ensure(8 * ns * o->H)) || (rc = f.FpR.ensure(8 * ns * o->NR)) || (rc = f.FpA.ensure(8 * ns * o->D)) ||
       (rc = f.fA.ensure(32 * ns * (size_t)(m->nbr.capA > 0 ? m->nbr.capA : 1))) ||
       (rc = f.aR.ensure(8 * ns * o->T * o->BR)))
+    return rc;
+  if ((int64_t)ns <= kTrainWaveSlots64) return f.part.ensure(8 * train_wave_part((int64_t)ns, o->T, sumE));
+  // the passes' hand-over arrays
+  if ((rc = f.Sdt.ensure(8 * ns * o->NA * o->K)) || (rc = f.qd.ensure(8 * ns * o->D)) ||
+      (rc = f.Pb.ensure(8 * ns * o->T * o->BR)) || (rc = f.Pdn.ensure(8 * ns * o->T * o->BR)) ||
+      (rc = f.abar.ensure(8 * ns * o->H)) || (rc = f.gw1.ensure(8 * ns * o->H)) || (rc = f.eat.ensure(8 * ns)) ||
+      (rc = f.qbR.ensure(8 * ns * o->NR)) || (rc = f.GA.ensure(8 * ns * o->T * o->NA * o->BA)) ||
+      (rc = f.part.ensure(8 * (size_t)o->T * kRBlocks * sumE)) || (rc = f.qbA.ensure(8 * ns * o->D)))
     return rc;
   return NEPMI_OK;
 }
@@ -235,8 +244,11 @@ int nepmi_backward_params(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off
   return m->with_lists(n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st, [&]() -> int {
     int rc;
     if ((rc = ensure_train(m))) return rc;
-    // the descriptor kernel writes the per-evaluation compact pair lists
-    if ((rc = m->ops->desc(st, m->io(nullptr, nullptr, nullptr), m->params.ptr<float>(), false, m->vdesc))) return rc;
+    // beyond the one-pass gradient, the descriptor kernel writes the compact
+    // pair lists
+    if (m->nbr.n_slots > kTrainWaveSlots &&
+        (rc = m->ops->desc(st, m->io(nullptr, nullptr, nullptr), m->params.ptr<float>(), false, m->vdesc)))
+      return rc;
     return run_backward(m, st, dev_ebar, dev_lambda, dev_mu, dev_grad);
   });
 }
