@@ -271,7 +271,8 @@ void nepmi_md_destroy(nepmi_md *md);
  * k_gather, each step into its own events; the other steps replay the plain
  * graph (the event nodes cost a few microseconds each).  ms_per_launch: host
  * double[3] = average duration (ms) of descriptors + network, pair forces +
- * virial, force gather over the timed replays.  Chunks, checkpoints and
+ * virial, force gather (with the second half kick, which it carries) over the
+ * timed replays.  Chunks, checkpoints and
  * overflow recovery as nepmi_md_step (a chunk run again records its steps
  * again).  Errors as nepmi_md_step, and NEPMI_UNSUPPORTED if the graph could
  * not be built with timing nodes. */

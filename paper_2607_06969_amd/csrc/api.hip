@@ -152,10 +152,9 @@ int run_eval(EvalWork& w, const nepmi_model* m, float* dev_forces, double* dev_e
   if (dev_atom_virial) io.Wi = dev_atom_virial;
   const float* P = m->params.ptr<float>();
   int rc;
-  if ((rc = m->ops->desc(st, io, P, true, m->vdesc)) || (rc = m->ops->force(st, io, P, m->vforce)) ||
-      (rc = m->ops->gather(st, io, m->vgather)))
-    return rc;
-  return w.red.run(st, io.Ei, io.Wi, nullptr, dev_energy, dev_virial, nullptr);
+  if ((rc = m->ops->desc(st, io, P, true, m->vdesc)) || (rc = m->ops->force(st, io, P, m->vforce))) return rc;
+  const SumArgs<float> sums = w.red.args<float>(io.Ei, io.Wi, nullptr, dev_energy, dev_virial, nullptr);
+  return m->ops->gather(st, io, m->vgather, &sums, nullptr);
 }
 
 }  // namespace nepmi

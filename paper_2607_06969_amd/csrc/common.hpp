@@ -294,10 +294,11 @@ __device__ __forceinline__ void cheb_basis_d(R d, R rc_inv, R (&Q)[B], R (&dQ)[B
 // its own L2: block b runs on XCD b % kXcds.  Per-atom kernels take their
 // tile from this remapping instead of blockIdx.x, so that every XCD walks one
 // contiguous range of slots (spatially close atoms, whose neighbours' data
-// then stay in that XCD's L2).  It is a bijection on [0, gridDim.x).
+// then stay in that XCD's L2).  It is a bijection on [0, gridDim.x); with
+// `skip`, of the blocks from `skip` on onto [0, gridDim.x - skip).
 constexpr unsigned kXcds = 8;
-__device__ __forceinline__ int64_t xcd_tile() {
-  const unsigned b = blockIdx.x, nb = gridDim.x;
+__device__ __forceinline__ int64_t xcd_tile(unsigned skip = 0) {
+  const unsigned b = blockIdx.x - skip, nb = gridDim.x - skip;
   const unsigned x = b % kXcds, i = b / kXcds, per = nb / kXcds, rem = nb % kXcds;
   return (int64_t)(x * per + (x < rem ? x : rem) + i);
 }

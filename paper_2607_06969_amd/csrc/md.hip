@@ -3,8 +3,8 @@
 // One step: half kick + drift (float64 positions, float32 copy for the force
 // kernels) and a displacement check; a neighbour-list rebuild whose kernels
 // all return at once unless an atom moved more than skin/2 since the last
-// build; descriptor/network, pair-force and gather kernels; the second half
-// kick; float64 sums of potential energy (Eq. 1), virial (Eq. 4) and kinetic
+// build; descriptor/network, pair-force and gather kernels, the last with the
+// second half kick; float64 sums of potential energy (Eq. 1), virial (Eq. 4) and kinetic
 // energy.  The graph topology is fixed; only the rebuild flag decides whether
 // the rebuild kernels do work.
 #include <cmath>
@@ -16,14 +16,6 @@
 namespace nepmi {
 
 constexpr float kAccUnit = 9.648533212e-3f;  // 1 eV/(A u) in A/fs^2
-constexpr int kMaxSpecies = 8;
-
-struct MdConst {
-  float acc[kMaxSpecies];   // dt/2 * kAccUnit / m_s   (half kick per unit force)
-  float kin[kMaxSpecies];   // m_s / (2 kAccUnit)       (eV per (A/fs)^2)
-  float dt;
-  float half_skin2;         // (skin/2)^2
-};
 
 struct Dbl3 {
   double x, y, z;
@@ -75,31 +67,7 @@ __global__ void k_md_unpermute(int64_t n_slots, const int* __restrict__ cfg_of, 
   v_user[i] = vel4[p];
 }
 
-// Second half kick and per-atom kinetic energy.  The first thread also ends
-// the step's bookkeeping: it counts the step (and the rebuild, if one ran)
-// and clears the rebuild flag, which nothing later in the step reads.
-__global__ void k_md_kick2(int64_t n_slots, MdConst mc, const int* __restrict__ orig, const float4* __restrict__ pos4,
-                           const float4* __restrict__ F4, float4* __restrict__ vel4, float* __restrict__ Ki,
-                           int* __restrict__ flags, long long* __restrict__ counters) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p == 0) {
-    if (flags[kFlagRebuild]) counters[1] += 1;
-    counters[0] += 1;
-    flags[kFlagRebuild] = 0;
-  }
-  if (p >= n_slots) return;
-  const int i = orig[p];
-  if (i < 0) return;
-  const int z = __float_as_int(pos4[p].w);
-  const float4 f = F4[p];
-  float4 v = vel4[p];
-  v.x = fmaf(mc.acc[z], f.x, v.x);
-  v.y = fmaf(mc.acc[z], f.y, v.y);
-  v.z = fmaf(mc.acc[z], f.z, v.z);
-  vel4[p] = v;
-  Ki[i] = mc.kin[z] * (v.x * v.x + v.y * v.y + v.z * v.z);
-}
-
+// Kinetic energies of a state (in a step, k_gather leaves them).
 __global__ void k_md_kin(int64_t n_slots, MdConst mc, const int* __restrict__ orig, const float4* __restrict__ pos4,
                          const float4* __restrict__ vel4, float* __restrict__ Ki) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -253,7 +221,8 @@ struct nepmi_md {
     tnode[i] = node;
   }
 
-  int forces(hipStream_t st, bool timed = false) {
+  // forces of the present positions; kick: and the half kick that follows them
+  int forces(hipStream_t st, const KickArgs* kick = nullptr, bool timed = false) {
     NepIO o = io();
     const float* P = m->params.ptr<float>();
     int rc;
@@ -262,9 +231,15 @@ struct nepmi_md {
     if (timed) mark(1, st);
     if ((rc = m->ops->force(st, o, P, m->vforce))) return rc;
     if (timed) mark(2, st);
-    if ((rc = m->ops->gather(st, o, m->vgather))) return rc;
+    if ((rc = m->ops->gather(st, o, m->vgather, nullptr, kick))) return rc;
     if (timed) mark(3, st);
     return NEPMI_OK;
+  }
+
+  // float64 sums of the energies and the virial
+  int sums(hipStream_t st) {
+    return red.run(st, red.args<float>(Ei.ptr<float>(), Wi.ptr<float>(), Ki.ptr<float>(), epot.ptr<double>(),
+                                       vir.ptr<double>(), ekin.ptr<double>()));
   }
 
   // Sort and lists; the sort takes the state back to caller order (wrapped)
@@ -305,15 +280,15 @@ struct nepmi_md {
                        ref4.ptr<float4>(), flags);
     int rc;
     if ((rc = rebuild(st, flags + kFlagRebuild))) return rc;
-    if ((rc = forces(st, timed))) return rc;
-    hipLaunchKernelGGL(k_md_kick2, dim3(nb256(ns)), dim3(256), 0, st, ns, mc, nbr.orig.ptr<int>(),
-                       nbr.pos4.ptr<float4>(), F4.ptr<float4>(), vel4.ptr<float4>(), Ki.ptr<float>(), flags,
-                       counters.ptr<long long>());
-    if ((rc = red.run(st, Ei.ptr<float>(), Wi.ptr<float>(), Ki.ptr<float>(), epot.ptr<double>(), vir.ptr<double>(),
-                      ekin.ptr<double>())))
-      return rc;
-    NEPMI_HIP(hipGetLastError());
-    return NEPMI_OK;
+    KickArgs kick;
+    kick.mc = mc;
+    kick.pos4 = nbr.pos4.ptr<float4>();
+    kick.vel4 = vel4.ptr<float4>();
+    kick.Ki = Ki.ptr<float>();
+    kick.flags = flags;
+    kick.counters = counters.ptr<long long>();
+    if ((rc = forces(st, &kick, timed))) return rc;
+    return sums(st);
   }
 
   void drop_graphs() {
@@ -399,9 +374,7 @@ struct nepmi_md {
     if ((rc = forces(st))) return rc;
     hipLaunchKernelGGL(k_md_kin, dim3(nb256(ns)), dim3(256), 0, st, ns, mc, nbr.orig.ptr<int>(),
                        nbr.pos4.ptr<float4>(), vel4.ptr<float4>(), Ki.ptr<float>());
-    if ((rc = red.run(st, Ei.ptr<float>(), Wi.ptr<float>(), Ki.ptr<float>(), epot.ptr<double>(), vir.ptr<double>(),
-                      ekin.ptr<double>())))
-      return rc;
+    if ((rc = sums(st))) return rc;
     NEPMI_HIP(hipStreamSynchronize(st));
     return capture();
   }
@@ -503,9 +476,7 @@ int nepmi_md_create(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
   if ((rc = md->forces(st))) return fail(rc);
   hipLaunchKernelGGL(k_md_kin, dim3(nb256(ns)), dim3(256), 0, st, ns, md->mc, nb.orig.ptr<int>(), nb.pos4.ptr<float4>(),
                      md->vel4.ptr<float4>(), md->Ki.ptr<float>());
-  if ((rc = md->red.run(st, md->Ei.ptr<float>(), md->Wi.ptr<float>(), md->Ki.ptr<float>(), md->epot.ptr<double>(),
-                        md->vir.ptr<double>(), md->ekin.ptr<double>())))
-    return fail(rc);
+  if ((rc = md->sums(st))) return fail(rc);
   if (hipStreamSynchronize(st) != hipSuccess) return fail(hip_fail(hipGetLastError(), "hipStreamSynchronize"));
   // capture one step
   for (int i = 0; i < 4; ++i)
@@ -693,7 +664,7 @@ int nepmi_md_time_kernels(nepmi_md* md, int32_t reps, double* ms, void* stream) 
     NEPMI_HIP(hipEventRecord(ev[1], st));
     if (!rc) rc = md->m->ops->force(st, o, P, md->m->vforce);
     NEPMI_HIP(hipEventRecord(ev[2], st));
-    if (!rc) rc = md->m->ops->gather(st, o, md->m->vgather);
+    if (!rc) rc = md->m->ops->gather(st, o, md->m->vgather, nullptr, nullptr);
     NEPMI_HIP(hipEventRecord(ev[3], st));
     // a full list rebuild on the current state (sort + lists)
     hipLaunchKernelGGL(k_set_int, dim3(1), dim3(64), 0, st, md->nbr.flags.ptr<int>() + kFlagRebuild, 1);

@@ -13,7 +13,7 @@ namespace nepmi {
 struct Ops {
   int (*desc)(hipStream_t, const NepIO&, const float*, bool, int);
   int (*force)(hipStream_t, const NepIO&, const float*, int);
-  int (*gather)(hipStream_t, const NepIO&, int);
+  int (*gather)(hipStream_t, const NepIO&, int, const SumArgs<float>*, const KickArgs*);
   int (*derive)(hipStream_t, float*);
   int (*seeds)(hipStream_t, const TrainSeedArgs&);
   int (*backward)(hipStream_t, TrainIO, const Cutoffs&, const float*, const float*, const int*, double*, double*,

@@ -66,7 +66,7 @@ struct PinBuf {
 // the stream 5).  The pinned memory is free again once the stream has passed
 // the kernel; the owner waits for that before the next upload.
 struct Uploader {
-  static constexpr int kMost = 4;
+  static constexpr int kMost = 5;
   struct Table {
     const void* src;
     DevBuf* dst;

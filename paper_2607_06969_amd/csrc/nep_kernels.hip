@@ -849,13 +849,41 @@ __device__ __forceinline__ void gather_masks(GatherStage& st, const uint64_t* __
   }
 }
 
-template <int BS>
+//
+// Work that only needs what the gather has, or nothing of it, shares the
+// launch: a kernel behind another one costs at least 4.5 us, which in small
+// batches is more than these take.
+//   sums  blocks 0 .. n_items - 1 sum the site energies and virials that the
+//         kernels before have written (sum_item), and the others gather
+//         (gather, chunk sums and their sums, 3,686 atoms: 17 us in three
+//         kernels, 6.7 in one; 900,000 atoms 116 and 103)
+//   KICK  the second half kick of an MD step and the kinetic energies, with
+//         the force still in registers (3,686 atoms 11.9 us in two kernels, 7.5
+//         in one); the first thread counts the step (and
+//         the rebuild, if one ran) and clears the rebuild flag, which nothing
+//         later in the step reads
+template <int BS, bool KICK>
 __global__ __launch_bounds__(BS) void k_gather(int64_t n_slots, const int* __restrict__ orig,
                                                    const uint32_t* __restrict__ cnA, const uint32_t* __restrict__ cpA,
                                                    const int* __restrict__ ccA, const uint64_t* __restrict__ amask,
                                                    const float4* __restrict__ frad, const float4* __restrict__ fA,
-                                                   float* __restrict__ Fuser, float4* __restrict__ Fproc) {
-  const int64_t p = xcd_tile() * BS + threadIdx.x;
+                                                   float* __restrict__ Fuser, float4* __restrict__ Fproc,
+                                                   SumArgs<float> sums, KickArgs kick) {
+  if constexpr (!KICK) {
+    if ((int)blockIdx.x < sums.n_items) {
+      __shared__ SumShared sh;
+      sum_item<BS>((int)blockIdx.x, sums, sh);
+      return;
+    }
+  }
+  const int64_t p = xcd_tile(KICK ? 0u : (unsigned)sums.n_items) * BS + threadIdx.x;
+  if constexpr (KICK) {
+    if (p == 0) {
+      if (kick.flags[kFlagRebuild]) kick.counters[1] += 1;
+      kick.counters[0] += 1;
+      kick.flags[kFlagRebuild] = 0;
+    }
+  }
   if (p >= n_slots) return;
   const int i = orig[p];
   if (i < 0) {
@@ -917,6 +945,15 @@ __global__ __launch_bounds__(BS) void k_gather(int64_t n_slots, const int* __res
     Fuser[(int64_t)i * 3 + 2] = F.z;
   }
   if (Fproc) Fproc[p] = F;
+  if constexpr (KICK) {
+    const int z = __float_as_int(kick.pos4[p].w);
+    float4 v = kick.vel4[p];
+    v.x = fmaf(kick.mc.acc[z], F.x, v.x);
+    v.y = fmaf(kick.mc.acc[z], F.y, v.y);
+    v.z = fmaf(kick.mc.acc[z], F.z, v.z);
+    kick.vel4[p] = v;
+    kick.Ki[i] = kick.mc.kin[z] * (v.x * v.x + v.y * v.y + v.z * v.z);
+  }
 }
 
 // Derived tables.  Coefficients: ctil[..][n][0] = c[..][n][0] + sum_k c[..][n][k],
@@ -1020,21 +1057,26 @@ int Launch<S>::force(hipStream_t st, const NepIO& io, const float* params, int v
 }
 
 template <int BS>
-static int launch_gather(hipStream_t st, const NepIO& io) {
+static int launch_gather(hipStream_t st, const NepIO& io, const SumArgs<float>* sums, const KickArgs* kick) {
   const unsigned g = (unsigned)((io.n_slots + BS - 1) / BS);
-  hipLaunchKernelGGL(k_gather<BS>, dim3(g), dim3(BS), 0, st, io.n_slots, io.orig, io.cnA, io.cpA, io.ccA, io.amask,
-                     io.frad, io.fA, io.Fuser, io.Fproc);
+  if (kick)
+    hipLaunchKernelGGL((k_gather<BS, true>), dim3(g), dim3(BS), 0, st, io.n_slots, io.orig, io.cnA, io.cpA, io.ccA,
+                       io.amask, io.frad, io.fA, io.Fuser, io.Fproc, SumArgs<float>{}, *kick);
+  else
+    hipLaunchKernelGGL((k_gather<BS, false>), dim3(g + (sums ? sums->n_items : 0)), dim3(BS), 0, st, io.n_slots,
+                       io.orig, io.cnA, io.cpA, io.ccA, io.amask, io.frad, io.fA, io.Fuser, io.Fproc,
+                       sums ? *sums : SumArgs<float>{}, KickArgs{});
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }
 
 template <class S>
-int Launch<S>::gather(hipStream_t st, const NepIO& io, int variant) {
+int Launch<S>::gather(hipStream_t st, const NepIO& io, int variant, const SumArgs<float>* sums, const KickArgs* kick) {
   switch (variant) {
-    case 1: return launch_gather<128>(st, io);
-    case 2: return launch_gather<512>(st, io);
-    case 3: return launch_gather<1024>(st, io);
-    default: return launch_gather<256>(st, io);
+    case 1: return launch_gather<128>(st, io, sums, kick);
+    case 2: return launch_gather<512>(st, io, sums, kick);
+    case 3: return launch_gather<1024>(st, io, sums, kick);
+    default: return launch_gather<256>(st, io, sums, kick);
   }
 }
 

@@ -25,7 +25,7 @@
 //            built with the lists and j's entry mask.
 #pragma once
 
-#include "common.hpp"
+#include "reduce.hpp"
 
 namespace nepmi {
 
@@ -67,11 +67,32 @@ constexpr int kDescVariants = 10;  // compiled variants of k_desc (4..7: network
 constexpr int kForceVariants = 6;  // compiled variants of k_force (4, 5: variant 0 in blocks of 128, 512)
 constexpr int kGatherVariants = 4; // k_gather in blocks of 256, 128, 512, 1024 threads
 
+// Constants of an MD step.
+constexpr int kMaxSpecies = 8;
+struct MdConst {
+  float acc[kMaxSpecies];   // dt/2 * kAccUnit / m_s   (half kick per unit force)
+  float kin[kMaxSpecies];   // m_s / (2 kAccUnit)       (eV per (A/fs)^2)
+  float dt;
+  float half_skin2;         // (skin/2)^2
+};
+
+// The second half kick of an MD step, and the step's bookkeeping.
+struct KickArgs {
+  MdConst mc;
+  const float4* pos4 = nullptr;
+  float4* vel4 = nullptr;         // [n_slots]
+  float* Ki = nullptr;            // [N] caller order, kinetic energies
+  int* flags = nullptr;           // of the neighbour lists
+  long long* counters = nullptr;  // steps, rebuilds
+};
+
 template <class S>
 struct Launch {
   static int desc(hipStream_t st, const NepIO& io, const float* params, bool want_adjoint, int variant);
   static int force(hipStream_t st, const NepIO& io, const float* params, int variant);
-  static int gather(hipStream_t st, const NepIO& io, int variant);
+  // with the sums of an evaluation (may be null), or the half kick that
+  // follows the forces of an MD step (may be null), in the same launch
+  static int gather(hipStream_t st, const NepIO& io, int variant, const SumArgs<float>* sums, const KickArgs* kick);
   // Writes the derived tables after the P parameters (the parameter buffer
   // holds PALL floats).
   static int derive(hipStream_t st, float* params);

@@ -212,7 +212,7 @@ int nepmi_compute_f64(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, co
   TrainIOT<double> io = f64_io(m, f.mu0.ptr<double>(), f.ebar1.ptr<double>(), Ei);
   if ((rc = m->ops->forward64(st, io, f64_cut(m), a, dev_forces))) return rc;
   // per-configuration float64 sums in the fixed chunking of the float32 path
-  return m->red.run64(st, Ei, a.Wi, dev_energy, dev_virial);
+  return m->red.run(st, m->red.args<double>(Ei, a.Wi, nullptr, dev_energy, dev_virial, nullptr));
 }
 
 int nepmi_backward_params_f64(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc,
@@ -270,8 +270,9 @@ int nepmi_loss_grad(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
     // forward: E, F, V
     NepIO io = m->io(t.F.ptr<float>(), nullptr, nullptr);
     const float* P = m->params.ptr<float>();
-    if ((rc = m->ops->desc(st, io, P, true, m->vdesc)) || (rc = m->ops->force(st, io, P, m->vforce)) || (rc = m->ops->gather(st, io, m->vgather)) ||
-        (rc = m->red.run(st, io.Ei, io.Wi, nullptr, t.E.ptr<double>(), t.V.ptr<double>(), nullptr)))
+    const SumArgs<float> sums = m->red.args<float>(io.Ei, io.Wi, nullptr, t.E.ptr<double>(), t.V.ptr<double>(), nullptr);
+    if ((rc = m->ops->desc(st, io, P, true, m->vdesc)) || (rc = m->ops->force(st, io, P, m->vforce)) ||
+        (rc = m->ops->gather(st, io, m->vgather, &sums, nullptr)))
       return rc;
     // loss and seeds
     TrainSeedArgs a;

@@ -60,11 +60,11 @@ int autotune_io(nepmi_model* m, const NepIO& io, hipStream_t st, int reps) {
   int bg = m->vgather;
   best = 1e300;
   for (int v = 0; v < kGatherVariants && !rc; ++v) {
-    rc = m->ops->gather(st, io, v);
+    rc = m->ops->gather(st, io, v, nullptr, nullptr);
     double t = 0.0;
     for (int r = 0; r < reps && !rc; ++r) {
       NEPMI_HIP(hipEventRecord(e0, st));
-      rc = m->ops->gather(st, io, v);
+      rc = m->ops->gather(st, io, v, nullptr, nullptr);
       NEPMI_HIP(hipEventRecord(e1, st));
       NEPMI_HIP(hipEventSynchronize(e1));
       float ms;
@@ -83,7 +83,7 @@ int autotune_io(nepmi_model* m, const NepIO& io, hipStream_t st, int reps) {
   m->vforce = bf;
   m->vgather = bg;
   // leave the outputs of the chosen variants behind
-  if ((rc = m->ops->gather(st, io, bg))) return rc;
+  if ((rc = m->ops->gather(st, io, bg, nullptr, nullptr))) return rc;
   return NEPMI_OK;
 }
 

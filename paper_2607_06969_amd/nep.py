@@ -358,7 +358,7 @@ class NepMD:
 
     def step_timed(self, n):
         """Advance n steps; returns the average duration (ms) of the descriptor,
-        pair-force and gather kernels over steps 0, 4, 8, ... of these (HIP
+        pair-force and gather (with the second half kick) kernels over steps 0, 4, 8, ... of these (HIP
         events recorded inside a copy of the step graph that those steps
         replay; the others replay the plain graph)."""
         ms = (C.c_double * 3)()
