@@ -83,7 +83,7 @@ static int eval_buffers(EvalWork& w, const Ops* ops) {
 
 int prepare_start(EvalWork& w, const Ops* ops, const nepmi_hparams& hp, int n_cfg, const int64_t* atom_off,
                   const double* cells, const int32_t* pbc, const float* pos, const int32_t* species, hipStream_t st,
-                  double skin) {
+                  double skin, bool post) {
   int rc;
   // the flags of an earlier build whose call ended in an error: its upload may
   // still read the pinned tables
@@ -94,7 +94,7 @@ int prepare_start(EvalWork& w, const Ops* ops, const nepmi_hparams& hp, int n_cf
   if ((rc = w.nbr.setup(n_cfg, atom_off, cells, pbc, ops->T, hp.rc_radial, hp.rc_angular, skin)) ||
       (rc = w.red.setup(n_cfg, atom_off, w.nbr.up)) || (rc = eval_buffers(w, ops)))
     return rc;
-  return w.nbr.build_start(st, pos, species);
+  return w.nbr.build_start(st, pos, species, post);
 }
 
 int prepare_end(EvalWork& w, const Ops* ops, hipStream_t st, bool& again) {
@@ -139,6 +139,7 @@ NepIO eval_io(EvalWork& w, const nepmi_hparams& hp, float* Fuser, float4* Fproc,
   o.Fuser = Fuser;
   o.Fproc = Fproc;
   o.Eproc = w.Eproc.ptr<float>();
+  o.mail = nbr.post();
   return o;
 }
 
@@ -192,7 +193,7 @@ int nepmi_model::prepare(int n_cfg, const int64_t* atom_off, const double* cells
   last.valid = false;
   int rc;
   bool again = false;
-  if ((rc = prepare_start(*this, ops, hp, n_cfg, atom_off, cells, pbc, pos, species, st, skin)) ||
+  if ((rc = prepare_start(*this, ops, hp, n_cfg, atom_off, cells, pbc, pos, species, st, skin, false)) ||
       (rc = prepare_end(*this, ops, st, again)))
     return rc;
   if (may_reuse) keep(n_cfg, atom_off, cells, pbc, pos, species, skin);
@@ -253,9 +254,7 @@ int nepmi_model_set_params(nepmi_model* m, const float* dev_params, void* stream
     set_error("null model or parameters");
     return NEPMI_INVALID_ARG;
   }
-  NEPMI_HIP(hipMemcpyAsync(m->params.p, dev_params, 4 * (size_t)m->ops->P, hipMemcpyDeviceToDevice,
-                           (hipStream_t)stream));
-  return m->ops->derive((hipStream_t)stream, m->params.ptr<float>());
+  return m->ops->derive((hipStream_t)stream, dev_params, m->params.ptr<float>());
 }
 
 int nepmi_model_reuse_lists(nepmi_model* m, int32_t enable) {

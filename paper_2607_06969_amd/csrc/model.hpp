@@ -14,10 +14,10 @@ struct Ops {
   int (*desc)(hipStream_t, const NepIO&, const float*, bool, int);
   int (*force)(hipStream_t, const NepIO&, const float*, int);
   int (*gather)(hipStream_t, const NepIO&, int, const SumArgs<float>*, const KickArgs*);
-  int (*derive)(hipStream_t, float*);
+  int (*derive)(hipStream_t, const float*, float*);
   int (*seeds)(hipStream_t, const TrainSeedArgs&);
   int (*backward)(hipStream_t, TrainIO, const Cutoffs&, const float*, const float*, const int*, double*, double*,
-                  float*);
+                  float*, const MailArgs&);
   int (*forward64)(hipStream_t, TrainIOT<double>, const CutoffsT<double>&, const F64Args&, double*);
   int (*backward64)(hipStream_t, TrainIOT<double>, const CutoffsT<double>&, const F64Args&, const double*, const int*,
                     double*, double*);
@@ -30,7 +30,7 @@ const Ops* find_ops(const nepmi_hparams& hp);
 
 // Training-only buffers (see train.hip).
 struct TrainBufs {
-  DevBuf F, E, V, lam, ebar, mu, partF, lam4;
+  DevBuf F, E, V, ebar, mu, partF, lam4;
   DevBuf Sst, Sdt, q, qd, Pb, Pdn, abar, zneg, gw1, eat, qbR, FpR, GA, part, grad64, FpA, qbA;
 };
 
@@ -62,10 +62,11 @@ struct EvalWork {
 // waits for the lists' flags and reports what is wrong with the input.  Work
 // on the lists can be launched between the two: it stays within its buffers
 // whatever the flags say, and has to be launched again if prepare_end says so
-// (the lists were too short and have been rebuilt).
+// (the lists were too short and have been rebuilt).  With `post`, that work
+// has to deliver the flags: its first kernel gets them (NepIO::mail).
 int prepare_start(EvalWork& w, const Ops* ops, const nepmi_hparams& hp, int n_cfg, const int64_t* atom_off,
                   const double* cells, const int32_t* pbc, const float* pos, const int32_t* species, hipStream_t st,
-                  double skin);
+                  double skin, bool post);
 int prepare_end(EvalWork& w, const Ops* ops, hipStream_t st, bool& again);
 // Kernel arguments of an evaluation on `w` (optional caller-order forces,
 // slot-order forces and descriptors).
@@ -97,7 +98,7 @@ struct nepmi_model : nepmi::EvalWork {
     last.valid = false;
     int rc;
     bool again = false;
-    if ((rc = nepmi::prepare_start(*this, ops, hp, n_cfg, atom_off, cells, pbc, pos, species, st, 0.0)) ||
+    if ((rc = nepmi::prepare_start(*this, ops, hp, n_cfg, atom_off, cells, pbc, pos, species, st, 0.0, true)) ||
         (rc = launch()) || (rc = nepmi::prepare_end(*this, ops, st, again)) || (again && (rc = launch())))
       return rc;
     keep(n_cfg, atom_off, cells, pbc, pos, species, 0.0);

@@ -29,6 +29,9 @@ constexpr int kMaxSortSpecies = 8;
 // Largest sort that one block does whole, and most keys that one block scans
 // (see k_sort_small, k_scan_one).
 constexpr int kSmallAtoms = 4096, kSmallKeys = 8192;
+// Upload that such a sort takes along, in 16-byte words: one per thread (3,686
+// atoms: sort 15.4 us behind an upload of 4.1, 18.3 with it and a launch less).
+constexpr int kSmallUpload = 1024;
 constexpr int kOneScan = 1 << 15, kOneScanGated = 1 << 20;
 
 // ------------------------------------------------------------------ staging
@@ -72,6 +75,15 @@ __device__ __forceinline__ int stage_atom(const CfgDev& C, int z, int total_bins
       o[a] = (float)((double)o[a] - m[0] * C.Hd[a] - m[1] * C.Hd[3 + a] - m[2] * C.Hd[6 + a]);
   }
   return z * total_bins + bin_key(C, b[0], b[1], b[2]);
+}
+
+// Thread t of `step` of an upload.
+__device__ __forceinline__ void upload_part(const UploadArgs& a, int64_t t, int64_t step) {
+  if (t < a.n_clear) a.clear[t] = 0;
+#pragma unroll
+  for (int s = 0; s < UploadArgs::kMost; ++s)
+    if (s < a.n_seg)
+      for (int64_t i = t; i < a.seg[s].n; i += step) a.seg[s].dst[i] = a.seg[s].src[i];
 }
 
 // Where the atoms to sort come from and what the sort works on.
@@ -469,7 +481,8 @@ __global__ void k_fill_slots(SortArgs a, const int* __restrict__ gate) {
 // costs an MD step one idle kernel instead of eight (4.5 us each).  3,686 atoms:
 // 37 us in seven kernels, 16 in one.
 template <bool SLOTS>
-__global__ __launch_bounds__(kScanBlock) void k_sort_small(SortArgs a, const int* __restrict__ gate) {
+__global__ __launch_bounds__(kScanBlock) void k_sort_small(SortArgs a, const int* __restrict__ gate,
+                                                           UploadArgs up) {
   if (gate && *gate == 0) return;
   constexpr int IT = kSmallAtoms / kScanBlock;
   constexpr int kOff = 512;         // configurations whose offsets fit LDS
@@ -479,6 +492,10 @@ __global__ __launch_bounds__(kScanBlock) void k_sort_small(SortArgs a, const int
   __shared__ int sh[kScanBlock / 64];
   __shared__ int lo_s[kMaxSortSpecies], base_s[kMaxSortSpecies + 1];
   const int t = threadIdx.x, M = a.n_species * a.total_bins;
+  if constexpr (!SLOTS) {
+    upload_part(up, t, kScanBlock);
+    __syncthreads();
+  }
   for (int k = t; k < M; k += kScanBlock) cur[k] = 0;
   const bool in_lds = a.n_cfg <= kOff;
   if (!SLOTS && in_lds)
@@ -1066,28 +1083,12 @@ PinBuf::~PinBuf() {
   if (p) (void)hipHostFree(p);
 }
 
-struct UploadArgs {
-  struct {
-    const uint4* src;
-    uint4* dst;
-    int64_t n;
-  } seg[Uploader::kMost];
-  int n_seg;
-  int* clear;
-  int n_clear;
-};
-
 __global__ void k_upload(UploadArgs a) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
-  if (t < a.n_clear) a.clear[t] = 0;
-#pragma unroll
-  for (int s = 0; s < Uploader::kMost; ++s)
-    if (s < a.n_seg)
-      for (int64_t i = t; i < a.seg[s].n; i += step) a.seg[s].dst[i] = a.seg[s].src[i];
+  upload_part(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
 int Uploader::add(const void* src, size_t bytes, DevBuf& dst) {
-  if (tables.size() >= (size_t)kMost) {
+  if (tables.size() >= (size_t)UploadArgs::kMost) {
     set_error("too many tables in one upload");
     return NEPMI_INVALID_ARG;
   }
@@ -1097,12 +1098,12 @@ int Uploader::add(const void* src, size_t bytes, DevBuf& dst) {
   return NEPMI_OK;
 }
 
-int Uploader::run(hipStream_t st, int* clear, int n_clear) {
+int Uploader::plan(int* clear, int n_clear, UploadArgs& a) {
   size_t total = 0;
   for (const Table& t : tables) total += (t.bytes + 15) / 16 * 16;
   const int rc = pin.ensure(total);
   if (rc) return rc;
-  UploadArgs a{};
+  a = UploadArgs{};
   char* h = static_cast<char*>(pin.p);
   for (const Table& t : tables) {
     const size_t n = (t.bytes + 15) / 16;
@@ -1116,11 +1117,22 @@ int Uploader::run(hipStream_t st, int* clear, int n_clear) {
   tables.clear();
   a.clear = clear;
   a.n_clear = n_clear;
-  const int64_t want = (int64_t)(total / 16 + 255) / 256;
+  a.words = (int64_t)(total / 16);
+  return NEPMI_OK;
+}
+
+static int launch_upload(hipStream_t st, const UploadArgs& a) {
+  const int64_t want = (a.words + 255) / 256;
   const unsigned blocks = (unsigned)(want < 1 ? 1 : (want > 256 ? 256 : want));
   hipLaunchKernelGGL(k_upload, dim3(blocks), dim3(256), 0, st, a);
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
+}
+
+int Uploader::run(hipStream_t st, int* clear, int n_clear) {
+  UploadArgs a;
+  const int rc = plan(clear, n_clear, a);
+  return rc ? rc : launch_upload(st, a);
 }
 
 int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells, const int32_t* pbc, int n_species_,
@@ -1306,28 +1318,34 @@ int NbrPipeline::check_flags(hipStream_t st, int* hf) {
   return flag_errors(hf);
 }
 
-// The flags into pinned host memory, then the number of the build.
-__global__ void k_mail_flags(const int* __restrict__ flags, int* __restrict__ mail, int number) {
-  if (threadIdx.x < kFlagCount) mail[threadIdx.x] = flags[threadIdx.x];
-  __threadfence_system();
-  __builtin_amdgcn_wave_barrier();
-  if (threadIdx.x == 0) __hip_atomic_store(&mail[kFlagCount], number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+__global__ void k_mail_flags(MailArgs m) { deliver(m); }
+
+static void mail_flags(hipStream_t st, const MailArgs& m) {
+  hipLaunchKernelGGL(k_mail_flags, dim3(1), dim3(1), 0, st, m);
 }
 
-static void mail_flags(hipStream_t st, const int* flags, int* mail, int number) {
-  hipLaunchKernelGGL(k_mail_flags, dim3(1), dim3(kWave), 0, st, flags, mail, number);
+MailArgs NbrPipeline::post() const {
+  MailArgs m;
+  if (!unsent) return m;
+  m.flags = flags.ptr<int>();
+  m.mail = static_cast<int*>(mail.p);
+  m.number = builds;
+  return m;
 }
 
-int NbrPipeline::build_start(hipStream_t st, const float* pos, const int32_t* species) {
+int NbrPipeline::build_start(hipStream_t st, const float* pos, const int32_t* species, bool post_later) {
   int rc = mail.ensure(sizeof(int) * (kFlagCount + 1));
   if (rc) return rc;
   if (builds == 0) static_cast<int*>(mail.p)[kFlagCount] = 0;
   waiting = true;
   builds = builds == INT32_MAX ? 1 : builds + 1;
-  if ((rc = up.run(st, flags.ptr<int>(), kFlagCount)) || (rc = launch_sort(st, pos, 3, species, n_species, nullptr)) ||
+  UploadArgs u;
+  if ((rc = up.plan(flags.ptr<int>(), kFlagCount, u)) ||
+      (rc = launch_sort(st, pos, 3, species, n_species, nullptr, nullptr, nullptr, &u)) ||
       (rc = launch_lists(st, n_species, nullptr)))
     return rc;
-  mail_flags(st, flags.ptr<int>(), static_cast<int*>(mail.p), builds);
+  unsent = true;
+  if (!post_later) mail_flags(st, post());
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }
@@ -1357,6 +1375,7 @@ static int await_mail(hipStream_t st, const int* mail, int number) {
 
 int NbrPipeline::build_end(hipStream_t st, bool& regrown) {
   regrown = false;
+  unsent = false;  // delivered by what has been launched
   int* m = static_cast<int*>(mail.p);
   for (int attempt = 0; attempt < 2; ++attempt) {
     int rc = await_mail(st, m, builds);
@@ -1380,7 +1399,9 @@ int NbrPipeline::build_end(hipStream_t st, bool& regrown) {
     if ((rc = launch_lists(st, n_species, nullptr))) return rc;
     builds = builds == INT32_MAX ? 1 : builds + 1;
     waiting = true;
-    mail_flags(st, flags.ptr<int>(), m, builds);
+    unsent = true;
+    mail_flags(st, post());
+    unsent = false;
     NEPMI_HIP(hipGetLastError());
   }
   set_error("neighbour capacity overflow after regrow");
@@ -1388,7 +1409,8 @@ int NbrPipeline::build_end(hipStream_t st, bool& regrown) {
 }
 
 int NbrPipeline::launch_sort(hipStream_t st, const float* pos, int pos_stride, const int32_t* species, int n_species,
-                             const int* gate, const SlotCarry* carry, const SlotSource* src) {
+                             const int* gate, const SlotCarry* carry, const SlotSource* src,
+                             const UploadArgs* upload) {
   if (n_species > kMaxSortSpecies) {
     set_error("too many species for the neighbour lists");
     return NEPMI_UNSUPPORTED;
@@ -1422,11 +1444,19 @@ int NbrPipeline::launch_sort(hipStream_t st, const float* pos, int pos_stride, c
   a.cntR = cntR.ptr<int>();
   a.cntAV = cntAV.ptr<int>();
   a.flags = flags.ptr<int>();
-  if (n_slots <= kSmallAtoms && M <= kSmallKeys) {
+  const bool small = n_slots <= kSmallAtoms && M <= kSmallKeys;
+  // the one block of a small sort takes a small upload along
+  const bool along = small && !src && upload && upload->words <= kSmallUpload;
+  if (upload && !along) {
+    const int rc = launch_upload(st, *upload);
+    if (rc) return rc;
+  }
+  if (small) {
     if (src)
-      hipLaunchKernelGGL(k_sort_small<true>, dim3(1), dim3(kScanBlock), 0, st, a, gate);
+      hipLaunchKernelGGL(k_sort_small<true>, dim3(1), dim3(kScanBlock), 0, st, a, gate, UploadArgs{});
     else
-      hipLaunchKernelGGL(k_sort_small<false>, dim3(1), dim3(kScanBlock), 0, st, a, gate);
+      hipLaunchKernelGGL(k_sort_small<false>, dim3(1), dim3(kScanBlock), 0, st, a, gate,
+                         along ? *upload : UploadArgs{});
     NEPMI_HIP(hipGetLastError());
     return NEPMI_OK;
   }

@@ -61,12 +61,24 @@ struct PinBuf {
   PinBuf& operator=(const PinBuf&) = delete;
 };
 
+struct UploadArgs {
+  static constexpr int kMost = 5;  // tables
+  struct {
+    const uint4* src;
+    uint4* dst;
+    int64_t n;
+  } seg[kMost];
+  int n_seg;
+  int* clear;
+  int n_clear;
+  int64_t words;  // 16-byte words of all tables
+};
+
 // Host tables on their way to device buffers: copied into pinned memory, then
 // moved by one kernel (a copy call for each table costs the host some 10 us and
 // the stream 5).  The pinned memory is free again once the stream has passed
 // the kernel; the owner waits for that before the next upload.
 struct Uploader {
-  static constexpr int kMost = 5;
   struct Table {
     const void* src;
     DevBuf* dst;
@@ -76,9 +88,24 @@ struct Uploader {
   std::vector<Table> tables;
   // dst receives the bytes (and is sized for them)
   int add(const void* src, size_t bytes, DevBuf& dst);
-  // launch the upload of the added tables, clearing n_clear ints at clear
+  // The upload of the added tables, clearing n_clear ints at clear: for a kernel
+  // that does it (upload_part), and launched by itself.
+  int plan(int* clear, int n_clear, UploadArgs& out);
   int run(hipStream_t st, int* clear, int n_clear);
 };
+
+// The list flags on their way to the host: the kernel that gets these writes
+// them into pinned memory, then the number of their build.
+struct MailArgs {
+  const int* flags = nullptr;
+  int* mail = nullptr;  // null: nothing to deliver
+  int number = 0;
+};
+__device__ __forceinline__ void deliver(const MailArgs& m) {
+  for (int k = 0; k < kFlagCount; ++k) m.mail[k] = m.flags[k];
+  __threadfence_system();
+  __hip_atomic_store(&m.mail[kFlagCount], m.number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // State that a rebuild moves from caller order into the new slot order along
 // with the positions (MD: float64 positions, velocities, and the positions the
@@ -137,6 +164,7 @@ struct NbrPipeline {
   PinBuf mail;          // the flags as the host reads them, then the number of the build they belong to
   int builds = 0;       // number of the last build started
   bool waiting = false; // its flags have not been read yet
+  bool unsent = false;  // a kernel launched on the lists is to deliver them (post)
 
   // Host-side setup of a batch: validates the cells, computes bins, sizes
   // buffers and adds the configuration tables to `up`.  pbc: host int32[3
@@ -152,16 +180,20 @@ struct NbrPipeline {
   // Stage, bin and sort (pos: N x pos_stride floats).  gate: optional device
   // flag; every kernel returns at once when *gate == 0.  carry: state moved
   // into slot order with the positions (optional).  src: take the atoms from
-  // this state instead of pos (optional).
+  // this state instead of pos (optional).  upload: to be done first (optional).
   int launch_sort(hipStream_t st, const float* pos, int pos_stride, const int32_t* species, int n_species,
-                  const int* gate, const SlotCarry* carry = nullptr, const SlotSource* src = nullptr);
+                  const int* gate, const SlotCarry* carry = nullptr, const SlotSource* src = nullptr,
+                  const UploadArgs* upload = nullptr);
   int launch_lists(hipStream_t st, int n_species, const int* gate);
   // Full build, in two parts so that work on the lists can be launched between
   // them: build_start launches the upload, sort and lists; build_end waits for
   // the flags, reports what the build found wrong, and builds lists that were
   // too short again with a larger capacity (regrown: work launched on the first
-  // ones, which kept within the capacity, is void).
-  int build_start(hipStream_t st, const float* pos, const int32_t* species);
+  // ones, which kept within the capacity, is void).  post: the first kernel
+  // launched on the lists delivers the flags (post()), as one of its own costs
+  // the 4.5 us of any kernel behind another; otherwise build_start launches it.
+  int build_start(hipStream_t st, const float* pos, const int32_t* species, bool post);
+  MailArgs post() const;
   int build_end(hipStream_t st, bool& regrown);
   int check_flags(hipStream_t st, int* host_flags);
 };

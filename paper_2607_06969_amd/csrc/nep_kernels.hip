@@ -212,11 +212,12 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     uint32_t* __restrict__ cnA, uint32_t* __restrict__ cpA, int* __restrict__ ccA, uint64_t* __restrict__ amask,
     int* __restrict__ flags, Cutoffs cut,
     const float* __restrict__ params, float* __restrict__ fp, float* __restrict__ aR, float* __restrict__ Ei,
-    float* __restrict__ qout, float* __restrict__ Eproc, int want_adjoint) {
+    float* __restrict__ qout, float* __restrict__ Eproc, int want_adjoint, MailArgs mail) {
   constexpr int T = S::T, NR = S::NR, NA = S::NA, BR = S::BR, BA = S::BA, L = S::L, K = S::K, D = S::D, H = S::H;
   constexpr int NH = NA / NSPLIT;
   static_assert(NA % NSPLIT == 0, "NSPLIT must divide n_angular");
   constexpr int HP = MlpPad<S>::HP, DP = MlpPad<S>::DP;
+  if (mail.mail && blockIdx.x == 0 && threadIdx.x == 0) deliver(mail);
   const float* __restrict__ dco = params + S::PD;  // derived coefficients: radial, then angular
   __shared__ float cA_s[T * T * NA * BA];
   __shared__ ImageTable itab;
@@ -962,22 +963,27 @@ __global__ __launch_bounds__(BS) void k_gather(int64_t n_slots, const int* __res
 // sum_k c_nk Q_k = hf sum_k ctil_nk T_k.  Then the first-layer weights
 // transposed, one thread per entry, for the kernels that give a hidden unit to
 // each lane.
+// The parameters themselves are copied on the way (given == params: they are in
+// place).
 template <class S>
-__global__ void k_derive(const float* __restrict__ params, float* __restrict__ out, float* __restrict__ wt) {
+__global__ void k_derive(const float* __restrict__ given, float* __restrict__ params) {
   constexpr int rowsR = S::T * S::T * S::NR, rowsA = S::T * S::T * S::NA;
   static_assert(S::H <= kWave, "the transposed weights hold one wavefront of hidden units");
+  float* out = params + S::PD;
+  float* wt = params + S::PWT;
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t k = r; k < S::P; k += (int64_t)gridDim.x * blockDim.x) params[k] = given[k];
   if (r < S::T * S::D * kWave) {
     const int h = r % kWave, d = (r / kWave) % S::D, z = r / (kWave * S::D);
-    wt[r] = h < S::H ? params[S::PCR + S::PCA + (int64_t)z * S::PMLP + h * S::D + d] : 0.0f;
+    wt[r] = h < S::H ? given[S::PCR + S::PCA + (int64_t)z * S::PMLP + h * S::D + d] : 0.0f;
   }
   if (r >= rowsR + rowsA) return;
   const int B = r < rowsR ? S::BR : S::BA;
   const int64_t o = r < rowsR ? (int64_t)r * S::BR : S::PCR + (int64_t)(r - rowsR) * S::BA;
   double sum = 0.0;
-  for (int k = 0; k < B; ++k) sum += (double)params[o + k];
-  out[o] = (float)((double)params[o] + sum);
-  for (int k = 1; k < B; ++k) out[o + k] = params[o + k];
+  for (int k = 0; k < B; ++k) sum += (double)given[o + k];
+  out[o] = (float)((double)given[o] + sum);
+  for (int k = 1; k < B; ++k) out[o + k] = given[o + k];
 }
 
 // ------------------------------------------------------------- launchers
@@ -1004,7 +1010,7 @@ static int launch_desc(hipStream_t st, const NepIO& io, const float* params, boo
   hipLaunchKernelGGL((k_desc<S, groups<S, NS>(), W, NET, BS>), dim3(g), dim3(BS), 0, st, io.n_slots, io.capA,
                      io.pos4, io.cfg_of, io.orig, io.cfgs, io.nbrR, io.cntR, io.vrev, io.cnR, io.ccR, io.cnA, io.cpA,
                      io.ccA, io.amask, io.flags, io.cut, params, io.fp, io.aR, io.Ei, io.qout, io.Eproc,
-                     want_adjoint ? 1 : 0);
+                     want_adjoint ? 1 : 0, io.mail);
   if constexpr (!NET) {
     const unsigned gk = (unsigned)((io.n_slots + kBlock - 1) / kBlock);
     const unsigned gn = gk < kNetBlocks ? gk : kNetBlocks;
@@ -1081,10 +1087,10 @@ int Launch<S>::gather(hipStream_t st, const NepIO& io, int variant, const SumArg
 }
 
 template <class S>
-int Launch<S>::derive(hipStream_t st, float* params) {
+int Launch<S>::derive(hipStream_t st, const float* given, float* params) {
   constexpr int rows = S::T * S::T * (S::NR + S::NA), wts = S::T * S::D * kWave;
   constexpr int n = rows > wts ? rows : wts;
-  hipLaunchKernelGGL(k_derive<S>, dim3((n + 127) / 128), dim3(128), 0, st, params, params + S::PD, params + S::PWT);
+  hipLaunchKernelGGL(k_derive<S>, dim3((n + 127) / 128), dim3(128), 0, st, given, params);
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }

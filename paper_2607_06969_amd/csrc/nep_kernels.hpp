@@ -60,6 +60,7 @@ struct NepIO {
   float* Fuser;  // [N][3] caller order, optional
   float4* Fproc; // [n_slots], optional
   float* Eproc;  // [n_slots] site energies in slot order, optional
+  MailArgs mail; // list flags for k_desc to deliver, if any
 };
 
 constexpr int kDescVariants = 10;  // compiled variants of k_desc (4..7: network in its own kernel;
@@ -93,9 +94,9 @@ struct Launch {
   // with the sums of an evaluation (may be null), or the half kick that
   // follows the forces of an MD step (may be null), in the same launch
   static int gather(hipStream_t st, const NepIO& io, int variant, const SumArgs<float>* sums, const KickArgs* kick);
-  // Writes the derived tables after the P parameters (the parameter buffer
-  // holds PALL floats).
-  static int derive(hipStream_t st, float* params);
+  // Copies the P parameters and writes the derived tables after them (the
+  // parameter buffer holds PALL floats).
+  static int derive(hipStream_t st, const float* given, float* params);
 };
 
 // Variant 0 of k_desc and k_force with one wavefront per atom, bit for bit the

@@ -119,6 +119,10 @@ __global__ __launch_bounds__(kWave) void k_desc_wave(NepIO io, const float* __re
 
   const int64_t ns = io.n_slots;
   const int64_t p = xcd_tile();
+  if (p == ns) {  // the block past the last slot (there only for the flags)
+    if (threadIdx.x == 0) deliver(io.mail);
+    return;
+  }
   const int lane = threadIdx.x;
   const int c = io.cfg_of[p];
   if (c < 0) {
@@ -622,7 +626,7 @@ __global__ __launch_bounds__(kWave) void k_force_wave(NepIO io, const float* __r
 
 template <class S>
 int WaveLaunch<S>::desc(hipStream_t st, const NepIO& io, const float* params, bool want_adjoint) {
-  hipLaunchKernelGGL(k_desc_wave<S>, dim3((unsigned)io.n_slots), dim3(kWave), 0, st, io, params, want_adjoint ? 1 : 0);
+  hipLaunchKernelGGL(k_desc_wave<S>, dim3((unsigned)io.n_slots + (io.mail.mail ? 1 : 0)), dim3(kWave), 0, st, io, params, want_adjoint ? 1 : 0);
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }

@@ -73,7 +73,7 @@ extern "C" int nepmi_compute_noalloc(nepmi_model* m, int32_t n_cfg, const int64_
   d->arena.used = 0;
   d->work.use_arena(&d->arena);
   bool again = false;
-  if ((rc = prepare_start(d->work, m->ops, m->hp, n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st, 0.0)) ||
+  if ((rc = prepare_start(d->work, m->ops, m->hp, n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st, 0.0, false)) ||
       (rc = prepare_end(d->work, m->ops, st, again)))
     return rc;
   return run_eval(d->work, m, dev_forces, dev_energy, dev_virial, dev_atom_energy, dev_atom_virial, st);

@@ -38,7 +38,8 @@ int Reducer::setup(int n_cfg_, const int64_t* atom_off, Uploader& up) {
     } while (a < b);
   }
   start[(size_t)n_cfg_] = (int)items.size();
-  host_done.assign((size_t)n_cfg_, 0);
+  host_done.assign((size_t)n_cfg_ + 1, 0);  // the last one counts all items
+ 
   n_cfg = n_cfg_;
   n_items = (int)items.size();
   int rc;

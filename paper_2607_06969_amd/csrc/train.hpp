@@ -62,10 +62,13 @@ struct TrainSeedArgs {
   const double* Eref;
   const double* V;
   const double* Vref;
-  float* lam;
+  const int* slot_of;
+  int64_t n_slots;
+  float4* lam4;  // [n_slots] (padding slots are not written)
   double* ebar;
   double* mu;
-  double* partF;
+  double* partF;  // [n_items]
+  int* done;      // items summed so far: 0 between launches
   double* loss;
 };
 
@@ -91,7 +94,7 @@ template <class S>
 struct TrainLaunch {
   static int seeds(hipStream_t st, const TrainSeedArgs& a);
   static int backward(hipStream_t st, TrainIO io, const Cutoffs& cut, const float* params, const float* lam,
-                      const int* base, double* part, double* grad64, float* grad);
+                      const int* base, double* part, double* grad64, float* grad, const MailArgs& mail);
   // float64 variant: forces, site energies (io.Ei) and per-atom virials
   // (a.Wi), all in caller order; the caller sums them per configuration ...
   static int forward64(hipStream_t st, TrainIOT<double> io, const CutoffsT<double>& cut, const F64Args& a,

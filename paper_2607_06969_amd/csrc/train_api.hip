@@ -17,7 +17,7 @@ int ensure_train(nepmi_model* m) {
                       2 * (size_t)o->H + 1;
   int rc;
   if ((rc = t.F.ensure(12 * N)) || (rc = t.E.ensure(8 * nc)) || (rc = t.V.ensure(72 * nc)) ||
-      (rc = t.lam.ensure(12 * N)) || (rc = t.ebar.ensure(8 * nc)) || (rc = t.mu.ensure(72 * nc)) ||
+      (rc = t.ebar.ensure(8 * nc)) || (rc = t.mu.ensure(72 * nc)) ||
       (rc = t.partF.ensure(8 * ni)) || (rc = t.lam4.ensure(16 * ns)))
     return rc;
   if ((int64_t)ns <= kTrainWaveSlots) return t.part.ensure(8 * train_wave_part((int64_t)ns, o->T, sumE));
@@ -71,13 +71,14 @@ TrainIO train_io(nepmi_model* m, const double* mu, const double* ebar) {
   return io;
 }
 
+// lam: caller order, or null if t.lam4 holds it in slot order
 int run_backward(nepmi_model* m, hipStream_t st, const double* ebar, const float* lam, const double* mu,
-                 float* dev_grad) {
+                 float* dev_grad, const MailArgs& mail = {}) {
   NepIO nio = m->io(nullptr, nullptr, nullptr);
   TrainIO io = train_io(m, mu, ebar);
   TrainBufs& t = m->tr;
   return m->ops->backward(st, io, nio.cut, m->params.ptr<float>(), lam, m->nbr.base.ptr<int>(), t.part.ptr<double>(),
-                          t.grad64.ptr<double>(), dev_grad);
+                          t.grad64.ptr<double>(), dev_grad, mail);
 }
 
 // ---- float64 variant
@@ -245,10 +246,9 @@ int nepmi_backward_params(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off
     int rc;
     if ((rc = ensure_train(m))) return rc;
     // beyond the one-pass gradient, the descriptor kernel writes the compact
-    // pair lists
-    if (m->nbr.n_slots > kTrainWaveSlots &&
-        (rc = m->ops->desc(st, m->io(nullptr, nullptr, nullptr), m->params.ptr<float>(), false, m->vdesc)))
-      return rc;
+    // pair lists (and delivers the list flags)
+    if (m->nbr.n_slots <= kTrainWaveSlots) return run_backward(m, st, dev_ebar, dev_lambda, dev_mu, dev_grad, m->nbr.post());
+    if ((rc = m->ops->desc(st, m->io(nullptr, nullptr, nullptr), m->params.ptr<float>(), false, m->vdesc))) return rc;
     return run_backward(m, st, dev_ebar, dev_lambda, dev_mu, dev_grad);
   });
 }
@@ -292,14 +292,17 @@ int nepmi_loss_grad(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
     a.Eref = dev_E_ref;
     a.V = t.V.ptr<double>();
     a.Vref = dev_V_ref;
-    a.lam = t.lam.ptr<float>();
+    a.slot_of = m->nbr.slot_of.ptr<int>();
+    a.n_slots = m->nbr.n_slots;
+    a.lam4 = t.lam4.ptr<float4>();
+    a.done = m->red.done_dev.ptr<int>() + n_cfg;
     a.ebar = t.ebar.ptr<double>();
     a.mu = t.mu.ptr<double>();
     a.partF = t.partF.ptr<double>();
     a.loss = dev_loss;
     if ((rc = m->ops->seeds(st, a))) return rc;
     if (!dev_grad) return NEPMI_OK;
-    return run_backward(m, st, t.ebar.ptr<double>(), t.lam.ptr<float>(), t.mu.ptr<double>(), dev_grad);
+    return run_backward(m, st, t.ebar.ptr<double>(), nullptr, t.mu.ptr<double>(), dev_grad);
   });
 }
 
