@@ -140,6 +140,7 @@ NepIO eval_io(EvalWork& w, const nepmi_hparams& hp, float* Fuser, float4* Fproc,
   o.Fproc = Fproc;
   o.Eproc = w.Eproc.ptr<float>();
   o.mail = nbr.post();
+  o.pairsA = nbr.pairs_within(hp.rc_angular);
   return o;
 }
 

@@ -85,10 +85,13 @@ struct Shape {
   static constexpr int64_t P = PCR + PCA + T * PMLP;
   // Derived tables stored after the parameters (see k_derive), 256-byte
   // aligned: coefficients with the "+1" of Q_k folded in (radial, angular), then
-  // the transposed first-layer weights [T][D][64], hidden units zero padded.
+  // the first-layer weights for a lane per hidden unit and for a lane per
+  // descriptor, four at a time: [T][WQ][64][4], W0[lane][4 q ..] in the rows q <
+  // ceil(D/4), then W0[4 q ..][lane], zero padded.
   static constexpr int64_t PD = (P + 63) / 64 * 64;
   static constexpr int64_t PWT = PD + (PCR + PCA + 63) / 64 * 64;
-  static constexpr int64_t PALL = PWT + (int64_t)T * D * 64;
+  static constexpr int WQ = (D + 3) / 4 + (H + 3) / 4;
+  static constexpr int64_t PALL = PWT + (int64_t)T * WQ * 256;
 };
 
 // Shapes compiled into the library: the 64-atom single-element test model,
@@ -132,6 +135,9 @@ constexpr int list_groups(int entries) {
 
 __device__ __forceinline__ uint32_t comp4(const uint4& v, int u) {
   return u == 0 ? v.x : (u == 1 ? v.y : (u == 2 ? v.z : v.w));
+}
+__device__ __forceinline__ float comp4(const float4& v, int u) {
+  return u == 0 ? v.x : u == 1 ? v.y : u == 2 ? v.z : v.w;
 }
 
 // Opaque copy of a group (see take_slot).

@@ -195,6 +195,7 @@ struct nepmi_md {
     o.Fuser = nullptr;
     o.Fproc = F4.ptr<float4>();
     o.Eproc = nullptr;
+    o.pairsA = nbr.pairs_within(m->hp.rc_angular);
     return o;
   }
 

@@ -1162,6 +1162,7 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
   const double rcl = rcR + skin_;
   std::vector<CfgDev> hc((size_t)n_cfg_);
   int64_t bins = 0, real = 0, most = 0;
+  double densest = 0.0;
   for (int c = 0; c < n_cfg_; ++c) {
     CfgDev& C = hc[(size_t)c];
     const double* H = cells + 9 * (size_t)c;
@@ -1201,6 +1202,7 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
     const int64_t nb = (int64_t)C.nb[0] * C.nb[1] * C.nb[2];
     real += nb;
     most = std::max(most, (C.n_atoms + nb - 1) / nb);
+    densest = std::max(densest, (double)C.n_atoms / fabs(det));
     bins += (int64_t)((C.nb[0] + 3) / 4) * ((C.nb[1] + 3) / 4) * ((C.nb[2] + 3) / 4) * 64;
   }
   // bin keys below 2^27: the list build packs a key and a 5-bit image code
@@ -1216,6 +1218,7 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
   total_bins = (int)bins;
   real_bins = (int)real;
   bin_atoms = (int)most;
+  density = densest;
   skin = skin_;
   const float rlR = (float)(rcR + skin_), rlA = (float)(rcA + skin_);
   rclR2 = rlR * rlR;
@@ -1248,17 +1251,9 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
     return rc;
   if (capR == 0) {
     // initial capacity from the densest configuration
-    double dmax = 0.0;
-    for (int c = 0; c < n_cfg_; ++c) {
-      const double* H = cells + 9 * (size_t)c;
-      double w[3], Hi[9], det;
-      cell_geometry(H, w, Hi, det);
-      const double dens = (double)hc[(size_t)c].n_atoms / fabs(det);
-      dmax = dens > dmax ? dens : dmax;
-    }
     const double vR = 4.18879020478639 * rlR * rlR * rlR, vA = 4.18879020478639 * rlA * rlA * rlA;
-    capR = (int)(1.5 * dmax * vR) + 16;
-    capA = (int)(1.5 * dmax * vA) + 16;
+    capR = (int)(1.5 * density * vR) + 16;
+    capA = (int)(1.5 * density * vA) + 16;
   }
   return ensure_lists(capR, capA);
 }

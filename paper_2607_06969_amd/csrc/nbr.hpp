@@ -141,6 +141,7 @@ struct NbrPipeline {
   int total_bins = 0;   // bins of every configuration in whole 4 x 4 x 4 tiles
   int real_bins = 0;    // those inside the cells
   int bin_atoms = 0;    // atoms per bin of the fullest configuration (mean over its bins, rounded up)
+  double density = 0.0; // atoms per volume of the densest configuration
   int capR = 0, capA = 0;
   float rclR2 = 0.f, rclA2 = 0.f;
   double skin = 0.0;
@@ -194,6 +195,8 @@ struct NbrPipeline {
   // the 4.5 us of any kernel behind another; otherwise build_start launches it.
   int build_start(hipStream_t st, const float* pos, const int32_t* species, bool post);
   MailArgs post() const;
+  // atoms within rc of a point at that density
+  float pairs_within(double rc) const { return (float)(density * 4.18879020478639 * rc * rc * rc); }
   int build_end(hipStream_t st, bool& regrown);
   int check_flags(hipStream_t st, int* host_flags);
 };

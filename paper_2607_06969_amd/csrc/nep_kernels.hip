@@ -960,22 +960,24 @@ __global__ __launch_bounds__(BS) void k_gather(int64_t n_slots, const int* __res
 // Derived tables.  Coefficients: ctil[..][n][0] = c[..][n][0] + sum_k c[..][n][k],
 // ctil[..][n][k] = c[..][n][k] for k >= 1, for every radial row (length BR)
 // and angular row (length BA).  With Q_k = hf (T_k + 1) this gives
-// sum_k c_nk Q_k = hf sum_k ctil_nk T_k.  Then the first-layer weights
-// transposed, one thread per entry, for the kernels that give a hidden unit to
-// each lane.
+// sum_k c_nk Q_k = hf sum_k ctil_nk T_k.  Then the first-layer weights, one
+// thread per entry, for the kernels that give a hidden unit or a descriptor to
+// each lane (see Shape).
 // The parameters themselves are copied on the way (given == params: they are in
 // place).
 template <class S>
 __global__ void k_derive(const float* __restrict__ given, float* __restrict__ params) {
   constexpr int rowsR = S::T * S::T * S::NR, rowsA = S::T * S::T * S::NA;
-  static_assert(S::H <= kWave, "the transposed weights hold one wavefront of hidden units");
+  static_assert(S::H <= kWave && S::D <= kWave, "the rows of weights hold one wavefront");
   float* out = params + S::PD;
   float* wt = params + S::PWT;
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   for (int64_t k = r; k < S::P; k += (int64_t)gridDim.x * blockDim.x) params[k] = given[k];
-  if (r < S::T * S::D * kWave) {
-    const int h = r % kWave, d = (r / kWave) % S::D, z = r / (kWave * S::D);
-    wt[r] = h < S::H ? given[S::PCR + S::PCA + (int64_t)z * S::PMLP + h * S::D + d] : 0.0f;
+  if (r < S::T * S::WQ * kWave * 4) {
+    constexpr int DQ = (S::D + 3) / 4;
+    const int u = r % 4, lane = r / 4 % kWave, q = r / (4 * kWave) % S::WQ, z = r / (4 * kWave * S::WQ);
+    const int h = q < DQ ? lane : 4 * (q - DQ) + u, d = q < DQ ? 4 * q + u : lane;
+    wt[r] = h < S::H && d < S::D ? given[S::PCR + S::PCA + (int64_t)z * S::PMLP + h * S::D + d] : 0.0f;
   }
   if (r >= rowsR + rowsA) return;
   const int B = r < rowsR ? S::BR : S::BA;
@@ -1088,7 +1090,7 @@ int Launch<S>::gather(hipStream_t st, const NepIO& io, int variant, const SumArg
 
 template <class S>
 int Launch<S>::derive(hipStream_t st, const float* given, float* params) {
-  constexpr int rows = S::T * S::T * (S::NR + S::NA), wts = S::T * S::D * kWave;
+  constexpr int rows = S::T * S::T * (S::NR + S::NA), wts = S::T * S::WQ * kWave * 4;
   constexpr int n = rows > wts ? rows : wts;
   hipLaunchKernelGGL(k_derive<S>, dim3((n + 127) / 128), dim3(128), 0, st, given, params);
   NEPMI_HIP(hipGetLastError());

@@ -1,7 +1,7 @@
 // nep_kernels.hpp -- NEP evaluation kernels for gfx950, templated on the shape.
 //
-// One thread evaluates one atom slot (one wavefront in small batches, see
-// nep_wave.hip); every wavefront holds one species (see
+// One thread evaluates one atom slot (a wavefront or half of one in small
+// batches, see nep_wave.hip); every wavefront holds one species (see
 // nbr.hip), so species-pair coefficients c[Z_i][.] and the network weights of
 // Z_i are read through the scalar unit.  Coefficients that depend on the
 // neighbour's species are read from LDS.  The kernels use a derived copy of
@@ -61,6 +61,7 @@ struct NepIO {
   float4* Fproc; // [n_slots], optional
   float* Eproc;  // [n_slots] site energies in slot order, optional
   MailArgs mail; // list flags for k_desc to deliver, if any
+  float pairsA = 0.f;  // angular pairs of an atom at the mean density of the fullest configuration
 };
 
 constexpr int kDescVariants = 10;  // compiled variants of k_desc (4..7: network in its own kernel;
@@ -99,14 +100,15 @@ struct Launch {
   static int derive(hipStream_t st, const float* given, float* params);
 };
 
-// Variant 0 of k_desc and k_force with one wavefront per atom, bit for bit the
+// Variant 0 of k_desc and k_force with a group of lanes per atom, bit for bit the
 // same results (nep_wave.hip), for batches that fit kWaveSlots slots.
 // With one thread per atom these kernels take the time of one walk up to about
-// 65,000 atoms (one wavefront per SIMD); with one wavefront the time grows with
-// the atoms.  k_desc + k_force of the Ge-Sb-Te model, thread -> wavefront (us):
-// 3,686 atoms 56 + 70 -> 15 + 18, 9,100 62 + 75 -> 28 + 31, 18,400 61 + 79 ->
-// 49 + 56, 29,500 54 (k_desc) -> 61.
-constexpr int64_t kWaveSlots = 24576;
+// 65,000 atoms (one wavefront per SIMD); with a group the time grows with the
+// atoms.  k_desc + k_force + k_gather, thread -> group (us): Ge-Sb-Te model
+// 9,285 atoms 146 -> 54, 19,812 147 -> 85, 34,707 164 -> 135, 46,872 166 -> 174;
+// Table 2 model 9,285 atoms 182 -> 65, 34,707 203 -> 187, 46,872 210 -> 242.
+// k_desc alone: 34,707 atoms 64 -> 51 and 78 -> 70, 46,872 68 -> 66 and 80 -> 91.
+constexpr int64_t kWaveSlots = 36864;
 template <class S>
 struct WaveLaunch {
   static int desc(hipStream_t st, const NepIO& io, const float* params, bool want_adjoint);
