@@ -1538,6 +1538,7 @@ template <class S>
 int TrainLaunch<S>::forward64(hipStream_t st, TrainIOT<double> io, const CutoffsT<double>& cut, const F64Args& a,
                               double* forces) {
   const int64_t ns = io.ns;
+  if (ns <= kWave64Slots) return Wave64<S>::forward(st, io, cut, a, forces);
   hipLaunchKernelGGL(k_fill64, dim3(blocks(4 * ns, 256)), dim3(256), 0, st, 4 * ns, 0.0,
                      reinterpret_cast<double*>(io.lam4));
   constexpr int NC = S::NA >= 4 ? 2 : 1;

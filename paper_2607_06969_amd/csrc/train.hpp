@@ -132,6 +132,20 @@ struct TrainWave {
                  double* part, R* grad);
 };
 
+// The float64 evaluation with one wavefront per atom (nep_wave64.hip), for io with
+// pos4, cfg_of, orig, cfgs, the list and Ei.  It serves batches of up to
+// kWave64Slots slots; larger ones take the passes of train.hip with a thread per
+// atom (whole evaluation, passes and one wavefront per atom, us: Ge-Sb-Te model
+// 2,555 atoms 350 and 125, 19,812 atoms 488 and 307, 39,402 atoms 595 and 511,
+// 58,570 atoms 700 and 692, 151,707 atoms 1354 and 1549; model of Table 2 2,555
+// atoms 478 and 147, 39,402 atoms 783 and 684, 58,570 atoms 899 and 930).
+constexpr int64_t kWave64Slots = 49152;
+template <class S>
+struct Wave64 {
+  static int forward(hipStream_t st, const TrainIOT<double>& io, const CutoffsT<double>& cut, const F64Args& a,
+                     double* forces);
+};
+
 // float64 helpers: stage positions in slot order, round positions to float32
 // (for the neighbour lists), fill a float64 array.
 int launch_stage64(hipStream_t st, const TrainIOT<double>& io, const F64Args& a, const float4* pos4f);

@@ -206,8 +206,9 @@ int nepmi_compute_f64(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, co
   int rc;
   if ((rc = prepare64(m, n_cfg, atom_off, cells, pbc, dev_pos, dev_species, dev_params, st, a))) return rc;
   F64Bufs& f = m->f64;
-  if ((rc = launch_fill64(st, n_cfg, 1.0, f.ebar1.ptr<double>())) ||
-      (rc = launch_fill64(st, 9 * (int64_t)n_cfg, 0.0, f.mu0.ptr<double>())))
+  // the seeds of the passes that large batches take
+  if (m->nbr.n_slots > kWave64Slots && ((rc = launch_fill64(st, n_cfg, 1.0, f.ebar1.ptr<double>())) ||
+                                        (rc = launch_fill64(st, 9 * (int64_t)n_cfg, 0.0, f.mu0.ptr<double>()))))
     return rc;
   double* Ei = dev_atom_energy ? dev_atom_energy : f.Ei.ptr<double>();
   TrainIOT<double> io = f64_io(m, f.mu0.ptr<double>(), f.ebar1.ptr<double>(), Ei);
