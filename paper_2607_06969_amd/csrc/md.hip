@@ -21,10 +21,22 @@ struct Dbl3 {
   double x, y, z;
 };
 
-__global__ void k_md_kick_drift(int64_t n_slots, MdConst mc, const int* __restrict__ cfg_of,
-                                const float4* __restrict__ F4, float4* __restrict__ vel4, Dbl3* __restrict__ xd,
-                                float4* __restrict__ pos4, const float4* __restrict__ ref4, int* __restrict__ flags) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Half kick, drift and the displacement check.  Blocks 0 .. n_items - 1 do the
+// sums of the step before (in a graph of several steps), which touch nothing that
+// this kernel writes: a launch less, and in small cells both are hardly longer
+// than the 4.5 us of any kernel behind another (3,686 atoms 10.9 us in two kernels,
+// 6.5 in one; 900,000 atoms 49 and 38).
+__global__ __launch_bounds__(256) void k_md_kick_drift(int64_t n_slots, MdConst mc, const int* __restrict__ cfg_of,
+                                                       const float4* __restrict__ F4, float4* __restrict__ vel4,
+                                                       Dbl3* __restrict__ xd, float4* __restrict__ pos4,
+                                                       const float4* __restrict__ ref4, int* __restrict__ flags,
+                                                       SumArgs<float> before) {
+  if ((int)blockIdx.x < before.n_items) {
+    __shared__ SumShared sh;
+    sum_item<256>((int)blockIdx.x, before, sh);
+    return;
+  }
+  const int64_t p = (int64_t)(blockIdx.x - before.n_items) * 256 + threadIdx.x;
   if (p >= n_slots || cfg_of[p] < 0) return;
   float4 x = pos4[p];
   const int z = __float_as_int(x.w);
@@ -246,10 +258,11 @@ struct nepmi_md {
   }
 
   // float64 sums of the energies and the virial
-  int sums(hipStream_t st) {
-    return red.run(st, red.args<float>(Ei.ptr<float>(), Wi.ptr<float>(), Ki.ptr<float>(), epot.ptr<double>(),
-                                       vir.ptr<double>(), ekin.ptr<double>()));
+  SumArgs<float> sum_args() const {
+    return red.args<float>(Ei.ptr<float>(), Wi.ptr<float>(), Ki.ptr<float>(), epot.ptr<double>(), vir.ptr<double>(),
+                           ekin.ptr<double>());
   }
+  int sums(hipStream_t st) { return red.run(st, sum_args()); }
 
   // Sort and lists; the sort takes the state back to caller order (wrapped)
   // and moves it into the new slot order.
@@ -281,12 +294,15 @@ struct nepmi_md {
     return nbr.launch_lists(st, n_species, gate);
   }
 
-  int step_launch(hipStream_t st, bool timed) {
+  // One step of several: the first leaves no sums before it to do, and all but the
+  // last leave theirs to the next.
+  int step_launch(hipStream_t st, bool timed, bool first, bool last) {
     const int64_t ns = nbr.n_slots;
     int* flags = nbr.flags.ptr<int>();
-    hipLaunchKernelGGL(k_md_kick_drift, dim3(nb256(ns)), dim3(256), 0, st, ns, mc, nbr.cfg_of.ptr<int>(),
-                       F4.ptr<float4>(), vel4.ptr<float4>(), xd.ptr<Dbl3>(), nbr.pos4.ptr<float4>(),
-                       ref4.ptr<float4>(), flags);
+    const SumArgs<float> before = first ? SumArgs<float>{} : sum_args();
+    hipLaunchKernelGGL(k_md_kick_drift, dim3(nb256(ns) + before.n_items), dim3(256), 0, st, ns, mc,
+                       nbr.cfg_of.ptr<int>(), F4.ptr<float4>(), vel4.ptr<float4>(), xd.ptr<Dbl3>(),
+                       nbr.pos4.ptr<float4>(), ref4.ptr<float4>(), flags, before);
     int rc;
     if ((rc = rebuild(st, flags + kFlagRebuild))) return rc;
     KickArgs kick;
@@ -297,7 +313,7 @@ struct nepmi_md {
     kick.flags = flags;
     kick.counters = counters.ptr<long long>();
     if ((rc = forces(st, &kick, timed))) return rc;
-    return sums(st);
+    return last ? sums(st) : NEPMI_OK;
   }
 
   void drop_graphs() {
@@ -314,7 +330,7 @@ struct nepmi_md {
   int capture_one(bool timed, int steps, hipGraph_t& graph_out, hipGraphExec_t& exec_out) {
     NEPMI_HIP(hipStreamBeginCapture(cap_stream, hipStreamCaptureModeThreadLocal));
     int rc = NEPMI_OK;
-    for (int s = 0; s < steps && !rc; ++s) rc = step_launch(cap_stream, timed);
+    for (int s = 0; s < steps && !rc; ++s) rc = step_launch(cap_stream, timed, s == 0, s == steps - 1);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(cap_stream, &g);
     if (rc) {
