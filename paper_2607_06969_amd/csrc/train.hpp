@@ -114,17 +114,19 @@ struct TrainLaunch {
 // pass against passes, us.  float32, Ge-Sb-Te model: 677 atoms 38 and 162, 9,285
 // atoms 120 and 190, 19,800 atoms 213 and 250, 39,402 atoms 370 and 348; model of
 // Table 2: 19,800 atoms 250 and 259, 27,173 atoms 351 and 335.  float64: 2,555
-// atoms 172 and 408, 46,872 atoms 1035 and 1128, Table 2 1273 and 1318, 74,000
+// atoms 142 and 408, 46,872 atoms 1000 and 1128, Table 2 1230 and 1318, 74,000
 // atoms 1910 and 1718).
 constexpr int64_t kTrainWaveSlots = 24576, kTrainWaveSlots64 = 49152;
 // Blocks: an atom per wavefront while the chip holds them all, then what it
-// holds in one round (float32) or two (float64).
+// holds in one round (two blocks per compute unit in float32, one in float64).
+template <class R>
 inline int train_wave_blocks(int64_t ns) {
-  const int64_t few = (ns + 3) / 4;
-  return (int)(few < 512 ? few : 512);
+  const int64_t few = (ns + 3) / 4, holds = sizeof(R) == 4 ? 512 : 256;
+  return (int)(few < holds ? few : holds);
 }
+template <class R>
 inline size_t train_wave_part(int64_t ns, int n_species, size_t entries) {
-  return (size_t)(train_wave_blocks(ns) + n_species) * entries;
+  return (size_t)(train_wave_blocks<R>(ns) + n_species) * entries;
 }
 template <class S, class R>
 struct TrainWave {

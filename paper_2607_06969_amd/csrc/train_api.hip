@@ -20,7 +20,7 @@ int ensure_train(nepmi_model* m) {
       (rc = t.ebar.ensure(8 * nc)) || (rc = t.mu.ensure(72 * nc)) ||
       (rc = t.partF.ensure(8 * ni)) || (rc = t.lam4.ensure(16 * ns)))
     return rc;
-  if ((int64_t)ns <= kTrainWaveSlots) return t.part.ensure(8 * train_wave_part((int64_t)ns, o->T, sumE));
+  if ((int64_t)ns <= kTrainWaveSlots) return t.part.ensure(8 * train_wave_part<float>((int64_t)ns, o->T, sumE));
   // the passes' hand-over arrays
   if ((rc = t.Sst.ensure(4 * ns * o->NA * o->K)) || (rc = t.Sdt.ensure(4 * ns * o->NA * o->K)) ||
       (rc = t.q.ensure(4 * ns * o->D)) || (rc = t.qd.ensure(4 * ns * o->D)) ||
@@ -99,7 +99,7 @@ int ensure_f64(nepmi_model* m) {
       (rc = f.fA.ensure(32 * ns * (size_t)(m->nbr.capA > 0 ? m->nbr.capA : 1))) ||
       (rc = f.aR.ensure(8 * ns * o->T * o->BR)))
     return rc;
-  if ((int64_t)ns <= kTrainWaveSlots64) return f.part.ensure(8 * train_wave_part((int64_t)ns, o->T, sumE));
+  if ((int64_t)ns <= kTrainWaveSlots64) return f.part.ensure(8 * train_wave_part<double>((int64_t)ns, o->T, sumE));
   // the passes' hand-over arrays
   if ((rc = f.Sdt.ensure(8 * ns * o->NA * o->K)) || (rc = f.qd.ensure(8 * ns * o->D)) ||
       (rc = f.Pb.ensure(8 * ns * o->T * o->BR)) || (rc = f.Pdn.ensure(8 * ns * o->T * o->BR)) ||

@@ -73,8 +73,8 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
   using G = GradEntries<S>;
   constexpr int PC = 16;                                         // angular pairs in LDS at a time
   constexpr int RR = 32;                                         // radial rows in LDS at a time
-  constexpr int RW = (2 * BR + T) | 1, YW = K | 1, GW = NA | 1, QW = (2 * BA) | 1, AW = 7;
-  constexpr int NS = (NA * K + 63) / 64;                         // S accumulators per lane
+  constexpr int RW = (2 * BR) | 1, YW = K | 1, GW = (NA + 3) / 4 * 4, QW = (2 * BA) | 1, AW = 7;
+  constexpr int LQ = 64 / K, NS = NA / LQ;                       // lanes per lm, S accumulators per lane
   constexpr int NC = (NR * T * BR + 63) / 64, NG = (NA * BA + 63) / 64;
   constexpr int kAng = PC * (2 * YW + 2 * GW + QW + 2), kRad = RR * RW;
   constexpr int kBuf = kAng > kRad ? kAng : kRad;
@@ -186,6 +186,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
     for (int x = 0; x < 9; ++x) mu[x] = (R)io.mu[9 * c + x];
     const int n = cur.n;
+    const int lm = lane % K, n0 = (lane / K < LQ ? lane / K : LQ - 1) * NS;  // S accumulators: lm, n0 ..
     R P = R(0), Pd = R(0), Sa[NS], Sb[NS];
 #pragma unroll
     for (int r = 0; r < NS; ++r) Sa[r] = Sb[r] = R(0);
@@ -273,8 +274,19 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
     //      sum_{j in b} dQ_k (u.t); lanes (n, lm): S and its derivative along t
     walk(
         [&](bool in, const PV<R>& v, R rt) {
-          const uint64_t mR = __ballot(in);
-          const int kr = ballot_rank(mR), nr = __builtin_popcountll(mR);
+          // rows by species: each accumulator runs over its own
+          int kr = 0, nr = 0, j0 = 0, j1 = 0;
+#pragma unroll
+          for (int b = 0; b < T; ++b) {
+            const uint64_t mR = __ballot(in && (T == 1 || v.zj == b));
+            if (T == 1 || v.zj == b) kr = nr + ballot_rank(mR);
+            const int nb = __builtin_popcountll(mR);
+            if (lane / BR == b) {
+              j0 = nr;
+              j1 = nr + nb;
+            }
+            nr += nb;
+          }
           R Q[BR], dQ[BR], ut = R(0);
           if (in) {
             const R d = sqrt_(v.d2);
@@ -290,19 +302,14 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
                 row[k] = Q[k];
                 row[BR + k] = dQ[k] * ut;
               }
-#pragma unroll
-              for (int b = 0; b < T; ++b) row[2 * BR + b] = (T == 1 || v.zj == b) ? R(1.0) : R(0.0);
             }
             lds_order();
-            if (lane < T * BR) {
-              const R* mb = m.buf + 2 * BR + lane / BR;
-              const R* q = m.buf + lane % BR;
-              const int cnt = nr - r0 < RR ? nr - r0 : RR;
-#pragma unroll 8
-              for (int i = 0; i < cnt; ++i) {
-                P = fma_(mb[i * RW], q[i * RW], P);
-                Pd = fma_(mb[i * RW], q[i * RW + BR], Pd);
-              }
+            const R* q = m.buf - r0 * RW + lane % BR;
+            const int i1 = j1 < r0 + RR ? j1 : r0 + RR;
+#pragma unroll 4
+            for (int i = j0 > r0 ? j0 : r0; i < i1; ++i) {
+              P += q[i * RW];
+              Pd += q[i * RW + BR];
             }
           }
         },
@@ -322,21 +329,16 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
             dS[i * GW + nn] = gp * uS[i];
           }
           lds_order();
-          const R *gr[NS], *yr[NS];
-#pragma unroll
-          for (int r = 0; r < NS; ++r) {
-            const int a = lane + 64 * r < NA * K ? lane + 64 * r : NA * K - 1;
-            gr[r] = gS + a / K;
-            yr[r] = yS + a % K;
-          }
 #pragma unroll 2
-          for (int i = 0; i < np; ++i)
+          for (int i = 0; i < np; ++i) {
+            const R y = yS[i * YW + lm], yl = lS[i * YW + lm];
 #pragma unroll
             for (int r = 0; r < NS; ++r) {
-              const R g = gr[r][i * GW], y = yr[r][i * YW];
+              const R g = gS[i * GW + n0 + r];
               Sa[r] = fma_(g, y, Sa[r]);
-              Sb[r] = fma_(gr[r][i * GW + PC * GW], y, fma_(g, yr[r][i * YW + PC * YW], Sb[r]));
+              Sb[r] = fma_(dS[i * GW + n0 + r], y, fma_(g, yl, Sb[r]));
             }
+          }
         });
     lds_order();
     if (lane < T * BR) {
@@ -345,9 +347,9 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
     }
 #pragma unroll
     for (int r = 0; r < NS; ++r)
-      if (lane + 64 * r < NA * K) {
-        m.S_[lane + 64 * r] = Sa[r];
-        m.Sd[lane + 64 * r] = Sb[r];
+      if (lane / K < LQ) {
+        m.S_[(n0 + r) * K + lm] = Sa[r];
+        m.Sd[(n0 + r) * K + lm] = Sb[r];
       }
     lds_order();
     ahead_entry(nxt, pn);
@@ -635,7 +637,7 @@ __global__ __launch_bounds__(32 * kFinalRuns) void k_train_final(const int* __re
 template <class S, class R>
 int TrainWave<S, R>::run(hipStream_t st, const TrainIOT<R>& io, const CutoffsT<R>& cut, const R* params,
                          const int* base, double* part, R* grad) {
-  const int want = train_wave_blocks(io.ns);
+  const int want = train_wave_blocks<R>(io.ns);
   hipLaunchKernelGGL((k_train_wave<S, R>), dim3((unsigned)(want + S::T)), dim3(64 * kTWaves), 0, st, io, cut, params,
                      base, want, part);
   hipLaunchKernelGGL((k_train_final<S, R>), dim3((unsigned)((S::T * GradEntries<S>::N + 31) / 32)),
