@@ -123,7 +123,8 @@ void nepmi_model_destroy(nepmi_model *m);
  *   dev_energy: double[n_cfg]; dev_forces: float[N*3]; dev_virial:
  *   double[9*n_cfg]; dev_atom_energy: float[N] or NULL; dev_atom_virial:
  *   float[N*9] or NULL (row-major 3x3 per atom, -sum_j dE_i/dr_ij (x) r_ij).
- * Synchronises `stream` once to check the neighbour capacity (twice when the
+ * Waits once for the neighbour lists on `stream` (not for the work launched
+ * behind them) to check the neighbour capacity (twice when the
  * lists must grow); the rest of the call is asynchronous. */
 int nepmi_compute(nepmi_model *m, int32_t n_cfg, const int64_t *atom_off, const double *cells, const int32_t *pbc,
                   const float *dev_pos, const int32_t *dev_species, double *dev_energy, float *dev_forces,
@@ -176,7 +177,9 @@ int nepmi_neighbors(nepmi_model *m, int32_t n_cfg, const int64_t *atom_off, cons
  * one of its own on dense 16x16x4 matrix products.  Descriptor variants:
  * 0..3 network in the kernel, 4..7 network apart, 8 and 9 variant 0 in
  * blocks of 128 and 512 threads.  Force variants: 0..3, and 4 and 5 variant 0
- * in blocks of 128 and 512.  The gather runs in blocks of 256, 128, 512 or
+ * in blocks of 128 and 512.  Variant 0 of both gives an atom a group of lanes
+ * instead of a thread in batches of up to 36,864 atoms (less 64 per species),
+ * with the same results bit for bit.  The gather runs in blocks of 256, 128, 512 or
  * 1024 threads (gather variants 0..3).  All compute the same result:
  * descriptors bitwise across descriptor variants, energies bitwise within
  * each network form and up to float32 summation order across them, forces
@@ -272,10 +275,9 @@ void nepmi_md_destroy(nepmi_md *md);
  * graph (the event nodes cost a few microseconds each).  ms_per_launch: host
  * double[3] = average duration (ms) of descriptors + network, pair forces +
  * virial, force gather (with the second half kick, which it carries) over the
- * timed replays.  Chunks, checkpoints and
- * overflow recovery as nepmi_md_step (a chunk run again records its steps
- * again).  Errors as nepmi_md_step, and NEPMI_UNSUPPORTED if the graph could
- * not be built with timing nodes. */
+ * timed replays.  Chunks, checkpoints and overflow recovery as nepmi_md_step
+ * (a chunk run again records its steps again).  Errors as nepmi_md_step, and
+ * NEPMI_UNSUPPORTED if the graph could not be built with timing nodes. */
 int nepmi_md_step_timed(nepmi_md *md, int32_t n_steps, double *ms_per_launch, void *stream);
 
 /* Average duration of each hot kernel, measured with HIP events recorded on

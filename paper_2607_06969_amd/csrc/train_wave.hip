@@ -9,8 +9,8 @@
 // the lanes hold over all atoms of their wavefront: lane h the row h of the
 // first layer, and so on.  Nothing per atom goes through memory.
 //
-// A wavefront's atoms are of one species.  A wavefront takes at most about 24
-// atoms, whose shares are summed in the arithmetic of the kernel; the block's
+// A wavefront's atoms are of one species.  A wavefront takes at most 12
+// atoms (48 in float64), whose shares are summed in its arithmetic; the block's
 // wavefronts are then added in float64, in order, and the blocks by
 // k_train_final, in order: the order depends on the batch only.
 #include "train_device.hpp"
@@ -64,7 +64,7 @@ __device__ __forceinline__ void load_coef(const double* __restrict__ src, double
 // Bound by the latency of its phases at two wavefronts per SIMD (255 registers,
 // 11.5 KB of LDS each; the vector units are busy 40 % of the time), some 2,300
 // vector and 500 LDS instructions per atom.  Loss gradient of 9,031 atoms of the
-// Ge-Sb-Te model: 165 us in seven kernels, 88 in this one and the sum.
+// Ge-Sb-Te model: 165 us in seven kernels, 83 in this one and the sum.
 template <class S, class R>
 __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2))) void k_train_wave(
     TrainIOT<R> io, CutoffsT<R> cut, const R* __restrict__ params, const int* __restrict__ base, int want,
