@@ -13,8 +13,8 @@
 //
 // Neighbour entries are 32-bit: slot index (27 bits) | image code (5 bits),
 // code = (w0+1)*9 + (w1+1)*3 + (w2+1) for the lattice shift w in {-1,0,1}^3.
-// Lists are column-major, entry k of slot p at [k * n_slots + p].  The
-// Verlet list holds pairs within rc_radial + skin; at every evaluation the
+// Lists are stored in groups of four entries, group g of slot p as one 16-byte
+// word at [g * n_slots + p] (group_index).  The Verlet list holds pairs within rc_radial + skin; at every evaluation the
 // descriptor kernel filters it into compact lists of the pairs within
 // rc_radial and within rc_angular, which all later kernels iterate.
 #include "nbr.hpp"
