@@ -137,7 +137,9 @@ int nepmi_compute(nepmi_model *m, int32_t n_cfg, const int64_t *atom_off, const 
  * buffer (neighbour lists, processing order, per-atom arrays, reduction plan)
  * is carved from one static device array of 64 MiB per GPU, which each GPU
  * the library runs on holds until the process ends; no hipMalloc or hipFree
- * is called (the model's parameters were allocated by nepmi_model_create).
+ * is called, and no host memory is allocated or freed for the GPU (the model's
+ * parameters and its 128 KiB of pinned host memory are nepmi_model_create's;
+ * tables of more configurations than fit it, some 500, are copied without it).
  * A batch whose work space exceeds 64 MiB (about 2.1 kB per atom with the
  * three-species Ge-Sb-Te model: some 30,000 atoms) returns NEPMI_INVALID_ARG.
  * All calls on one GPU share that array and it keeps the last call's

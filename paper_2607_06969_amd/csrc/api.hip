@@ -85,21 +85,22 @@ int prepare_start(EvalWork& w, const Ops* ops, const nepmi_hparams& hp, int n_cf
                   const double* cells, const int32_t* pbc, const float* pos, const int32_t* species, hipStream_t st,
                   double skin, bool post) {
   int rc;
-  // the flags of an earlier build whose call ended in an error: its upload may
-  // still read the pinned tables
-  if (w.nbr.waiting) {
-    NEPMI_HIP(hipDeviceSynchronize());
-    w.nbr.waiting = false;
-  }
   if ((rc = w.nbr.setup(n_cfg, atom_off, cells, pbc, ops->T, hp.rc_radial, hp.rc_angular, skin)) ||
       (rc = w.red.setup(n_cfg, atom_off, w.nbr.up)) || (rc = eval_buffers(w, ops)))
     return rc;
-  return w.nbr.build_start(st, pos, species, post);
+  return settle(w, st, w.nbr.build_start(st, pos, species, post));
+}
+
+int settle(EvalWork& w, hipStream_t st, int rc) {
+  if (!rc) return rc;
+  w.nbr.unsent = false;
+  if (hipStreamSynchronize(st) != hipSuccess) (void)hipGetLastError();
+  return rc;
 }
 
 int prepare_end(EvalWork& w, const Ops* ops, hipStream_t st, bool& again) {
   const int rc = w.nbr.build_end(st, again);
-  return rc || !again ? rc : eval_buffers(w, ops);
+  return settle(w, st, rc || !again ? rc : eval_buffers(w, ops));
 }
 
 NepIO eval_io(EvalWork& w, const nepmi_hparams& hp, float* Fuser, float4* Fproc, float* qout) {
@@ -242,10 +243,12 @@ int nepmi_model_create(const nepmi_hparams* hp, nepmi_model** out) {
   if (!m) return NEPMI_INVALID_ARG;
   m->hp = *hp;
   m->ops = ops;
-  if (hipGetDevice(&m->device) != hipSuccess || (rc = m->params.ensure(4 * (size_t)ops->P_alloc))) {
+  if (hipGetDevice(&m->device) != hipSuccess || (rc = m->params.ensure(4 * (size_t)ops->P_alloc)) ||
+      (rc = m->host.take())) {
     delete m;
     return rc ? rc : NEPMI_HIP_ERROR;
   }
+  m->nbr.use_pinned(m->host);
   *out = m;
   return NEPMI_OK;
 }

@@ -437,7 +437,9 @@ int nepmi_md_create(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
   md->m = m;
   md->n_species = m->ops->T;
   int rc = NEPMI_OK;
+  PinBlock pinned;  // of the upload below; what fails waits for what it has launched
   auto fail = [&](int code) {
+    if (hipStreamSynchronize(st) != hipSuccess) (void)hipGetLastError();
     delete md;
     return code;
   };
@@ -452,6 +454,8 @@ int nepmi_md_create(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
   md->mc.dt = (float)dt_fs;
   md->mc.half_skin2 = (float)(0.25 * skin * skin);
   NbrPipeline& nb = md->nbr;
+  if ((rc = pinned.take())) return fail(rc);
+  nb.use_pinned(pinned);
   if ((rc = nb.setup(n_cfg, atom_off, cells, pbc, md->n_species, m->hp.rc_radial, m->hp.rc_angular, skin)))
     return fail(rc);
   if ((rc = md->red.setup(n_cfg, atom_off, nb.up))) return fail(rc);
@@ -514,6 +518,7 @@ int nepmi_md_create(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
     return fail(hip_fail(hipGetLastError(), "hipStreamCreate"));
   if ((rc = md->capture())) return fail(rc);
   if (hipStreamSynchronize(st) != hipSuccess) return fail(hip_fail(hipGetLastError(), "hipStreamSynchronize"));
+  nb.up.pin = nullptr;
   *out = md;
   return NEPMI_OK;
 }

@@ -68,6 +68,9 @@ int prepare_start(EvalWork& w, const Ops* ops, const nepmi_hparams& hp, int n_cf
                   const double* cells, const int32_t* pbc, const float* pos, const int32_t* species, hipStream_t st,
                   double skin, bool post);
 int prepare_end(EvalWork& w, const Ops* ops, hipStream_t st, bool& again);
+// rc; if it is an error, after what has been launched on `st` is done (the pinned
+// block and the caller's inputs may still be read by it).  Both parts end so.
+int settle(EvalWork& w, hipStream_t st, int rc);
 // Kernel arguments of an evaluation on `w` (optional caller-order forces,
 // slot-order forces and descriptors).
 NepIO eval_io(EvalWork& w, const nepmi_hparams& hp, float* Fuser, float4* Fproc, float* qout);
@@ -78,6 +81,7 @@ struct nepmi_model : nepmi::EvalWork {
   nepmi_hparams hp{};
   const nepmi::Ops* ops = nullptr;
   nepmi::DevBuf params;
+  nepmi::PinBlock host;  // pinned memory
   nepmi::TrainBufs tr;
   nepmi::F64Bufs f64;
   int device = 0;
@@ -98,9 +102,10 @@ struct nepmi_model : nepmi::EvalWork {
     last.valid = false;
     int rc;
     bool again = false;
-    if ((rc = nepmi::prepare_start(*this, ops, hp, n_cfg, atom_off, cells, pbc, pos, species, st, 0.0, true)) ||
-        (rc = launch()) || (rc = nepmi::prepare_end(*this, ops, st, again)) || (again && (rc = launch())))
+    if ((rc = nepmi::prepare_start(*this, ops, hp, n_cfg, atom_off, cells, pbc, pos, species, st, 0.0, true)))
       return rc;
+    if ((rc = launch()) || (rc = nepmi::prepare_end(*this, ops, st, again)) || (again && (rc = launch())))
+      return nepmi::settle(*this, st, rc);
     keep(n_cfg, atom_off, cells, pbc, pos, species, 0.0);
     return NEPMI_OK;
   }

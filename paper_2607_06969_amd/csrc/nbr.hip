@@ -21,6 +21,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 
 namespace nepmi {
 
@@ -1079,19 +1080,38 @@ static void cell_geometry(const double* H, double w[3], double Hi[9], double& de
   }
 }
 
-int PinBuf::ensure(size_t n) {
-  if (n <= bytes && p) return NEPMI_OK;
-  if (p) (void)hipHostFree(p);
-  p = nullptr;
-  bytes = 0;
-  const size_t want = n < 4096 ? 4096 : n + n / 2;
-  NEPMI_HIP(hipHostMalloc(&p, want, hipHostMallocDefault));
-  bytes = want;
+// Free blocks of the pool.
+struct PinFree {
+  PinFree* next;
+};
+static std::mutex g_pin_mutex;
+static PinFree* g_pin_free = nullptr;
+
+int PinBlock::take() {
+  if (p) return NEPMI_OK;
+  std::lock_guard<std::mutex> lock(g_pin_mutex);
+  if (!g_pin_free) {
+    constexpr int kBlocks = 16;  // per chunk
+    void* chunk = nullptr;
+    NEPMI_HIP(hipHostMalloc(&chunk, kBlocks * kPinBytes,
+                            hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent));
+    for (int k = 0; k < kBlocks; ++k) {
+      PinFree* b = reinterpret_cast<PinFree*>(static_cast<char*>(chunk) + k * kPinBytes);
+      b->next = g_pin_free;
+      g_pin_free = b;
+    }
+  }
+  p = reinterpret_cast<char*>(g_pin_free);
+  g_pin_free = g_pin_free->next;
   return NEPMI_OK;
 }
 
-PinBuf::~PinBuf() {
-  if (p) (void)hipHostFree(p);
+PinBlock::~PinBlock() {
+  if (!p) return;
+  std::lock_guard<std::mutex> lock(g_pin_mutex);
+  PinFree* b = reinterpret_cast<PinFree*>(p);
+  b->next = g_pin_free;
+  g_pin_free = b;
 }
 
 __global__ void k_upload(UploadArgs a) {
@@ -1109,13 +1129,18 @@ int Uploader::add(const void* src, size_t bytes, DevBuf& dst) {
   return NEPMI_OK;
 }
 
-int Uploader::plan(int* clear, int n_clear, UploadArgs& a) {
+int Uploader::plan(hipStream_t st, int* clear, int n_clear, UploadArgs& a) {
   size_t total = 0;
   for (const Table& t : tables) total += (t.bytes + 15) / 16 * 16;
-  const int rc = pin.ensure(total);
-  if (rc) return rc;
   a = UploadArgs{};
-  char* h = static_cast<char*>(pin.p);
+  a.clear = clear;
+  a.n_clear = n_clear;
+  if (total > kPinBytes - kPinMail) {
+    for (const Table& t : tables) NEPMI_HIP(hipMemcpyAsync(t.dst->p, t.src, t.bytes, hipMemcpyHostToDevice, st));
+    tables.clear();
+    return NEPMI_OK;
+  }
+  char* h = pin + kPinMail;
   for (const Table& t : tables) {
     const size_t n = (t.bytes + 15) / 16;
     memcpy(h, t.src, t.bytes);
@@ -1126,8 +1151,6 @@ int Uploader::plan(int* clear, int n_clear, UploadArgs& a) {
     h += 16 * n;
   }
   tables.clear();
-  a.clear = clear;
-  a.n_clear = n_clear;
   a.words = (int64_t)(total / 16);
   return NEPMI_OK;
 }
@@ -1142,7 +1165,7 @@ static int launch_upload(hipStream_t st, const UploadArgs& a) {
 
 int Uploader::run(hipStream_t st, int* clear, int n_clear) {
   UploadArgs a;
-  const int rc = plan(clear, n_clear, a);
+  const int rc = plan(st, clear, n_clear, a);
   return rc ? rc : launch_upload(st, a);
 }
 
@@ -1334,19 +1357,16 @@ MailArgs NbrPipeline::post() const {
   MailArgs m;
   if (!unsent) return m;
   m.flags = flags.ptr<int>();
-  m.mail = static_cast<int*>(mail.p);
-  m.number = builds;
+  m.mail = mail();
   return m;
 }
 
 int NbrPipeline::build_start(hipStream_t st, const float* pos, const int32_t* species, bool post_later) {
-  int rc = mail.ensure(sizeof(int) * (kFlagCount + 1));
-  if (rc) return rc;
-  if (builds == 0) static_cast<int*>(mail.p)[kFlagCount] = 0;
-  waiting = true;
-  builds = builds == INT32_MAX ? 1 : builds + 1;
+  static_assert(sizeof(int) * (kFlagCount + 1) <= kPinMail, "the flags fit their part of the block");
+  int rc;
   UploadArgs u;
-  if ((rc = up.plan(flags.ptr<int>(), kFlagCount, u)) ||
+  __atomic_store_n(&mail()[kFlagCount], 0, __ATOMIC_RELEASE);
+  if ((rc = up.plan(st, flags.ptr<int>(), kFlagCount, u)) ||
       (rc = launch_sort(st, pos, 3, species, n_species, nullptr, nullptr, nullptr, &u)) ||
       (rc = launch_lists(st, n_species, nullptr)))
     return rc;
@@ -1356,12 +1376,12 @@ int NbrPipeline::build_start(hipStream_t st, const float* pos, const int32_t* sp
   return NEPMI_OK;
 }
 
-// Wait until the stream has delivered the flags of build `number`.  The host
+// Wait until the stream has delivered the flags.  The host
 // watches the pinned word (a synchronisation of the stream would also wait for
 // the work launched behind the lists); every so often it asks the stream, which
 // ends the wait if the stream has failed or finished.
-static int await_mail(hipStream_t st, const int* mail, int number) {
-  for (unsigned n = 1; __atomic_load_n(&mail[kFlagCount], __ATOMIC_ACQUIRE) != number; ++n) {
+static int await_mail(hipStream_t st, const int* mail) {
+  for (unsigned n = 1; !__atomic_load_n(&mail[kFlagCount], __ATOMIC_ACQUIRE); ++n) {
     if (n % 16384) {
       __builtin_ia32_pause();
       continue;
@@ -1372,7 +1392,7 @@ static int await_mail(hipStream_t st, const int* mail, int number) {
       continue;
     }
     if (e != hipSuccess) return hip_fail(e, "hipStreamQuery (neighbour lists)");
-    if (__atomic_load_n(&mail[kFlagCount], __ATOMIC_ACQUIRE) == number) break;
+    if (__atomic_load_n(&mail[kFlagCount], __ATOMIC_ACQUIRE)) break;
     set_error("the neighbour build ended without its flags");
     return NEPMI_HIP_ERROR;
   }
@@ -1382,11 +1402,10 @@ static int await_mail(hipStream_t st, const int* mail, int number) {
 int NbrPipeline::build_end(hipStream_t st, bool& regrown) {
   regrown = false;
   unsent = false;  // delivered by what has been launched
-  int* m = static_cast<int*>(mail.p);
+  int* m = mail();
   for (int attempt = 0; attempt < 2; ++attempt) {
-    int rc = await_mail(st, m, builds);
+    int rc = await_mail(st, m);
     if (rc) return rc;
-    waiting = false;
     int hf[kFlagCount];
     memcpy(hf, m, sizeof hf);
     if ((rc = flag_errors(hf))) return rc;
@@ -1403,8 +1422,7 @@ int NbrPipeline::build_end(hipStream_t st, bool& regrown) {
     if ((rc = ensure_lists(hf[kFlagMaxR] + 8, hf[kFlagMaxA] + 8))) return rc;
     fill_int(st, flags.ptr<int>(), kFlagCount, 0, nullptr);
     if ((rc = launch_lists(st, n_species, nullptr))) return rc;
-    builds = builds == INT32_MAX ? 1 : builds + 1;
-    waiting = true;
+    __atomic_store_n(&m[kFlagCount], 0, __ATOMIC_RELEASE);
     unsent = true;
     mail_flags(st, post());
     unsent = false;

@@ -50,15 +50,21 @@ struct DevBuf {
   DevBuf& operator=(const DevBuf&) = delete;
 };
 
-// Pinned host memory that grows on demand.
-struct PinBuf {
-  void* p = nullptr;
-  size_t bytes = 0;
-  int ensure(size_t n);
-  ~PinBuf();
-  PinBuf() = default;
-  PinBuf(const PinBuf&) = delete;
-  PinBuf& operator=(const PinBuf&) = delete;
+// A handle's block of pinned host memory: the list flags on their way to the
+// host (the first kPinMail bytes), then tables on their way to the GPU.  Blocks
+// come from a pool that grows by a chunk when more handles live than ever before
+// and keeps its memory until the process ends: a call never allocates or frees
+// host memory, and host memory that a kernel has read is never unmapped.  A
+// handle gives its block back when nothing on the GPU uses it any more (every
+// call that ends in an error has waited for its stream, see settle).
+constexpr size_t kPinBytes = (size_t)128 << 10, kPinMail = 128;
+struct PinBlock {
+  char* p = nullptr;
+  int take();  // from the pool, unless one is held
+  ~PinBlock();
+  PinBlock() = default;
+  PinBlock(const PinBlock&) = delete;
+  PinBlock& operator=(const PinBlock&) = delete;
 };
 
 struct UploadArgs {
@@ -74,37 +80,37 @@ struct UploadArgs {
   int64_t words;  // 16-byte words of all tables
 };
 
-// Host tables on their way to device buffers: copied into pinned memory, then
-// moved by one kernel (a copy call for each table costs the host some 10 us and
-// the stream 5).  The pinned memory is free again once the stream has passed
-// the kernel; the owner waits for that before the next upload.
+// Host tables on their way to device buffers: copied into the handle's pinned
+// block, then moved by one kernel (a copy call for each table costs the host some
+// 10 us and the stream 5).  The block is free again once the stream has passed the
+// kernel; the owner waits for that before the next upload.  Tables that exceed
+// the block (some 500 configurations) are copied by the runtime instead.
 struct Uploader {
   struct Table {
     const void* src;
     DevBuf* dst;
     size_t bytes;
   };
-  PinBuf pin;
+  char* pin = nullptr;  // the handle's block
   std::vector<Table> tables;
   // dst receives the bytes (and is sized for them)
   int add(const void* src, size_t bytes, DevBuf& dst);
   // The upload of the added tables, clearing n_clear ints at clear: for a kernel
-  // that does it (upload_part), and launched by itself.
-  int plan(int* clear, int n_clear, UploadArgs& out);
+  // on st that does it (upload_part), and launched by itself.
+  int plan(hipStream_t st, int* clear, int n_clear, UploadArgs& out);
   int run(hipStream_t st, int* clear, int n_clear);
 };
 
 // The list flags on their way to the host: the kernel that gets these writes
-// them into pinned memory, then the number of their build.
+// them into pinned memory, then a one behind them (a zero before).
 struct MailArgs {
   const int* flags = nullptr;
   int* mail = nullptr;  // null: nothing to deliver
-  int number = 0;
 };
 __device__ __forceinline__ void deliver(const MailArgs& m) {
   for (int k = 0; k < kFlagCount; ++k) m.mail[k] = m.flags[k];
   __threadfence_system();
-  __hip_atomic_store(&m.mail[kFlagCount], m.number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&m.mail[kFlagCount], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // State that a rebuild moves from caller order into the new slot order along
@@ -162,10 +168,10 @@ struct NbrPipeline {
                                              // in groups of four entries (see list_groups)
   DevBuf flags;
   Uploader up;
-  PinBuf mail;          // the flags as the host reads them, then the number of the build they belong to
-  int builds = 0;       // number of the last build started
-  bool waiting = false; // its flags have not been read yet
-  bool unsent = false;  // a kernel launched on the lists is to deliver them (post)
+  bool unsent = false;  // a kernel launched on the lists is to deliver the flags (post)
+  // Work in the pinned block of a handle from now on.
+  void use_pinned(const PinBlock& b) { up.pin = b.p; }
+  int* mail() const { return reinterpret_cast<int*>(up.pin); }
 
   // Host-side setup of a batch: validates the cells, computes bins, sizes
   // buffers and adds the configuration tables to `up`.  pbc: host int32[3
@@ -175,8 +181,8 @@ struct NbrPipeline {
             double rcA, double skin);
   // Sizes the lists for capR x capA entries per slot.
   int ensure_lists(int capR_, int capA_);
-  // Take every buffer from `a` from now on (releases what is held; the next
-  // setup sizes the lists afresh).
+  // Take every device buffer from `a` from now on (releases what is held; the
+  // next setup sizes the lists afresh).
   void use_arena(Arena* a);
   // Stage, bin and sort (pos: N x pos_stride floats).  gate: optional device
   // flag; every kernel returns at once when *gate == 0.  carry: state moved

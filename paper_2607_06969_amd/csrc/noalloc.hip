@@ -72,6 +72,7 @@ extern "C" int nepmi_compute_noalloc(nepmi_model* m, int32_t n_cfg, const int64_
   // every call lays the workspace out afresh from the start of the array
   d->arena.used = 0;
   d->work.use_arena(&d->arena);
+  d->work.nbr.use_pinned(m->host);
   bool again = false;
   if ((rc = prepare_start(d->work, m->ops, m->hp, n_cfg, atom_off, cells, pbc, dev_pos, dev_species, st, 0.0, false)) ||
       (rc = prepare_end(d->work, m->ops, st, again)))
