@@ -41,7 +41,10 @@
  *     call; handles own their workspace, which grows on demand.
  *   - Every call returns NEPMI_OK (0) or a negative code; nepmi_last_error()
  *     gives a message for the calling thread.  No C++ exception crosses the
- *     ABI.  A handle must not be used from two threads or streams at once.
+ *     ABI.  An evaluation or training call that refuses its inputs (positions,
+ *     species, cells, sizes) has written no output array, and nothing it
+ *     launched is still running when it returns.  A handle must not be used
+ *     from two threads or streams at once.
  */
 #ifndef NEPMI_H
 #define NEPMI_H

@@ -122,6 +122,7 @@ NepIO eval_io(EvalWork& w, const nepmi_hparams& hp, float* Fuser, float4* Fproc,
   o.cpA = nbr.cposA.ptr<uint32_t>();
   o.ccA = nbr.ccntA.ptr<int>();
   o.flags = nbr.flags.ptr<int>();
+  o.stop = o.flags;
   const float rcR = (float)hp.rc_radial, rcA = (float)hp.rc_angular;
   o.cut.rcR = rcR;
   o.cut.rcA = rcA;

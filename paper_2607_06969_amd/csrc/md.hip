@@ -197,6 +197,7 @@ struct nepmi_md {
     o.cpA = nbr.cposA.ptr<uint32_t>();
     o.ccA = nbr.ccntA.ptr<int>();
     o.flags = nbr.flags.ptr<int>();
+    o.stop = o.flags + kFlagNone;
     const float rcR = (float)m->hp.rc_radial, rcA = (float)m->hp.rc_angular;
     o.cut.rcR = rcR;
     o.cut.rcA = rcA;
@@ -589,7 +590,7 @@ static int md_run(nepmi_md* md, int32_t n_steps, hipStream_t st, double* ms) {
       ++md->regrows;
       continue;
     }
-    if (hf[kFlagAsym]) {
+    if (hf[kFlagAsym] || hf[kFlagLate]) {
       set_error("angular neighbour list is not symmetric");
       return NEPMI_INVALID_ARG;
     }

@@ -212,7 +212,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     uint32_t* __restrict__ cnA, uint32_t* __restrict__ cpA, int* __restrict__ ccA, uint64_t* __restrict__ amask,
     int* __restrict__ flags, Cutoffs cut,
     const float* __restrict__ params, float* __restrict__ fp, float* __restrict__ aR, float* __restrict__ Ei,
-    float* __restrict__ qout, float* __restrict__ Eproc, int want_adjoint, MailArgs mail) {
+    float* __restrict__ qout, float* __restrict__ Eproc, int want_adjoint, MailArgs mail, const int* stop) {
   constexpr int T = S::T, NR = S::NR, NA = S::NA, BR = S::BR, BA = S::BA, L = S::L, K = S::K, D = S::D, H = S::H;
   constexpr int NH = NA / NSPLIT;
   static_assert(NA % NSPLIT == 0, "NSPLIT must divide n_angular");
@@ -228,6 +228,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
   // network, so lanes past the last slot stay alive as inactive atoms.
   const int64_t p = xcd_tile() * BS + threadIdx.x;
   const bool in_range = p < n_slots;
+  const bool none = lists_void(stop);
   const int64_t pc = in_range ? p : n_slots - 1;
   const float4 xi = pos4[pc];
   const int Zs = __builtin_amdgcn_readfirstlane(__float_as_int(xi.w));
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
   }
 
   const int c = in_range ? cfg_of[p] : -1;
-  const bool active = c >= 0;
+  const bool active = c >= 0 && !none;
   float Hc[9];
   load_cell(cfgs, c, Hc);
   const float rcR_inv = 1.0f / cut.rcR, rcA_inv = 1.0f / cut.rcA;
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
       *wa = front4(ga, nA & 3);
       *wp = front4(gp, nA & 3);
     }
-    if (bad) atomicOr(&flags[kFlagAsym], 1);
+    if (bad) atomicOr(&flags[kFlagLate], 1);
   }
   if (in_range) {
     ccR[p] = nR;
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
                                                 const float* __restrict__ params, float* __restrict__ fp,
                                                 float* __restrict__ aR, float* __restrict__ Ei,
                                                 float* __restrict__ qout, float* __restrict__ Eproc,
-                                                int want_adjoint) {
+                                                int want_adjoint, const int* stop) {
   constexpr int T = S::T, NR = S::NR, BR = S::BR, D = S::D, H = S::H;
   constexpr int MT = (H + 15) / 16;   // tiles of hidden units
   constexpr int KS = (D + 3) / 4;     // reduction steps of the forward product
@@ -428,6 +429,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
   __shared__ float fr_s[kBlock / kWave][NR][kWave + 1];  // radial dE/dq, transposed to one atom per lane
   // The grid is at most two blocks per compute unit, each looping over tiles
   // of kBlock slots: the weights of every species enter LDS once per block.
+  const bool none = lists_void(stop);
   for (int t = threadIdx.x; t < T * HR * WSR; t += kBlock) {
     const int z = t / (HR * WSR), h = (t / WSR) % HR, d = t % WSR;
     W0s[t] = (h < H && d < D) ? params[S::PCR + S::PCA + (int64_t)z * S::PMLP + h * D + d] : 0.0f;
@@ -452,7 +454,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     const bool in_range = p < ns;
     const int64_t pc = in_range ? p : ns - 1;
     const int Zs = __builtin_amdgcn_readfirstlane(__float_as_int(pos4[pc].w));
-    const bool active = in_range && cfg_of[p] >= 0;
+    const bool active = in_range && cfg_of[p] >= 0 && !none;
     auto q_at = [&](int d, int64_t a) {
       return d < NR ? aR[((int64_t)(d / BR) * ns + a) * BR + d % BR] : fp[(int64_t)(d - NR) * ns + a];
     };
@@ -593,7 +595,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     int64_t n_slots, const float4* __restrict__ pos4, const int* __restrict__ cfg_of,
     const int* __restrict__ orig, const CfgDev* __restrict__ cfgs, const uint32_t* __restrict__ cnR,
     const int* __restrict__ ccR, const uint32_t* __restrict__ cnA, const int* __restrict__ ccA, Cutoffs cut, const float* __restrict__ params, const float* __restrict__ fp,
-    const float* aR, float4* __restrict__ frad, float4* __restrict__ fA, float* __restrict__ Wi) {
+    const float* aR, float4* __restrict__ frad, float4* __restrict__ fA, float* __restrict__ Wi, const int* stop) {
   // aR is not declared restrict: loads through a restrict read-only pointer may
   // be sunk past the pair walker's barrier, into the pair body after the
   // prefetches, where waiting for them would drain the prefetch ring
@@ -610,10 +612,11 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
 
   const int64_t p = xcd_tile() * BS + threadIdx.x;
   if (p >= n_slots) return;
+  const bool none = lists_void(stop);
   const float4 xi = pos4[p];
   const int Zs = __builtin_amdgcn_readfirstlane(__float_as_int(xi.w));
   const int c = cfg_of[p];
-  if (c < 0) return;
+  if (c < 0 || none) return;
   float Hc[9];
   load_cell(cfgs, c, Hc);
   const float rcR_inv = 1.0f / cut.rcR, rcA_inv = 1.0f / cut.rcA;
@@ -869,11 +872,12 @@ __global__ __launch_bounds__(BS) void k_gather(int64_t n_slots, const int* __res
                                                    const int* __restrict__ ccA, const uint64_t* __restrict__ amask,
                                                    const float4* __restrict__ frad, const float4* __restrict__ fA,
                                                    float* __restrict__ Fuser, float4* __restrict__ Fproc,
-                                                   SumArgs<float> sums, KickArgs kick) {
+                                                   SumArgs<float> sums, KickArgs kick, const int* stop) {
+  const bool none = lists_void(stop);
   if constexpr (!KICK) {
     if ((int)blockIdx.x < sums.n_items) {
       __shared__ SumShared sh;
-      sum_item<BS>((int)blockIdx.x, sums, sh);
+      sum_item<BS>((int)blockIdx.x, sums, sh, none);
       return;
     }
   }
@@ -887,6 +891,7 @@ __global__ __launch_bounds__(BS) void k_gather(int64_t n_slots, const int* __res
   }
   if (p >= n_slots) return;
   const int i = orig[p];
+  if (none) return;
   if (i < 0) {
     if (Fproc) Fproc[p] = make_float4(0.f, 0.f, 0.f, 0.f);
     return;
@@ -1012,12 +1017,12 @@ static int launch_desc(hipStream_t st, const NepIO& io, const float* params, boo
   hipLaunchKernelGGL((k_desc<S, groups<S, NS>(), W, NET, BS>), dim3(g), dim3(BS), 0, st, io.n_slots, io.capA,
                      io.pos4, io.cfg_of, io.orig, io.cfgs, io.nbrR, io.cntR, io.vrev, io.cnR, io.ccR, io.cnA, io.cpA,
                      io.ccA, io.amask, io.flags, io.cut, params, io.fp, io.aR, io.Ei, io.qout, io.Eproc,
-                     want_adjoint ? 1 : 0, io.mail);
+                     want_adjoint ? 1 : 0, io.mail, io.stop);
   if constexpr (!NET) {
     const unsigned gk = (unsigned)((io.n_slots + kBlock - 1) / kBlock);
     const unsigned gn = gk < kNetBlocks ? gk : kNetBlocks;
     hipLaunchKernelGGL(k_net<S>, dim3(gn), dim3(kBlock), 0, st, io.n_slots, io.pos4, io.cfg_of, io.orig, params,
-                       io.fp, io.aR, io.Ei, io.qout, io.Eproc, want_adjoint ? 1 : 0);
+                       io.fp, io.aR, io.Ei, io.qout, io.Eproc, want_adjoint ? 1 : 0, io.stop);
   }
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
@@ -1028,7 +1033,7 @@ static int launch_force(hipStream_t st, const NepIO& io, const float* params) {
   const unsigned g = (unsigned)((io.n_slots + BS - 1) / BS);
   hipLaunchKernelGGL((k_force<S, groups<S, NS>(), W, BS>), dim3(g), dim3(BS), 0, st, io.n_slots, io.pos4,
                      io.cfg_of, io.orig, io.cfgs, io.cnR, io.ccR, io.cnA, io.ccA, io.cut, params, io.fp, io.aR,
-                     io.frad, io.fA, io.Wi);
+                     io.frad, io.fA, io.Wi, io.stop);
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }
@@ -1069,11 +1074,11 @@ static int launch_gather(hipStream_t st, const NepIO& io, const SumArgs<float>* 
   const unsigned g = (unsigned)((io.n_slots + BS - 1) / BS);
   if (kick)
     hipLaunchKernelGGL((k_gather<BS, true>), dim3(g), dim3(BS), 0, st, io.n_slots, io.orig, io.cnA, io.cpA, io.ccA,
-                       io.amask, io.frad, io.fA, io.Fuser, io.Fproc, SumArgs<float>{}, *kick);
+                       io.amask, io.frad, io.fA, io.Fuser, io.Fproc, SumArgs<float>{}, *kick, io.stop);
   else
     hipLaunchKernelGGL((k_gather<BS, false>), dim3(g + (sums ? sums->n_items : 0)), dim3(BS), 0, st, io.n_slots,
                        io.orig, io.cnA, io.cpA, io.ccA, io.amask, io.frad, io.fA, io.Fuser, io.Fproc,
-                       sums ? *sums : SumArgs<float>{}, KickArgs{});
+                       sums ? *sums : SumArgs<float>{}, KickArgs{}, io.stop);
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }

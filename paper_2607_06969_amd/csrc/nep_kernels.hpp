@@ -47,6 +47,7 @@ struct NepIO {
   uint32_t* cpA;         // own angular-part position | reverse position << 16, grouped as cnA
   int* ccA;
   int* flags;
+  const int* stop;       // see lists_void
   Cutoffs cut;
   float* fp;     // [NANG][n_slots]  dE_i/dq (angular descriptors)
   float* aR;     // [T][n_slots][BR] radial adjoint, part b = atil_i[b][.]

@@ -165,7 +165,8 @@ __device__ __forceinline__ bool group_atom(const NepIO& io, int64_t p0, GroupAto
   a.g = W == kWave ? 0 : (int)threadIdx.x / W;
   a.l = W == kWave ? (int)threadIdx.x : (int)threadIdx.x % W;
   a.p = p0 + a.g;
-  a.act = a.p < io.n_slots && io.cfg_of[a.p < io.n_slots ? a.p : io.n_slots - 1] >= 0;
+  const bool none = lists_void(io.stop);
+  a.act = a.p < io.n_slots && io.cfg_of[a.p < io.n_slots ? a.p : io.n_slots - 1] >= 0 && !none;
   const uint64_t m = __ballot(a.act);
   if (!m) return false;
   a.pa = a.act ? a.p : p0 + __builtin_ctzll(m) / W;
@@ -382,7 +383,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     io.cnA[group_index(ns, p, nA + l)] = A.last[1];
     io.cpA[group_index(ns, p, nA + l)] = A.last[2];
   }
-  if (bad) atomicOr(&io.flags[kFlagAsym], 1);
+  if (bad) atomicOr(&io.flags[kFlagLate], 1);
 
   // ---- descriptors, Eq. 11, 16, 17
   float* PT_s = buf;            // [b][k]

@@ -111,9 +111,10 @@ __device__ __forceinline__ double block_sum(F&& add, SumShared& sh) {
 }
 
 template <int BS, class T>
-__device__ __forceinline__ void sum_item(int item, const SumArgs<T>& a, SumShared& sh) {
+__device__ __forceinline__ void sum_item(int item, const SumArgs<T>& a, SumShared& sh, bool none = false) {
   constexpr int NV = kRedValues;
   const RedItem it = a.items[item];
+  if (none) return;  // all items of a launch or no item
   double s = block_sum<BS>(
       [&](int t, double(&acc)[NV]) {
         for (int64_t i = it.a0 + t; i < it.a1; i += kRedThreads) {

@@ -35,7 +35,9 @@ constexpr int kTB = 256;
 __global__ __launch_bounds__(kTB) void k_loss(TrainSeedArgs a) {
   __shared__ double sh[3][kTB];
   __shared__ int last;
+  const bool none = lists_void(a.stop);
   const RedItem it = a.items[blockIdx.x];
+  if (none) return;
   const double B = (double)a.n_cfg;
   {
     const double Nc = (double)(a.off[it.cfg + 1] - a.off[it.cfg]);
@@ -803,9 +805,9 @@ __global__ void k_part_final(PartPlan pl, const double* __restrict__ part, doubl
   grad[off + (int64_t)s * sstride + dst] = acc;
 }
 
-__global__ void k_to_float(int64_t n, const double* __restrict__ a, float* __restrict__ b) {
+__global__ void k_to_float(int64_t n, const double* __restrict__ a, float* __restrict__ b, const int* stop) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) b[i] = (float)a[i];
+  if (i < n && !lists_void(stop)) b[i] = (float)a[i];
 }
 
 static inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -1520,7 +1522,7 @@ int TrainLaunch<S>::backward(hipStream_t st, TrainIO io, const Cutoffs& cut, con
   hipLaunchKernelGGL((k_train_atom<S, NC, float, 3>), dim3(blocks(ns, kTB), S::NA), dim3(kTB), 0, st, io, cut, params);
   hipLaunchKernelGGL((k_train_coefA<S, float>), dim3(blocks(ns, kTB), S::NA), dim3(kTB), 0, st, io, cut, params);
   species_sums<S, float>(st, io, base, part, grad64);
-  hipLaunchKernelGGL(k_to_float, dim3(blocks(S::P, 256)), dim3(256), 0, st, (int64_t)S::P, grad64, grad);
+  hipLaunchKernelGGL(k_to_float, dim3(blocks(S::P, 256)), dim3(256), 0, st, (int64_t)S::P, grad64, grad, io.stop);
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }

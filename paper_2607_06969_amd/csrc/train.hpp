@@ -44,6 +44,7 @@ struct TrainIOT {
   R* FpA;              // [D] dE/dq (rows NR..D-1 used), network pass -> sigma pass
   R* qbA;              // [D] dj/dq (rows NR..D-1 used), network pass -> sigma pass
   R* Ei;               // [N] site energies, caller order (float64 variant only; may be null)
+  const int* stop;     // see lists_void
 };
 using TrainIO = TrainIOT<float>;
 
@@ -68,6 +69,7 @@ struct TrainSeedArgs {
   double* ebar;
   double* mu;
   double* partF;  // [n_items]
+  const int* stop;  // see lists_void
   int* done;      // items summed so far: 0 between launches
   double* loss;
 };

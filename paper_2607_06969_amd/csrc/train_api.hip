@@ -67,6 +67,7 @@ TrainIO train_io(nepmi_model* m, const double* mu, const double* ebar) {
   io.GA = t.GA.ptr<float>();
   io.FpA = t.FpA.ptr<float>();
   io.qbA = t.qbA.ptr<float>();
+  io.stop = m->nbr.flags.ptr<int>();
   io.Ei = nullptr;
   return io;
 }
@@ -141,6 +142,7 @@ TrainIOT<double> f64_io(nepmi_model* m, const double* mu, const double* ebar, do
   io.GA = f.GA.ptr<double>();
   io.FpA = f.FpA.ptr<double>();
   io.qbA = f.qbA.ptr<double>();
+  io.stop = m->nbr.flags.ptr<int>() + kFlagNone;
   io.Ei = Ei;
   return io;
 }
@@ -300,6 +302,7 @@ int nepmi_loss_grad(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, cons
     a.ebar = t.ebar.ptr<double>();
     a.mu = t.mu.ptr<double>();
     a.partF = t.partF.ptr<double>();
+    a.stop = m->nbr.flags.ptr<int>();
     a.loss = dev_loss;
     if ((rc = m->ops->seeds(st, a))) return rc;
     if (!dev_grad) return NEPMI_OK;

@@ -594,7 +594,8 @@ constexpr int kFinalRuns = 8;
 template <class S, class O>
 __global__ __launch_bounds__(32 * kFinalRuns) void k_train_final(const int* __restrict__ base, int want,
                                                                  const double* __restrict__ part,
-                                                                 O* __restrict__ grad) {
+                                                                 O* __restrict__ grad, const int* stop) {
+  const bool none = lists_void(stop);
   using G = GradEntries<S>;
   constexpr int T = S::T, NR = S::NR, BR = S::BR;
   __shared__ double sh[kFinalRuns][32];
@@ -617,7 +618,7 @@ __global__ __launch_bounds__(32 * kFinalRuns) void k_train_final(const int* __re
   }
   sh[run][x] = acc;
   __syncthreads();
-  if (run != 0 || !in) return;
+  if (run != 0 || !in || none) return;
   for (int r = 1; r < kFinalRuns; ++r) acc += sh[r][x];
   const int64_t mlp = S::PCR + S::PCA + (int64_t)s * S::PMLP;
   int64_t dst;
@@ -641,7 +642,7 @@ int TrainWave<S, R>::run(hipStream_t st, const TrainIOT<R>& io, const CutoffsT<R
   hipLaunchKernelGGL((k_train_wave<S, R>), dim3((unsigned)(want + S::T)), dim3(64 * kTWaves), 0, st, io, cut, params,
                      base, want, part);
   hipLaunchKernelGGL((k_train_final<S, R>), dim3((unsigned)((S::T * GradEntries<S>::N + 31) / 32)),
-                     dim3(32 * kFinalRuns), 0, st, base, want, part, grad);
+                     dim3(32 * kFinalRuns), 0, st, base, want, part, grad, io.stop);
   NEPMI_HIP(hipGetLastError());
   return NEPMI_OK;
 }
