@@ -558,6 +558,7 @@ __global__ __launch_bounds__(kScanBlock) void k_sort_small(SortArgs a, const int
     const int q0 = k > 0 ? cur[k - 1] : 0, q1 = cur[k];
     int rank = 0;
     for (int q = q0; q < q1; ++q) rank += perm[q] < s[u].i ? 1 : 0;
+    a.key[s[u].i] = k;
     put_slot(a, base_s[z] + (q0 - lo_s[z]) + rank, s[u]);
   }
   for (int z = 0; z < a.n_species; ++z) {
@@ -631,7 +632,9 @@ __device__ __forceinline__ float wave_max(float v) {
 //
 // Grid (bins, parts): part y of a bin takes its atoms y, y + parts, ...; a
 // batch of few bins takes several parts, so that a wavefront has a few atoms
-// whatever the bin holds (see launch_lists).
+// whatever the bin holds.  With SPARSE a wavefront per slot instead: the one of
+// every share-th atom of a bin takes that atom and the share - 1 after it, the
+// others end at once (see launch_lists).
 //
 // What bounds it: with one atom per thread and a scan of the 27 bins each, the
 // bins of a wavefront's lanes differ in occupancy (45 % of the lanes in use),
@@ -641,16 +644,54 @@ __device__ __forceinline__ float wave_max(float v) {
 // 97 per atom.  One thread per atom -> one bin per wavefront (us): 900,000
 // atoms 610 -> 346, 64 cells of 64..512 atoms 189 -> 35, 3,686 atoms 160 -> 20,
 // 64 atoms 77 -> 9.
+// Longest lists of a wavefront to the flags (one lane).
+__device__ __forceinline__ void note_lengths(int maxR, int maxA, int capR, int capA, int* __restrict__ flags) {
+  if ((threadIdx.x & (kWave - 1)) != 0) return;
+  if (maxR > capR || maxA > capA) atomicOr(&flags[kFlagOverflow], 1);
+  // read first, past the L2 of this XCD: few wavefronts raise the maximum, and
+  // atomics on one address run one after another
+  auto raise = [&](int f, int v) {
+    if (v > __hip_atomic_load(&flags[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&flags[f], v);
+  };
+  raise(kFlagMaxR, maxR);
+  raise(kFlagMaxA, maxA);
+}
+
+// Bin o of the 27 around bin (b0, b1, b2), packed with its image code; `none` if
+// there is nothing (beyond the cell along a non-periodic direction).
+__device__ __forceinline__ uint32_t stencil_bin(const CfgDev& C, int b0, int b1, int b2, int o, uint32_t none) {
+  int t0 = b0 + o / 9 - 1, t1 = b1 + (o / 3) % 3 - 1, t2 = b2 + o % 3 - 1;
+  const int w0 = t0 < 0 ? -1 : (t0 >= C.nb[0] ? 1 : 0);
+  const int w1 = t1 < 0 ? -1 : (t1 >= C.nb[1] ? 1 : 0);
+  const int w2 = t2 < 0 ? -1 : (t2 >= C.nb[2] ? 1 : 0);
+  if ((w0 && !(C.periodic & 1)) || (w1 && !(C.periodic & 2)) || (w2 && !(C.periodic & 4))) return none;
+  t0 -= w0 * C.nb[0];
+  t1 -= w1 * C.nb[1];
+  t2 -= w2 * C.nb[2];
+  return ((uint32_t)bin_key(C, t0, t1, t2) << 5) | (uint32_t)((w0 + 1) * 9 + (w1 + 1) * 3 + (w2 + 1));
+}
+
+// The bin of a key (see bin_key).
+__device__ __forceinline__ void bin_of_key(const CfgDev& C, int k, int& b0, int& b1, int& b2) {
+  const int rel = k - C.bin_off, tl = rel >> 6;
+  const int nt1 = (C.nb[1] + 3) >> 2, nt2 = (C.nb[2] + 3) >> 2;
+  b0 = ((tl / (nt1 * nt2)) << 2) | ((rel >> 4) & 3);
+  b1 = (((tl / nt2) % nt1) << 2) | ((rel >> 2) & 3);
+  b2 = ((tl % nt2) << 2) | (rel & 3);
+}
+
 constexpr int kListSpecies = 4;                 // species the range tables hold
 constexpr int kListRanges = 27 * kListSpecies;  // (species, stencil bin) slot ranges
 constexpr int kListCandMin = 512, kListCandMax = 2048;  // candidates listed in LDS (CAND); longer lists are searched
 constexpr int kListRegs = 3;                    // rounds of candidates held in registers
 constexpr int kListWaves = 1024;                // wavefronts a small batch is split into
 constexpr unsigned kListGated = 16384;          // most blocks of a gated launch
-template <int CAND>
-__global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_species, int total_bins,
+constexpr int64_t kListThread = 49152;          // slots from which sparse batches take a thread per atom
+template <int CAND, bool SPARSE>
+__global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_species, int total_bins, int share,
                                                        const CfgDev* __restrict__ cfgs,
                                                        const float4* __restrict__ pos4, const int* __restrict__ cfg_of,
+                                                       const int* __restrict__ orig, const int* __restrict__ key,
                                                        const int* __restrict__ start, const int* __restrict__ base,
                                                        float rclR2, float rclA2, int capR, int capA, int rowTA,
                                                        uint32_t* __restrict__ nbrR, uint32_t* __restrict__ nbrTA,
@@ -674,11 +715,19 @@ __global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_sp
 #pragma unroll
   for (int z = 0; z < kListSpecies; ++z) zoff[z] = z < n_species ? base[z] - start[z * total_bins] : 0;
   int maxR = 0, maxA = 0;
-  // every XCD takes one contiguous range of bins (see xcd_tile)
-  const int per = (total_bins + (int)kXcds - 1) / (int)kXcds;
+  // every XCD takes one contiguous range of bins, or of slots (see xcd_tile)
+  const int units = SPARSE ? (int)n_slots : total_bins;
+  const int per = (units + (int)kXcds - 1) / (int)kXcds;
   const int b_lo = (int)(blockIdx.x % kXcds) * per;
-  const int b_hi = b_lo + per < total_bins ? b_lo + per : total_bins;
-  for (int hb = b_lo + (int)(blockIdx.x / kXcds); hb < b_hi; hb += (int)(gridDim.x / kXcds)) {
+  const int b_hi = b_lo + per < units ? b_lo + per : units;
+  for (int unit = b_lo + (int)(blockIdx.x / kXcds); unit < b_hi; unit += (int)(gridDim.x / kXcds)) {
+    int hb = unit, uz = 0;  // the home bin, and with SPARSE the species of the slot
+    if constexpr (SPARSE) {
+      if (cfg_of[unit] < 0) continue;
+      const int k = key[orig[unit]];
+      uz = k / total_bins;
+      hb = k - uz * total_bins;
+    }
     // the bin's atoms: slots hq[z] .. hq[z] + hn[z] - 1 (most padding bins are empty)
     int hq[kListSpecies], hn[kListSpecies], nh = 0;
 #pragma unroll
@@ -691,7 +740,17 @@ __global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_sp
       }
       nh += hn[z];
     }
-    if (nh <= (int)blockIdx.y) continue;
+    // the atoms of the bin that this wavefront takes: h0, h0 + step, ... < h1
+    int h0 = (int)blockIdx.y, h1 = nh;
+    const int step = SPARSE ? 1 : (int)gridDim.y;
+    if constexpr (SPARSE) {
+      h0 = unit;
+#pragma unroll
+      for (int z = 0; z < kListSpecies; ++z) h0 += z < uz ? hn[z] : z == uz ? -hq[z] : 0;
+      if (h0 % share != 0) continue;
+      h1 = h0 + share < nh ? h0 + share : nh;
+    }
+    if (h0 >= h1) continue;
     // slot of home atom h (clamped to the last)
     auto home = [&](int h) {
       h = h < nh ? h : nh - 1;
@@ -706,8 +765,8 @@ __global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_sp
     int hp = home(lane);  // one home atom per lane
     float4 hx = pos4[hp];
     float lox = hx.x, loy = hx.y, loz = hx.z, hix = hx.x, hiy = hx.y, hiz = hx.z;
-    for (int h0 = kWave; h0 < nh; h0 += kWave) {
-      const float4 x = pos4[home(h0 + lane)];
+    for (int q0 = kWave; q0 < nh; q0 += kWave) {
+      const float4 x = pos4[home(q0 + lane)];
       lox = fminf(lox, x.x);
       loy = fminf(loy, x.y);
       loz = fminf(loz, x.z);
@@ -719,20 +778,9 @@ __global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_sp
     __syncthreads();  // the previous bin's tables are no longer read
     uint32_t v = kNoBin;
     if (lane < 27) {
-      const int rel = hb - C.bin_off, tl = rel >> 6;
-      const int nt1 = (C.nb[1] + 3) >> 2, nt2 = (C.nb[2] + 3) >> 2;
-      const int h0 = ((tl / (nt1 * nt2)) << 2) | ((rel >> 4) & 3), h1 = (((tl / nt2) % nt1) << 2) | ((rel >> 2) & 3),
-                h2 = ((tl % nt2) << 2) | (rel & 3);
-      int t0 = h0 + lane / 9 - 1, t1 = h1 + (lane / 3) % 3 - 1, t2 = h2 + lane % 3 - 1;
-      const int w0 = t0 < 0 ? -1 : (t0 >= C.nb[0] ? 1 : 0);
-      const int w1 = t1 < 0 ? -1 : (t1 >= C.nb[1] ? 1 : 0);
-      const int w2 = t2 < 0 ? -1 : (t2 >= C.nb[2] ? 1 : 0);
-      const bool skip = (w0 && !(C.periodic & 1)) || (w1 && !(C.periodic & 2)) || (w2 && !(C.periodic & 4));
-      t0 -= w0 * C.nb[0];
-      t1 -= w1 * C.nb[1];
-      t2 -= w2 * C.nb[2];
-      const uint32_t code = (uint32_t)((w0 + 1) * 9 + (w1 + 1) * 3 + (w2 + 1));
-      if (!skip) v = ((uint32_t)bin_key(C, t0, t1, t2) << 5) | code;
+      int c0, c1, c2;
+      bin_of_key(C, hb, c0, c1, c2);
+      v = stencil_bin(C, c0, c1, c2, lane, kNoBin);
       float sx, sy, sz;
       image_shift(C.H, (uint32_t)lane, sx, sy, sz);
       shift_s[lane] = make_float4(sx, sy, sz, 0.f);
@@ -833,8 +881,8 @@ __global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_sp
       cs[u] = shift_s[ce[u] >> kNbrShift];
       if (c >= total) cx[u].x = __builtin_inff();
     }
-    for (int h = (int)blockIdx.y; h < nh; h += (int)gridDim.y) {
-      if (nh > kWave && (h & (kWave - 1)) < (int)gridDim.y) {  // the next 64 home atoms
+    for (int h = h0; h < h1; h += step) {
+      if (nh > kWave && (h == h0 || (h & (kWave - 1)) < step)) {  // the next 64 home atoms
         hp = home((h & ~(kWave - 1)) + lane);
         hx = pos4[hp];
       }
@@ -908,16 +956,112 @@ __global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_sp
       wave_fence();
     }
   }
-  if (lane == 0) {
-    if (maxR > capR || maxA > capA) atomicOr(&flags[kFlagOverflow], 1);
-    // read first, past the L2 of this XCD: few wavefronts raise the maximum, and
-    // atomics on one address run one after another
-    auto raise = [&](int f, int v) {
-      if (v > __hip_atomic_load(&flags[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&flags[f], v);
+  note_lengths(maxR, maxA, capR, capA, flags);
+}
+
+// The same lists with a thread per atom, for large batches of mostly empty bins: a
+// wavefront for each bin's few atoms spends its 520 instructions of set-up on
+// them, a thread walks its 27 bins for some 10 candidates.  300,000 atoms in a
+// 1,000 A cell, descriptors of the Ge-Sb-Te model: 857 us with a wavefront per
+// occupied bin, 449 so; see launch_lists for where the line lies.
+//
+// The sorted bins wait in the thread's LDS column.  Entries and mask bits shift in
+// from the top, so a full group or word holds them in list order; the store
+// pointers advance one column at a time.
+__global__ __launch_bounds__(256) void k_build_lists_thread(
+    int64_t n_slots, int n_species, int total_bins, const CfgDev* __restrict__ cfgs, const float4* __restrict__ pos4,
+    const int* __restrict__ cfg_of, const int* __restrict__ orig, const int* __restrict__ key,
+    const int* __restrict__ start, const int* __restrict__ base, float rclR2, float rclA2, int capR, int capA,
+    int rowTA, uint32_t* __restrict__ nbrR, uint32_t* __restrict__ nbrTA, uint32_t* __restrict__ angm,
+    int* __restrict__ cntR, int* __restrict__ cntAV, int* __restrict__ flags, const int* __restrict__ gate) {
+  if (gate && *gate == 0) return;
+  constexpr uint32_t kNoBin = 0xFFFFFFFFu;
+  __shared__ uint32_t sorted_bins[27 * 256];
+  const int64_t p = xcd_tile() * 256 + threadIdx.x;
+  const int c = p < n_slots ? cfg_of[p] : -1;
+  int kR = 0, kA = 0;
+  if (c >= 0) {
+    const CfgDev& C = cfgs[c];
+    const float4 xi = pos4[p];
+    int b0, b1, b2;
+    bin_of_key(C, key[orig[p]] % total_bins, b0, b1, b2);
+    uint32_t sb[27];
+#pragma unroll
+    for (int o = 0; o < 27; ++o) sb[o] = stencil_bin(C, b0, b1, b2, o, kNoBin);
+#pragma unroll
+    for (int i = 1; i < 27; ++i)
+#pragma unroll
+      for (int j = i; j > 0; --j) {
+        const uint32_t lo = sb[j - 1] < sb[j] ? sb[j - 1] : sb[j];
+        const uint32_t hi = sb[j - 1] < sb[j] ? sb[j] : sb[j - 1];
+        sb[j - 1] = lo;
+        sb[j] = hi;
+      }
+#pragma unroll
+    for (int o = 0; o < 27; ++o) sorted_bins[o * 256 + threadIdx.x] = sb[o];
+    const int capG = 4 * list_groups(capR);   // entries the groups can hold
+    const int capGA = 4 * list_groups(capA);
+    uint4 grp = make_uint4(0u, 0u, 0u, 0u), gra = grp;
+    uint32_t mword = 0;
+    uint4* colG = reinterpret_cast<uint4*>(nbrR) + p;           // next group
+    uint4* rowA = reinterpret_cast<uint4*>(nbrTA + p * rowTA);  // angular part
+    uint32_t* colM = angm + p;                                  // next mask word
+    for (int z = 0; z < n_species; ++z) {
+      for (int o = 0; o < 27; ++o) {
+        const uint32_t sbo = sorted_bins[o * 256 + threadIdx.x];
+        if (sbo == kNoBin) break;
+        const uint32_t code = sbo & 31u;
+        float sx, sy, sz;
+        image_shift(C.H, code, sx, sy, sz);
+        const int k = z * total_bins + (int)(sbo >> 5);
+        const int q0 = base[z] + start[k] - start[z * total_bins];
+        const int q1 = q0 + start[k + 1] - start[k];
+        // four candidates per round, loaded together (clamped into the bin)
+        for (int q4 = q0; q4 < q1; q4 += 4) {
+          float4 xs[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) xs[u] = pos4[q4 + u < q1 ? q4 + u : q1 - 1];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int q = q4 + u;
+            if (q >= q1 || (q == (int)p && code == 13u)) continue;
+            const float rx = (xs[u].x - xi.x) + sx, ry = (xs[u].y - xi.y) + sy, rz = (xs[u].z - xi.z) + sz;
+            const float d2 = pair_d2(rx, ry, rz);
+            if (!(d2 < rclR2)) continue;
+            const uint32_t e = (uint32_t)q | (code << kNbrShift);
+            grp = make_uint4(grp.y, grp.z, grp.w, e);
+            mword = (mword >> 1) | (d2 < rclA2 ? 0x80000000u : 0u);
+            ++kR;
+            if ((kR & 3) == 0 && kR <= capG) {
+              *colG = grp;
+              colG += n_slots;
+            }
+            if ((kR & 31) == 0 && kR <= capG) {
+              *colM = mword;
+              colM += n_slots;
+            }
+            if (d2 < rclA2) {
+              gra = make_uint4(gra.y, gra.z, gra.w, e);
+              ++kA;
+              if ((kA & 3) == 0 && kA <= capGA) rowA[(kA >> 2) - 1] = gra;
+            }
+          }
+        }
+      }
+    }
+    // the last, partly filled groups (their r entries sit in the top r
+    // components: moved down to the front) and mask word
+    auto front = [](uint4 g, int r) {
+      return r == 1 ? make_uint4(g.w, g.w, g.w, g.w) : r == 2 ? make_uint4(g.z, g.w, g.w, g.w)
+                                                             : make_uint4(g.y, g.z, g.w, g.w);
     };
-    raise(kFlagMaxR, maxR);
-    raise(kFlagMaxA, maxA);
+    if ((kR & 3) && kR < capG) *colG = front(grp, kR & 3);
+    if ((kR & 31) && kR < capG) *colM = mword >> (32 - (kR & 31));
+    if ((kA & 3) && kA < capGA) rowA[kA >> 2] = front(gra, kA & 3);
+    cntR[p] = kR < capR ? kR : capR;
+    cntAV[p] = kA < capA ? kA : capA;
   }
+  note_lengths((int)wave_max((float)kR), (int)wave_max((float)kA), capR, capA, flags);
 }
 
 // Reverse index: for every entry k of i's Verlet list whose pair is within
@@ -1515,21 +1659,43 @@ int NbrPipeline::launch_lists(hipStream_t st, int n_species, const int* gate) {
     set_error("too many species for the neighbour lists");
     return NEPMI_UNSUPPORTED;
   }
-  // parts: enough that about one wavefront per SIMD is at work
-  const unsigned parts = (unsigned)std::min(bin_atoms, std::max(1, kListWaves / real_bins));
-  // without a gate, a block per bin (at 900k atoms 346 us, 371 in 16384 blocks
-  // and 437 in 8192: most of a block's bins are alike, but the empty ones and
-  // the fuller ones are not spread evenly); with one, fewer blocks, since
-  // blocks cost time even when the gate sends them home at once
-  const unsigned want = ((unsigned)total_bins + kXcds - 1) / kXcds * kXcds;
-  const unsigned blocks = gate && want > kListGated ? kListGated : want;
-  // the larger candidate table takes LDS that the smaller one leaves to more
-  // wavefronts; a third is left for bins fuller than the mean
-  const auto kernel = 27 * bin_atoms * 4 / 3 <= kListCandMin ? k_build_lists<kListCandMin> : k_build_lists<kListCandMax>;
-  hipLaunchKernelGGL(kernel, dim3(blocks, parts), dim3(kWave), 0, st, n_slots, n_species, total_bins,
-                     cfgs.ptr<CfgDev>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), start.ptr<int>(), base.ptr<int>(),
-                     rclR2, rclA2, capR, capA, rowTA, nbrR.ptr<uint32_t>(), nbrTA.ptr<uint32_t>(),
-                     angm.ptr<uint32_t>(), cntR.ptr<int>(), cntAV.ptr<int>(), flags.ptr<int>(), gate);
+  // Where bins outnumber slots (a cluster or a gas in a wide cell, many small
+  // cells) most are empty, and the fuller ones are not told by the mean: a
+  // wavefront per slot, of which those of every share-th atom of a bin work, with
+  // the larger candidate table; and from kListThread slots on a thread per atom.
+  // Descriptors of the Ge-Sb-Te model (us), wavefront per bin, per slot, thread per
+  // atom: 1,000 atoms in 1,000 A 1450, 150, -; a cluster of 27,000 atoms 1.9 A
+  // apart in 600 A 1050, 340, -; 30,000 atoms spread over 600 A 410, 190, -; 50,000
+  // over 300 A -, 222, 195; 64,000 over 350 A -, 256, 200; a cluster of 64,000 in
+  // 600 A 545, 287, 313; 300,000 over 1,000 A 1760, 857, 449.
+  const bool sparse = total_bins > n_slots;
+  if (sparse && n_slots >= kListThread) {
+    hipLaunchKernelGGL(k_build_lists_thread, dim3(nblk(n_slots, 256)), dim3(256), 0, st, n_slots, n_species, total_bins,
+                       cfgs.ptr<CfgDev>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), orig.ptr<int>(), key.ptr<int>(),
+                       start.ptr<int>(), base.ptr<int>(), rclR2, rclA2, capR, capA, rowTA, nbrR.ptr<uint32_t>(),
+                       nbrTA.ptr<uint32_t>(), angm.ptr<uint32_t>(), cntR.ptr<int>(), cntAV.ptr<int>(),
+                       flags.ptr<int>(), gate);
+  } else {
+    const int share = (int)std::max<int64_t>(1, N / kListWaves);
+    // parts: enough that about one wavefront per SIMD is at work
+    const unsigned parts = sparse ? 1u : (unsigned)std::min(bin_atoms, std::max(1, kListWaves / real_bins));
+    // without a gate, a block per bin (at 900k atoms 346 us, 371 in 16384 blocks
+    // and 437 in 8192: most of a block's bins are alike, but the empty ones and
+    // the fuller ones are not spread evenly); with one, fewer blocks, since
+    // blocks cost time even when the gate sends them home at once
+    const unsigned want = ((unsigned)(sparse ? n_slots : total_bins) + kXcds - 1) / kXcds * kXcds;
+    const unsigned blocks = gate && want > kListGated ? kListGated : want;
+    // the larger candidate table takes LDS that the smaller one leaves to more
+    // wavefronts; a third is left for bins fuller than the mean
+    const auto kernel = sparse ? k_build_lists<kListCandMax, true>
+                        : 27 * bin_atoms * 4 / 3 <= kListCandMin ? k_build_lists<kListCandMin, false>
+                                                                 : k_build_lists<kListCandMax, false>;
+    hipLaunchKernelGGL(kernel, dim3(blocks, parts), dim3(kWave), 0, st, n_slots, n_species, total_bins, share,
+                       cfgs.ptr<CfgDev>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), orig.ptr<int>(), key.ptr<int>(),
+                       start.ptr<int>(), base.ptr<int>(), rclR2, rclA2, capR, capA, rowTA, nbrR.ptr<uint32_t>(),
+                       nbrTA.ptr<uint32_t>(), angm.ptr<uint32_t>(), cntR.ptr<int>(), cntAV.ptr<int>(),
+                       flags.ptr<int>(), gate);
+  }
   const unsigned rev_tiles = (nblk(n_slots, kRevAtoms) + kXcds - 1) / kXcds * kXcds;
   const unsigned rev_blocks = gate && rev_tiles > kRevGated ? kRevGated : rev_tiles;
   hipLaunchKernelGGL(k_reverse, dim3(rev_blocks), dim3(256), 0, st, n_slots, cfg_of.ptr<int>(),
