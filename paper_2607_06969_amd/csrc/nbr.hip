@@ -831,14 +831,23 @@ __global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_sp
     const bool listed = total <= CAND;
     if (listed) {
       // drop the candidates farther than the list cutoff from the box of the
-      // home atoms (with a margin far above the rounding), keeping the order
+      // home atoms, keeping the order.  The margin is far above what the roundings
+      // of position plus shift here and of the pair vector can differ by: at most
+      // an ulp (2^-23) of the coordinates and of the lattice vectors per component
+      // (a cell of 1e5 A: 0.02 A).
       lox = wave_min(lox);
       loy = wave_min(loy);
       loz = wave_min(loz);
       hix = wave_max(hix);
       hiy = wave_max(hiy);
       hiz = wave_max(hiz);
-      const float far2 = rclR2 * 1.001f + 1e-3f;
+      float reach = 0.f;
+#pragma unroll
+      for (int x = 0; x < 9; ++x) reach = fmaxf(reach, fabsf(C.H[x]));
+      reach = 3.f * reach + fmaxf(fmaxf(fmaxf(fabsf(lox), fabsf(hix)), fmaxf(fabsf(loy), fabsf(hiy))),
+                                  fmaxf(fabsf(loz), fabsf(hiz)));
+      const float far = sqrt_(rclR2) * 1.0005f + 5e-4f + reach * 4e-7f;
+      const float far2 = far * far;
       int out = 0;
       for (int c0 = 0; c0 < total; c0 += kWave) {
         const int c = c0 + lane;
