@@ -1065,7 +1065,7 @@ __global__ __launch_bounds__(256) void k_build_lists_thread(
                                                              : make_uint4(g.y, g.z, g.w, g.w);
     };
     if ((kR & 3) && kR < capG) *colG = front(grp, kR & 3);
-    if ((kR & 31) && kR < capG) *colM = mword >> (32 - (kR & 31));
+    if ((kR & 31) && (kR & ~31) < capG) *colM = mword >> (32 - (kR & 31));
     if ((kA & 3) && kA < capGA) rowA[kA >> 2] = front(gra, kA & 3);
     cntR[p] = kR < capR ? kR : capR;
     cntAV[p] = kA < capA ? kA : capA;
