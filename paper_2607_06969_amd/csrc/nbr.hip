@@ -647,14 +647,15 @@ __device__ __forceinline__ float wave_max(float v) {
 // Longest lists of a wavefront to the flags (one lane).
 __device__ __forceinline__ void note_lengths(int maxR, int maxA, int capR, int capA, int* __restrict__ flags) {
   if ((threadIdx.x & (kWave - 1)) != 0) return;
-  if (maxR > capR || maxA > capA) atomicOr(&flags[kFlagOverflow], 1);
-  // read first, past the L2 of this XCD: few wavefronts raise the maximum, and
-  // atomics on one address run one after another
+  // read first, past the L2 of this XCD: few wavefronts raise a value, and atomics
+  // on one address run one after another (lists of 900 open cells of 20 atoms that
+  // all exceed the capacity: 280 us with an atomic per wavefront, 50 so)
   auto raise = [&](int f, int v) {
     if (v > __hip_atomic_load(&flags[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&flags[f], v);
   };
   raise(kFlagMaxR, maxR);
   raise(kFlagMaxA, maxA);
+  raise(kFlagOverflow, maxR > capR || maxA > capA ? 1 : 0);
 }
 
 // Bin o of the 27 around bin (b0, b1, b2), packed with its image code; `none` if

@@ -197,3 +197,16 @@ def test_cost_of_empty_bins():
     m = nep.NepModel(hp, W.random_params(hp, 3))
     b = nep.Batch.from_system(_gas(1000, 1000.0, 9))
     assert _median_us(lambda: m.descriptors(b)) < 700
+
+
+def test_cost_of_lists_beyond_their_capacity():
+    """900 open cells whose every list exceeds the capacity that the mean density suggests, on the workspace that
+    starts from it in every call: two list builds (some 0.05 ms each), an atomic per wavefront on one word 0.8 ms more."""
+    from paper_2607_06969_amd import nep
+    hp = W.hp_gst()
+    m = nep.NepModel(hp, W.random_params(hp, 3))
+    s = W.concat_systems([_islands(1, 20, 40.0, 40 + c) for c in range(900)])
+    s.pbc[:] = 0
+    b = nep.Batch.from_system(s)
+    kept, fresh = _median_us(lambda: m.compute(b)), _median_us(lambda: m.compute(b, noalloc=True))
+    assert fresh < kept + 250
