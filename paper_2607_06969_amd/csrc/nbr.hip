@@ -1498,6 +1498,8 @@ static int flag_errors(const int* hf) {
 int NbrPipeline::check_flags(hipStream_t st, int* hf) {
   NEPMI_HIP(hipMemcpyAsync(hf, flags.p, sizeof(int) * kFlagCount, hipMemcpyDeviceToHost, st));
   NEPMI_HIP(hipStreamSynchronize(st));
+  longestR = hf[kFlagMaxR];
+  longestA = hf[kFlagMaxA];
   return flag_errors(hf);
 }
 
@@ -1563,6 +1565,8 @@ int NbrPipeline::build_end(hipStream_t st, bool& regrown) {
     int hf[kFlagCount];
     memcpy(hf, m, sizeof hf);
     if ((rc = flag_errors(hf))) return rc;
+    longestR = hf[kFlagMaxR];
+    longestA = hf[kFlagMaxA];
     if (!hf[kFlagOverflow]) {
       if (hf[kFlagAsym]) {
         set_error("neighbour list is not symmetric");
@@ -1669,17 +1673,24 @@ int NbrPipeline::launch_lists(hipStream_t st, int n_species, const int* gate) {
     set_error("too many species for the neighbour lists");
     return NEPMI_UNSUPPORTED;
   }
-  // Where bins outnumber slots (a cluster or a gas in a wide cell, many small
-  // cells) most are empty, and the fuller ones are not told by the mean: a
-  // wavefront per slot, of which those of every share-th atom of a bin work, with
-  // the larger candidate table; and from kListThread slots on a thread per atom.
+  // Candidates of a bin's atoms, from the mean over all bins and, as a hint (the
+  // lists are the same either way), from the longest list read last: 27 bins at the
+  // density of the atoms that have it.
+  const int mean = 27 * bin_atoms, dense = 7 * longestR;
+  // Where most bins are empty (a cluster or a gas in a wide cell, many small cells)
+  // or the full ones hold far more than the mean, a wavefront per slot, of which
+  // those of every share-th atom of a bin work, with the larger candidate table;
+  // from kListThread slots on a thread per atom, and sooner.
   // Descriptors of the Ge-Sb-Te model (us), wavefront per bin, per slot, thread per
   // atom: 1,000 atoms in 1,000 A 1450, 150, -; a cluster of 27,000 atoms 1.9 A
-  // apart in 600 A 1050, 340, -; 30,000 atoms spread over 600 A 410, 190, -; 50,000
-  // over 300 A -, 222, 195; 64,000 over 350 A -, 256, 200; a cluster of 64,000 in
-  // 600 A 545, 287, 313; 300,000 over 1,000 A 1760, 857, 449.
-  const bool sparse = total_bins > n_slots;
-  if (sparse && n_slots >= kListThread) {
+  // apart in 600 A 1050, 340, -, in 200 A 824, 323, -; a cluster of 2,197 atoms 2.9 A
+  // apart in 100 A (1.7 bins per slot) 110, 125, -; 30,000 atoms spread over 600 A
+  // 410, 190, -; 50,000 over 300 A -, 222, 195; 64,000 over 350 A -, 256, 200; a
+  // cluster of 64,000 in 600 A 545, 287, 313; 100,000 spread over 300 A (1.4 bins per
+  // slot) 293, 344, 230; 300,000 over 1,000 A 1760, 857, 449.
+  const bool many = n_slots >= kListThread;
+  const bool sparse = total_bins > (many ? 1 : 4) * n_slots || (dense > kListCandMin && dense > 2 * mean);
+  if (sparse && many) {
     hipLaunchKernelGGL(k_build_lists_thread, dim3(nblk(n_slots, 256)), dim3(256), 0, st, n_slots, n_species, total_bins,
                        cfgs.ptr<CfgDev>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), orig.ptr<int>(), key.ptr<int>(),
                        start.ptr<int>(), base.ptr<int>(), rclR2, rclA2, capR, capA, rowTA, nbrR.ptr<uint32_t>(),
@@ -1696,10 +1707,13 @@ int NbrPipeline::launch_lists(hipStream_t st, int n_species, const int* gate) {
     const unsigned want = ((unsigned)(sparse ? n_slots : total_bins) + kXcds - 1) / kXcds * kXcds;
     const unsigned blocks = gate && want > kListGated ? kListGated : want;
     // the larger candidate table takes LDS that the smaller one leaves to more
-    // wavefronts; a third is left for bins fuller than the mean
+    // wavefronts (lists of 900,000 atoms 361 and 493 us); a third is left for bins
+    // fuller than the mean, and a handle's first lists take it in any case: beyond
+    // the table every candidate of every atom is searched for (27,000 atoms 1.9 A
+    // apart, half of a 150 A cell: 507 us searched, 193 listed, with a thread per atom 329)
     const auto kernel = sparse ? k_build_lists<kListCandMax, true>
-                        : 27 * bin_atoms * 4 / 3 <= kListCandMin ? k_build_lists<kListCandMin, false>
-                                                                 : k_build_lists<kListCandMax, false>;
+                        : longestR > 0 && mean * 4 / 3 <= kListCandMin ? k_build_lists<kListCandMin, false>
+                                                                       : k_build_lists<kListCandMax, false>;
     hipLaunchKernelGGL(kernel, dim3(blocks, parts), dim3(kWave), 0, st, n_slots, n_species, total_bins, share,
                        cfgs.ptr<CfgDev>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), orig.ptr<int>(), key.ptr<int>(),
                        start.ptr<int>(), base.ptr<int>(), rclR2, rclA2, capR, capA, rowTA, nbrR.ptr<uint32_t>(),

@@ -163,6 +163,7 @@ struct NbrPipeline {
   int bin_atoms = 0;    // atoms per bin of the fullest configuration (mean over its bins, rounded up)
   double density = 0.0; // atoms per volume of the densest configuration
   int capR = 0, capA = 0;
+  int longestR = 0, longestA = 0;  // longest lists that the last flags read told of (0: none read yet)
   float rclR2 = 0.f, rclA2 = 0.f;
   double skin = 0.0;
   std::vector<CfgDev> host_cfgs;
