@@ -18,9 +18,9 @@ struct Ops {
   int (*seeds)(hipStream_t, const TrainSeedArgs&);
   int (*backward)(hipStream_t, TrainIO, const Cutoffs&, const float*, const float*, const int*, double*, double*,
                   float*, const MailArgs&);
-  int (*forward64)(hipStream_t, TrainIOT<double>, const CutoffsT<double>&, const F64Args&, double*);
+  int (*forward64)(hipStream_t, TrainIOT<double>, const CutoffsT<double>&, const F64Args&, double*, bool);
   int (*backward64)(hipStream_t, TrainIOT<double>, const CutoffsT<double>&, const F64Args&, const double*, const int*,
-                    double*, double*);
+                    double*, double*, bool);
   int T, NR, NA, BR, BA, L, D, NANG, H, K;
   int64_t P;
   int64_t P_alloc;  // P parameters + the derived tables

@@ -1538,9 +1538,9 @@ static int stage64(hipStream_t st, const TrainIOT<double>& io, const F64Args& a,
 
 template <class S>
 int TrainLaunch<S>::forward64(hipStream_t st, TrainIOT<double> io, const CutoffsT<double>& cut, const F64Args& a,
-                              double* forces) {
+                              double* forces, bool wave) {
   const int64_t ns = io.ns;
-  if (ns <= kWave64Slots) return Wave64<S>::forward(st, io, cut, a, forces);
+  if (wave) return Wave64<S>::forward(st, io, cut, a, forces);
   hipLaunchKernelGGL(k_fill64, dim3(blocks(4 * ns, 256)), dim3(256), 0, st, 4 * ns, 0.0,
                      reinterpret_cast<double*>(io.lam4));
   constexpr int NC = S::NA >= 4 ? 2 : 1;
@@ -1565,11 +1565,11 @@ int TrainLaunch<S>::forward64(hipStream_t st, TrainIOT<double> io, const Cutoffs
 
 template <class S>
 int TrainLaunch<S>::backward64(hipStream_t st, TrainIOT<double> io, const CutoffsT<double>& cut, const F64Args& a,
-                               const double* lam, const int* base, double* part, double* grad) {
+                               const double* lam, const int* base, double* part, double* grad, bool wave) {
   const int64_t ns = io.ns;
   hipLaunchKernelGGL(k_lam_slots<double>, dim3(blocks(ns, 256)), dim3(256), 0, st, ns, io.orig, lam, io.lam4,
                      MailArgs{});
-  if (ns <= kTrainWaveSlots64) return TrainWave<S, double>::run(st, io, cut, a.params, base, part, grad);
+  if (wave) return TrainWave<S, double>::run(st, io, cut, a.params, base, part, grad);
   constexpr int NC = S::NA >= 4 ? 2 : 1;
   hipLaunchKernelGGL((k_train_atom<S, NC, double, 1>), dim3(blocks(ns, kTB), 1 + S::NA / NC), dim3(kTB), 0, st, io, cut, a.params);
   hipLaunchKernelGGL((k_train_atom<S, NC, double, 2>), dim3(blocks(ns, kTB)), dim3(kTB), 0, st, io, cut, a.params);

@@ -98,27 +98,38 @@ struct TrainLaunch {
   static int backward(hipStream_t st, TrainIO io, const Cutoffs& cut, const float* params, const float* lam,
                       const int* base, double* part, double* grad64, float* grad, const MailArgs& mail);
   // float64 variant: forces, site energies (io.Ei) and per-atom virials
-  // (a.Wi), all in caller order; the caller sums them per configuration ...
+  // (a.Wi), all in caller order; the caller sums them per configuration (wave: with
+  // a wavefront per atom, otherwise in passes that need the passes' buffers) ...
   static int forward64(hipStream_t st, TrainIOT<double> io, const CutoffsT<double>& cut, const F64Args& a,
-                       double* forces);
+                       double* forces, bool wave);
   // ... and the parameter gradient of ebar.E + lambda.F + mu:V
   static int backward64(hipStream_t st, TrainIOT<double> io, const CutoffsT<double>& cut, const F64Args& a,
-                        const double* lam, const int* base, double* part, double* grad);
+                        const double* lam, const int* base, double* part, double* grad, bool wave);
 };
 
 // The parameter gradient in one pass over the atoms (train_wave.hip), for io with
 // pos4, cfg_of, cfgs, lam4, mu, ebar and the list nbrR, cntR (every pair within
 // the radial cutoff, more allowed).  part holds train_wave_part(...) doubles.
 //
-// It serves batches of up to kTrainWaveSlots slots in float32 and
-// kTrainWaveSlots64 in float64; larger ones take the passes of train.hip, which
+// It serves batches of up to kTrainWaveSlots slots in float32 and train_wave64(...)
+// in float64; larger ones take the passes of train.hip, which
 // hold an atom per lane and so keep more atoms in flight (lists and gradient, one
 // pass against passes, us.  float32, Ge-Sb-Te model: 677 atoms 38 and 162, 9,285
 // atoms 120 and 190, 19,800 atoms 213 and 250, 39,402 atoms 370 and 348; model of
 // Table 2: 19,800 atoms 250 and 259, 27,173 atoms 351 and 335.  float64: 2,555
 // atoms 142 and 408, 46,872 atoms 1000 and 1128, Table 2 1230 and 1318, 74,000
 // atoms 1910 and 1718).
-constexpr int64_t kTrainWaveSlots = 24576, kTrainWaveSlots64 = 49152;
+constexpr int64_t kTrainWaveSlots = 24576;
+// In float64 up to 49,152 slots, but 20,480 where an atom has more angular pairs
+// than one chunk holds and few others (molecules): it then walks its list twice,
+// and a short radial list is soon done by one lane.  Whole call, one pass and
+// passes, Table 2 model, open cells of 20 atoms: 18,000 atoms 573 and 549 us, 24,000
+// 702 and 621, 36,000 945 and 824; its solids (angular lists of 20, radial ones of
+// 56 at most): 42,000 atoms 1105 and 1185.
+inline bool few_beyond_angular(int longestR, int longestA) { return longestA > 16 && longestR < 32; }
+inline bool train_wave64(int64_t ns, int longestR, int longestA) {
+  return ns <= (few_beyond_angular(longestR, longestA) ? 20480 : 49152);
+}
 // Blocks: an atom per wavefront while the chip holds them all, then what it
 // holds in one round (two blocks per compute unit in float32, one in float64).
 template <class R>
@@ -137,13 +148,17 @@ struct TrainWave {
 };
 
 // The float64 evaluation with one wavefront per atom (nep_wave64.hip), for io with
-// pos4, cfg_of, orig, cfgs, the list and Ei.  It serves batches of up to
-// kWave64Slots slots; larger ones take the passes of train.hip with a thread per
+// pos4, cfg_of, orig, cfgs, the list and Ei.  It serves batches as wave64(...)
+// says; larger ones take the passes of train.hip with a thread per
 // atom (whole evaluation, passes and one wavefront per atom, us: Ge-Sb-Te model
 // 2,555 atoms 350 and 125, 19,812 atoms 488 and 307, 39,402 atoms 595 and 511,
 // 58,570 atoms 700 and 692, 151,707 atoms 1354 and 1549; model of Table 2 2,555
-// atoms 478 and 147, 39,402 atoms 783 and 684, 58,570 atoms 899 and 930).
-constexpr int64_t kWave64Slots = 49152;
+// atoms 478 and 147, 39,402 atoms 783 and 684, 58,570 atoms 899 and 930; its open
+// cells of 20 atoms: 30,000 atoms 613 and 600, 36,000 665 and 685, 44,000 723 and
+// 797).
+inline bool wave64(int64_t ns, int longestR, int longestA) {
+  return ns <= (few_beyond_angular(longestR, longestA) ? 32768 : 49152);
+}
 template <class S>
 struct Wave64 {
   static int forward(hipStream_t st, const TrainIOT<double>& io, const CutoffsT<double>& cut, const F64Args& a,

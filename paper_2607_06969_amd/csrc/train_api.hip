@@ -84,7 +84,8 @@ int run_backward(nepmi_model* m, hipStream_t st, const double* ebar, const float
 
 // ---- float64 variant
 
-int ensure_f64(nepmi_model* m) {
+// wave: for a call that takes an atom per wavefront, else for one in passes
+int ensure_f64(nepmi_model* m, bool wave) {
   const Ops* o = m->ops;
   F64Bufs& f = m->f64;
   const size_t ns = (size_t)m->nbr.n_slots, N = (size_t)(m->nbr.N > 0 ? m->nbr.N : 1);
@@ -100,7 +101,7 @@ int ensure_f64(nepmi_model* m) {
       (rc = f.fA.ensure(32 * ns * (size_t)(m->nbr.capA > 0 ? m->nbr.capA : 1))) ||
       (rc = f.aR.ensure(8 * ns * o->T * o->BR)))
     return rc;
-  if ((int64_t)ns <= kTrainWaveSlots64) return f.part.ensure(8 * train_wave_part<double>((int64_t)ns, o->T, sumE));
+  if (wave) return f.part.ensure(8 * train_wave_part<double>((int64_t)ns, o->T, sumE));
   // the passes' hand-over arrays
   if ((rc = f.Sdt.ensure(8 * ns * o->NA * o->K)) || (rc = f.qd.ensure(8 * ns * o->D)) ||
       (rc = f.Pb.ensure(8 * ns * o->T * o->BR)) || (rc = f.Pdn.ensure(8 * ns * o->T * o->BR)) ||
@@ -163,9 +164,11 @@ CutoffsT<double> f64_cut(const nepmi_model* m) {
 // float64 is listed; the kernels then test each pair in float64.
 constexpr double kSkin64 = 0.01;
 
-// lists from the float32 rounding of the positions, then the float64 staging
+// lists from the float32 rounding of the positions, then the float64 staging;
+// wave: whether the call is to take an atom per wavefront, as by_wave says
 int prepare64(nepmi_model* m, int n_cfg, const int64_t* atom_off, const double* cells, const int32_t* pbc, const double* dev_pos,
-              const int32_t* dev_species, const double* dev_params, hipStream_t st, F64Args& a) {
+              const int32_t* dev_species, const double* dev_params, hipStream_t st, F64Args& a,
+              bool (*by_wave)(int64_t, int, int), bool& wave) {
   if (n_cfg < 1 || !atom_off || atom_off[0] != 0 || atom_off[n_cfg] < 0) {
     set_error("invalid batch");
     return NEPMI_INVALID_ARG;
@@ -174,9 +177,10 @@ int prepare64(nepmi_model* m, int n_cfg, const int64_t* atom_off, const double* 
   int rc;
   if ((rc = m->f64.posf.ensure(12 * (size_t)(N > 0 ? N : 1))) ||
       (rc = launch_round_pos(st, 3 * N, dev_pos, m->f64.posf.ptr<float>())) ||
-      (rc = m->prepare(n_cfg, atom_off, cells, pbc, m->f64.posf.ptr<float>(), dev_species, st, kSkin64, false)) ||
-      (rc = ensure_f64(m)))
+      (rc = m->prepare(n_cfg, atom_off, cells, pbc, m->f64.posf.ptr<float>(), dev_species, st, kSkin64, false)))
     return rc;
+  wave = by_wave(m->nbr.n_slots, m->nbr.longestR, m->nbr.longestA);
+  if ((rc = ensure_f64(m, wave))) return rc;
   a.atom_off = m->nbr.atom_off_dev.ptr<int64_t>();
   a.n_cfg = n_cfg;
   a.pos = dev_pos;
@@ -205,16 +209,18 @@ int nepmi_compute_f64(nepmi_model* m, int32_t n_cfg, const int64_t* atom_off, co
   }
   hipStream_t st = (hipStream_t)stream;
   F64Args a;
+  bool wave;
   int rc;
-  if ((rc = prepare64(m, n_cfg, atom_off, cells, pbc, dev_pos, dev_species, dev_params, st, a))) return rc;
+  if ((rc = prepare64(m, n_cfg, atom_off, cells, pbc, dev_pos, dev_species, dev_params, st, a, wave64, wave)))
+    return rc;
   F64Bufs& f = m->f64;
-  // the seeds of the passes that large batches take
-  if (m->nbr.n_slots > kWave64Slots && ((rc = launch_fill64(st, n_cfg, 1.0, f.ebar1.ptr<double>())) ||
-                                        (rc = launch_fill64(st, 9 * (int64_t)n_cfg, 0.0, f.mu0.ptr<double>()))))
+  // the seeds of the passes
+  if (!wave && ((rc = launch_fill64(st, n_cfg, 1.0, f.ebar1.ptr<double>())) ||
+                (rc = launch_fill64(st, 9 * (int64_t)n_cfg, 0.0, f.mu0.ptr<double>()))))
     return rc;
   double* Ei = dev_atom_energy ? dev_atom_energy : f.Ei.ptr<double>();
   TrainIOT<double> io = f64_io(m, f.mu0.ptr<double>(), f.ebar1.ptr<double>(), Ei);
-  if ((rc = m->ops->forward64(st, io, f64_cut(m), a, dev_forces))) return rc;
+  if ((rc = m->ops->forward64(st, io, f64_cut(m), a, dev_forces, wave))) return rc;
   // per-configuration float64 sums in the fixed chunking of the float32 path
   return m->red.run(st, m->red.args<double>(Ei, a.Wi, nullptr, dev_energy, dev_virial, nullptr));
 }
@@ -229,11 +235,13 @@ int nepmi_backward_params_f64(nepmi_model* m, int32_t n_cfg, const int64_t* atom
   }
   hipStream_t st = (hipStream_t)stream;
   F64Args a;
+  bool wave;
   int rc;
-  if ((rc = prepare64(m, n_cfg, atom_off, cells, pbc, dev_pos, dev_species, dev_params, st, a))) return rc;
+  if ((rc = prepare64(m, n_cfg, atom_off, cells, pbc, dev_pos, dev_species, dev_params, st, a, train_wave64, wave)))
+    return rc;
   TrainIOT<double> io = f64_io(m, dev_mu, dev_ebar, nullptr);
   return m->ops->backward64(st, io, f64_cut(m), a, dev_lambda, m->nbr.base.ptr<int>(), m->f64.part.ptr<double>(),
-                            dev_grad);
+                            dev_grad, wave);
 }
 
 
