@@ -694,7 +694,8 @@ __global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_sp
                                                        const float4* __restrict__ pos4, const int* __restrict__ cfg_of,
                                                        const int* __restrict__ orig, const int* __restrict__ key,
                                                        const int* __restrict__ start, const int* __restrict__ base,
-                                                       float rclR2, float rclA2, int capR, int capA, int rowTA,
+                                                       float rclR2, float rclA2, float far0, int capR, int capA,
+                                                       int rowTA,
                                                        uint32_t* __restrict__ nbrR, uint32_t* __restrict__ nbrTA,
                                                        uint32_t* __restrict__ angm, int* __restrict__ cntR,
                                                        int* __restrict__ cntAV, int* __restrict__ flags,
@@ -832,22 +833,19 @@ __global__ __launch_bounds__(kWave) void k_build_lists(int64_t n_slots, int n_sp
     const bool listed = total <= CAND;
     if (listed) {
       // drop the candidates farther than the list cutoff from the box of the
-      // home atoms, keeping the order.  The margin is far above what the roundings
-      // of position plus shift here and of the pair vector can differ by: at most
-      // an ulp (2^-23) of the coordinates and of the lattice vectors per component
-      // (a cell of 1e5 A: 0.02 A).
+      // home atoms, keeping the order.  The margin (that of the lattice vectors is in
+      // far0) is far above what the roundings of position plus shift here and of the
+      // pair vector can differ by: at most an ulp (2^-23) of the coordinates and of
+      // the lattice vectors per component (a cell of 1e5 A: 0.02 A).
       lox = wave_min(lox);
       loy = wave_min(loy);
       loz = wave_min(loz);
       hix = wave_max(hix);
       hiy = wave_max(hiy);
       hiz = wave_max(hiz);
-      float reach = 0.f;
-#pragma unroll
-      for (int x = 0; x < 9; ++x) reach = fmaxf(reach, fabsf(C.H[x]));
-      reach = 3.f * reach + fmaxf(fmaxf(fmaxf(fabsf(lox), fabsf(hix)), fmaxf(fabsf(loy), fabsf(hiy))),
-                                  fmaxf(fabsf(loz), fabsf(hiz)));
-      const float far = sqrt_(rclR2) * 1.0005f + 5e-4f + reach * 4e-7f;
+      const float reach = fmaxf(fmaxf(fmaxf(fabsf(lox), fabsf(hix)), fmaxf(fabsf(loy), fabsf(hiy))),
+                                fmaxf(fabsf(loz), fabsf(hiz)));
+      const float far = fmaf(reach, 4e-7f, far0);
       const float far2 = far * far;
       int out = 0;
       for (int c0 = 0; c0 < total; c0 += kWave) {
@@ -1350,7 +1348,7 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
   const double rcl = rcR + skin_;
   std::vector<CfgDev> hc((size_t)n_cfg_);
   int64_t bins = 0, real = 0, most = 0;
-  double densest = 0.0;
+  double densest = 0.0, longest = 0.0;
   for (int c = 0; c < n_cfg_; ++c) {
     CfgDev& C = hc[(size_t)c];
     const double* H = cells + 9 * (size_t)c;
@@ -1383,6 +1381,7 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
     for (int x = 0; x < 9; ++x) {
       C.Hd[x] = H[x];
       C.H[x] = (float)H[x];
+      longest = std::max(longest, fabs(H[x]));
     }
     C.bin_off = (int)bins;
     C.atom_off = atom_off[c];
@@ -1411,6 +1410,7 @@ int NbrPipeline::setup(int n_cfg_, const int64_t* atom_off, const double* cells,
   const float rlR = (float)(rcR + skin_), rlA = (float)(rcA + skin_);
   rclR2 = rlR * rlR;
   rclA2 = rlA * rlA;
+  far0 = (float)(1.0005 * rlR + 5e-4 + 3.0 * 4e-7 * longest);
   host_cfgs = hc;
   host_off.assign(atom_off, atom_off + n_cfg_ + 1);
   const int64_t M = (int64_t)n_species_ * bins;
@@ -1716,7 +1716,7 @@ int NbrPipeline::launch_lists(hipStream_t st, int n_species, const int* gate) {
                                                                        : k_build_lists<kListCandMax, false>;
     hipLaunchKernelGGL(kernel, dim3(blocks, parts), dim3(kWave), 0, st, n_slots, n_species, total_bins, share,
                        cfgs.ptr<CfgDev>(), pos4.ptr<float4>(), cfg_of.ptr<int>(), orig.ptr<int>(), key.ptr<int>(),
-                       start.ptr<int>(), base.ptr<int>(), rclR2, rclA2, capR, capA, rowTA, nbrR.ptr<uint32_t>(),
+                       start.ptr<int>(), base.ptr<int>(), rclR2, rclA2, far0, capR, capA, rowTA, nbrR.ptr<uint32_t>(),
                        nbrTA.ptr<uint32_t>(), angm.ptr<uint32_t>(), cntR.ptr<int>(), cntAV.ptr<int>(),
                        flags.ptr<int>(), gate);
   }

@@ -165,6 +165,7 @@ struct NbrPipeline {
   int capR = 0, capA = 0;
   int longestR = 0, longestA = 0;  // longest lists that the last flags read told of (0: none read yet)
   float rclR2 = 0.f, rclA2 = 0.f;
+  float far0 = 0.f;     // beyond it from a bin's atoms, no candidate is a neighbour (see k_build_lists)
   double skin = 0.0;
   std::vector<CfgDev> host_cfgs;
   std::vector<int64_t> host_off;
