@@ -19,6 +19,7 @@ int hip_fail(hipError_t e, const char* what) {
 
 template <class S>
 static const Ops* ops_of() {
+  static_assert(S::T <= kListSpecies && S::T <= kMaxSpecies, "species of the neighbour lists and of MD");
   static const Ops o = {&Launch<S>::desc, &Launch<S>::force, &Launch<S>::gather, &Launch<S>::derive,
                         &TrainLaunch<S>::seeds, &TrainLaunch<S>::backward,
                         &TrainLaunch<S>::forward64, &TrainLaunch<S>::backward64, S::T, S::NR, S::NA, S::BR, S::BA, S::L,

@@ -140,6 +140,36 @@ __device__ __forceinline__ float comp4(const float4& v, int u) {
   return u == 0 ? v.x : u == 1 ? v.y : u == 2 ? v.z : v.w;
 }
 
+// Order between one wavefront's LDS writes and its other lanes' reads.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Set bits of a ballot below this lane: the lane's place in its compaction.
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// A row of N coefficients (float: N a multiple of 4, rows 16-byte aligned).
+template <int N>
+__device__ __forceinline__ void load_row(const float* __restrict__ src, float (&c)[N]) {
+  static_assert(N % 4 == 0, "coefficient rows are read as float4");
+#pragma unroll
+  for (int k = 0; k < N / 4; ++k) {
+    const float4 v = reinterpret_cast<const float4*>(src)[k];
+    c[4 * k] = v.x;
+    c[4 * k + 1] = v.y;
+    c[4 * k + 2] = v.z;
+    c[4 * k + 3] = v.w;
+  }
+}
+template <int N>
+__device__ __forceinline__ void load_row(const double* __restrict__ src, double (&c)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) c[k] = src[k];
+}
+
 // Opaque copy of a group (see take_slot).
 __device__ __forceinline__ uint4 take_group(const uint4& v) {
   return make_uint4(take_slot(v.x), take_slot(v.y), take_slot(v.z), take_slot(v.w));

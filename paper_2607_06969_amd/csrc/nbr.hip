@@ -14,9 +14,10 @@
 // Neighbour entries are 32-bit: slot index (27 bits) | image code (5 bits),
 // code = (w0+1)*9 + (w1+1)*3 + (w2+1) for the lattice shift w in {-1,0,1}^3.
 // Lists are stored in groups of four entries, group g of slot p as one 16-byte
-// word at [g * n_slots + p] (group_index).  The Verlet list holds pairs within rc_radial + skin; at every evaluation the
-// descriptor kernel filters it into compact lists of the pairs within
-// rc_radial and within rc_angular, which all later kernels iterate.
+// word at [g * n_slots + p] (group_index).  The Verlet list holds pairs within
+// rc_radial + skin; at every evaluation the descriptor kernel filters it into
+// compact lists of the pairs within rc_radial and within rc_angular, which all
+// later kernels iterate.
 #include "nbr.hpp"
 
 #include <algorithm>
@@ -26,7 +27,6 @@
 namespace nepmi {
 
 constexpr int kScanBlock = 1024;
-constexpr int kMaxSortSpecies = 8;
 // Largest sort that one block does whole, and most keys that one block scans
 // (see k_sort_small, k_scan_one).
 constexpr int kSmallAtoms = 4096, kSmallKeys = 8192;
@@ -37,7 +37,6 @@ constexpr int kOneScan = 1 << 15, kOneScanGated = 1 << 20;
 
 // ------------------------------------------------------------------ staging
 
-// Per caller-order atom: validate, wrap into the cell, find its bin and sort key.
 // Global sort key of a cell bin.  Bins are numbered in 4 x 4 x 4 tiles (tile
 // row-major, then row-major inside the tile), so that a contiguous range of
 // slots covers a compact region of space: the atoms a GPU die processes at
@@ -228,28 +227,33 @@ __device__ __forceinline__ void pad_slot(const SortArgs& a, int64_t p, int z) {
 constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanBlock * kScanItems;
 
-__device__ int block_exclusive_scan(int v, int* sh, int& total) {
-  // Hillis-Steele within a block of kScanBlock threads (deterministic).
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int off = 1; off < kScanBlock; off <<= 1) {
-    const int add = t >= off ? sh[t - off] : 0;
-    __syncthreads();
-    sh[t] += add;
-    __syncthreads();
+// Inclusive scan over a block of kScanBlock threads (wavefront scans, then the
+// wavefront totals); sh holds one int per wavefront.  Ends with a barrier.
+__device__ __forceinline__ int block_inclusive(int v, int* sh, int& total) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(v, o, 64);
+    if (lane >= o) v += u;
   }
-  total = sh[kScanBlock - 1];
-  const int incl = sh[t];
+  if (lane == 63) sh[wv] = v;
   __syncthreads();
-  return incl - v;
+  int before = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < kScanBlock / 64; ++w) {
+    before += w < wv ? sh[w] : 0;
+    total += sh[w];
+  }
+  __syncthreads();
+  return v + before;
 }
 
 // out[0..M] = exclusive prefix sum of in[0..M-1] (out[M] = total), tile level.
 __global__ __launch_bounds__(kScanBlock) void k_scan_tiles(const int* __restrict__ in, int M, int* __restrict__ out,
                                                            int* __restrict__ tile_sums, const int* __restrict__ gate) {
   if (gate && *gate == 0) return;
-  __shared__ int sh[kScanBlock];
+  __shared__ int sh[kScanBlock / 64];
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
   int v[kScanItems], s = 0;
   for (int j = 0; j < kScanItems; ++j) {
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_tiles(const int* __restrict
     s += v[j];
   }
   int total;
-  int ex = block_exclusive_scan(s, sh, total);
+  int ex = block_inclusive(s, sh, total) - s;
   for (int j = 0; j < kScanItems; ++j) {
     if (base + j < M) out[base + j] = ex;
     ex += v[j];
@@ -275,7 +279,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_sums(int* __restrict__ tile
                                                           int n_species, int* __restrict__ species_base,
                                                           const int* __restrict__ gate) {
   if (gate && *gate == 0) return;
-  __shared__ int sh[kScanBlock];
+  __shared__ int sh[kScanBlock / 64];
   __shared__ int tile_ex[kScanTile];
   const int b0 = threadIdx.x * kScanItems;
   int v[kScanItems], s = 0;
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_sums(int* __restrict__ tile
     s += v[j];
   }
   int total;
-  int ex = block_exclusive_scan(s, sh, total);
+  int ex = block_inclusive(s, sh, total) - s;
   for (int j = 0; j < kScanItems; ++j) {
     if (b0 + j < n_tiles) {
       tile_sums[b0 + j] = ex;
@@ -320,38 +324,16 @@ __global__ void k_scan_add(int* __restrict__ out, int M, const int* __restrict__
   }
 }
 
-// Inclusive scan over a block of kScanBlock threads (wavefront scans, then the
-// wavefront totals); sh holds one int per wavefront.  Ends with a barrier.
-__device__ __forceinline__ int block_inclusive(int v, int* sh, int& total) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(v, o, 64);
-    if (lane >= o) v += u;
-  }
-  if (lane == 63) sh[wv] = v;
-  __syncthreads();
-  int before = 0;
-  total = 0;
-#pragma unroll
-  for (int w = 0; w < kScanBlock / 64; ++w) {
-    before += w < wv ? sh[w] : 0;
-    total += sh[w];
-  }
-  __syncthreads();
-  return v + before;
-}
-
 // Species bases from the number of atoms before each species: base[z] = first
 // slot of species z, each group padded to the wavefront size.
-__device__ __forceinline__ void species_bases(const SortArgs& a, const int* lo, int total) {
+__device__ __forceinline__ void species_bases(int n_species, const int* lo, int total, int* base) {
   int acc = 0;
-  for (int z = 0; z < a.n_species; ++z) {
-    const int n = (z + 1 < a.n_species ? lo[z + 1] : total) - lo[z];
-    a.base[z] = acc;
+  for (int z = 0; z < n_species; ++z) {
+    const int n = (z + 1 < n_species ? lo[z + 1] : total) - lo[z];
+    base[z] = acc;
     acc += (n + kWave - 1) / kWave * kWave;
   }
-  a.base[a.n_species] = acc;
+  base[n_species] = acc;
 }
 
 // The whole scan by one block: prefixes, cursors, cleared counts, species
@@ -364,7 +346,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_one(SortArgs a, const int* 
   if (gate && *gate == 0) return;
   constexpr int Q = 2;  // int4 per thread and round
   __shared__ int sh[kScanBlock / 64];
-  __shared__ int lo_s[kMaxSortSpecies];
+  __shared__ int lo_s[kListSpecies];
   const int M = a.n_species * a.total_bins;  // a multiple of 64 (bins come in tiles of 64)
   int4* cnt = reinterpret_cast<int4*>(a.cnt);
   int4* start = reinterpret_cast<int4*>(a.start);
@@ -420,7 +402,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_one(SortArgs a, const int* 
   __syncthreads();
   if (threadIdx.x == 0) {
     a.start[M] = run;
-    species_bases(a, lo_s, run);
+    species_bases(a.n_species, lo_s, run, a.base);
   }
 }
 
@@ -491,7 +473,7 @@ __global__ __launch_bounds__(kScanBlock) void k_sort_small(SortArgs a, const int
   __shared__ int perm[kSmallAtoms];
   __shared__ int off_s[SLOTS ? 1 : kOff];
   __shared__ int sh[kScanBlock / 64];
-  __shared__ int lo_s[kMaxSortSpecies], base_s[kMaxSortSpecies + 1];
+  __shared__ int lo_s[kListSpecies], base_s[kListSpecies + 1];
   const int t = threadIdx.x, M = a.n_species * a.total_bins;
   if constexpr (!SLOTS) {
     upload_part(up, t, kScanBlock);
@@ -538,13 +520,8 @@ __global__ __launch_bounds__(kScanBlock) void k_sort_small(SortArgs a, const int
   __syncthreads();
   if (t == 0) {
     a.start[M] = run;
-    species_bases(a, lo_s, run);
-    int acc = 0;
-    for (int z = 0; z < a.n_species; ++z) {
-      base_s[z] = acc;
-      acc += ((z + 1 < a.n_species ? lo_s[z + 1] : run) - lo_s[z] + kWave - 1) / kWave * kWave;
-    }
-    base_s[a.n_species] = acc;
+    species_bases(a.n_species, lo_s, run, base_s);
+    for (int z = 0; z <= a.n_species; ++z) a.base[z] = base_s[z];
   }
 #pragma unroll
   for (int u = 0; u < IT; ++u)
@@ -569,17 +546,6 @@ __global__ __launch_bounds__(kScanBlock) void k_sort_small(SortArgs a, const int
 }
 
 // --------------------------------------------------------- Verlet lists
-
-// Compacted position of this lane in a ballot: set bits below the lane.
-__device__ __forceinline__ int lanes_below(uint64_t m) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
-// Order between one wavefront's LDS writes and its other lanes' reads.
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 // Smallest and largest value over the wavefront (DPP butterfly towards lane 63;
 // lanes without a source keep their own value, which changes neither).
@@ -681,7 +647,6 @@ __device__ __forceinline__ void bin_of_key(const CfgDev& C, int k, int& b0, int&
   b2 = ((tl % nt2) << 2) | (rel & 3);
 }
 
-constexpr int kListSpecies = 4;                 // species the range tables hold
 constexpr int kListRanges = 27 * kListSpecies;  // (species, stencil bin) slot ranges
 constexpr int kListCandMin = 512, kListCandMax = 2048;  // candidates listed in LDS (CAND); longer lists are searched
 constexpr int kListRegs = 3;                    // rounds of candidates held in registers
@@ -1593,10 +1558,6 @@ int NbrPipeline::build_end(hipStream_t st, bool& regrown) {
 int NbrPipeline::launch_sort(hipStream_t st, const float* pos, int pos_stride, const int32_t* species, int n_species,
                              const int* gate, const SlotCarry* carry, const SlotSource* src,
                              const UploadArgs* upload) {
-  if (n_species > kMaxSortSpecies) {
-    set_error("too many species for the neighbour lists");
-    return NEPMI_UNSUPPORTED;
-  }
   const int M = n_species * total_bins;
   SortArgs a{};
   a.N = N;
@@ -1669,10 +1630,6 @@ int NbrPipeline::launch_sort(hipStream_t st, const float* pos, int pos_stride, c
 }
 
 int NbrPipeline::launch_lists(hipStream_t st, int n_species, const int* gate) {
-  if (n_species > kListSpecies) {
-    set_error("too many species for the neighbour lists");
-    return NEPMI_UNSUPPORTED;
-  }
   // Candidates of a bin's atoms, from the mean over all bins and, as a hint (the
   // lists are the same either way), from the longest list read last: 27 bins at the
   // density of the atoms that have it.

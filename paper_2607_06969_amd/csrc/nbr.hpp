@@ -33,6 +33,10 @@ __device__ __forceinline__ bool lists_void(const int* stop) {
   return (f.x | f.y | f.z | f.w) != 0;
 }
 
+// Most species of a model: the list build holds a slot range per species of every
+// neighbouring bin.
+constexpr int kListSpecies = 4;
+
 // Largest Verlet list length: positions are kept in 16 bits.
 constexpr int kMaxListRows = 65535;
 

@@ -24,11 +24,6 @@
 
 namespace nepmi {
 
-// Order between the wavefront's LDS writes and its other lanes' reads.
-__device__ __forceinline__ void lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 // A ballot over the lanes of a group, its size and this lane's rank in it.
 template <int W>
 struct GroupBallot {
@@ -63,20 +58,6 @@ constexpr int pair_chunk() {
   return W / 2;
 }
 constexpr int odd(int n) { return n | 1; }  // row strides that spread a column over the banks
-
-// Row of a derived coefficient table (16-byte aligned).
-template <int B>
-__device__ __forceinline__ void load_row(const float* __restrict__ src, float (&c)[B]) {
-  static_assert(B % 4 == 0, "coefficient rows are read as float4");
-#pragma unroll
-  for (int k = 0; k < B / 4; ++k) {
-    const float4 v = reinterpret_cast<const float4*>(src)[k];
-    c[4 * k] = v.x;
-    c[4 * k + 1] = v.y;
-    c[4 * k + 2] = v.z;
-    c[4 * k + 3] = v.w;
-  }
-}
 
 // The harmonics' constants, for lanes to read their own.
 template <int L>
@@ -233,7 +214,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
   // entries the mask's words hold (a list cut off at its capacity, which is
   // rebuilt before its results are used, may have more)
   const int kaMax = (io.capA + 63) / 64 * 64;
-  lds_fence();
+  wave_fence();
 
   // ---- filter the Verlet list into the pairs inside the two cutoffs, W
   //      entries per round; accumulator (b, k) = b B_R + k sums the radial
@@ -310,7 +291,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
       row[4] = __int_as_float(v.zj);
     }
     if (part) A.part[kp] = okA ? 1 : 0;
-    lds_fence();
+    wave_fence();
     // the mask bits of this round's entries of the angular part, appended
     const int np = mP.count();
     const uint64_t bits = GroupBallot<W>(l < np && A.part[l] != 0).bits();
@@ -337,7 +318,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
 #pragma unroll 4
       for (int j = 0; j < nj; ++j) PT[r] = fmaf(row[j * RW + BR], row[j * RW + a % BR], PT[r]);
     }
-    lds_fence();
+    wave_fence();
     // the angular pairs of this round: S_nlm = sum_j g_n(r_ij) Y_lm(u_ij)
     const int most = over_groups<W>(cA);
     for (int a0 = 0; a0 < most; a0 += PC) {
@@ -354,7 +335,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
         hS[l] = f.hf;
         cS[l] = row[4];
       }
-      lds_fence();
+      wave_fence();
       for (int it = l; it < m * NA; it += W) {
         const int j = it / NA, nn = it % NA;
         float Tk[BA], cl[BA];
@@ -365,9 +346,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
         for (int kk = 0; kk < BA; ++kk) acc = fmaf(cl[kk], Tk[kk], acc);
         gS[j * GW + nn] = hS[j] * acc;
       }
-      lds_fence();
+      wave_fence();
       sum.add(gS, pS, m);
-      lds_fence();
+      wave_fence();
     }
   }
   // the last, partly filled mask word and groups (they repeat the last entry)
@@ -393,7 +374,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
   for (int r = 0; r < RR; ++r)
     if (l + W * r < T * BR) PT_s[l + W * r] = PT[r];
   sum.store(S_s);
-  lds_fence();
+  wave_fence();
   const float* cR = dco + (int64_t)Zs * (T * NR * BR);
   if (l < NR) {
     float acc = 0.f;
@@ -426,7 +407,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
       q[S::OFF4 + l] = tr_cube(B);
     }
   }
-  lds_fence();
+  wave_fence();
 
   // ---- network: one hidden unit, then one descriptor, of every atom per lane
   const int i = io.orig[p];
@@ -458,7 +439,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     atoms[g].angr[lane] = t;
     atoms[g].angr[kWave + lane] = w1 * fmaf(-t, t, 1.0f);
   }
-  lds_fence();
+  wave_fence();
   float E = w1g[H];
 #pragma unroll 25
   for (int h = 0; h < H; ++h) E = fmaf(w_s[h], A.angr[h], E);
@@ -475,13 +456,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
 #pragma unroll
     for (int g = 0; g < G; ++g) Fp[g] = fmaf(w, atoms[g].angr[kWave + h], Fp[g]);
   });
-  lds_fence();
+  wave_fence();
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     if (lane >= NR && lane < D && p0 + g < ns) io.fp[(int64_t)(lane - NR) * ns + p0 + g] = Fp[g];
     if (lane < NR) q_s[g][lane] = Fp[g];
   }
-  lds_fence();
+  wave_fence();
   // radial adjoint atil[b][k] = sum_n dE/dq_n ctil[Z_i][b][n][k]
   for (int it = l; it < T * BR; it += W) {
     const int b = it / BR, kk = it % BR;
@@ -542,7 +523,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
   load_cell(io.cfgs, io.cfg_of[p], Hc);
   const float rcR_inv = 1.0f / io.cut.rcR, rcA_inv = 1.0f / io.cut.rcA;
   const int nR = at.act ? io.ccR[p] : 0, nA = at.act ? io.ccA[p] : 0;
-  lds_fence();
+  wave_fence();
 
   // ---- radial pairs: f_ij - f_ji = (s_own + s_rev) u_ij.  Accumulators of
   //      lanes 0..2: force; 3..8: virial xx, yy, zz, xy, xz, yz.  Every term
@@ -584,16 +565,16 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
       row[5] = -(so * v.ry);
       row[6] = -(so * v.rz);
     }
-    lds_fence();
+    wave_fence();
     if (l < 9) {
 #pragma unroll 4
       for (int j = 0; j < m; ++j) acc = fmaf(buf[j * RW + oa], buf[j * RW + ob], acc);
     }
-    lds_fence();
+    wave_fence();
   }
   // from here lanes 0..2 hold the force and 3..11 the virial, row-major
   if (l < 9) acc_s[l] = acc;
-  lds_fence();
+  wave_fence();
   const int wi = (l - 3) / 3, wj = (l - 3) % 3;  // virial entry of lanes 3..11
   if (l >= 3 && l < 12) {
     const int lo = wi < wj ? wi : wj, hi = wi < wj ? wj : wi;
@@ -613,7 +594,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     }
   };
   auto chunk = [&](int a0, int m) {
-    lds_fence();
+    wave_fence();
     if (l < m) {
       const uint32_t e = io.cnA[group_index(ns, p, a0 + l)];
       const PairVec v = pair_vec(e, io.pos4[e & kNbrMask], xi, Hc, itab);
@@ -635,7 +616,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
       row[11] = f.dfc2;
       row[12] = __int_as_float(v.zj);
     }
-    lds_fence();
+    wave_fence();
     for (int it = l; it < m * NA; it += W) {
       const int j = it / NA, nn = it % NA;
       const float* row = qS + j * QW;
@@ -651,7 +632,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
       gS[j * GW + nn] = row[9] * ct;
       dS[j * ZW + nn] = fmaf(row[10], cd, row[11] * ct);
     }
-    lds_fence();
+    wave_fence();
   };
   auto chunk_len = [&](int a0) { return nA - a0 < PC ? nA - a0 : PC; };
   const int nA_most = over_groups<W>(nA);
@@ -661,11 +642,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
       const int m = chunk_len(a0);
       chunk(a0, m);
       harmonics(m, true);
-      lds_fence();
+      wave_fence();
       sum.add(gS, pS, m);
     }
     sum.store(S_s);
-    lds_fence();
+    wave_fence();
     // sigma = dE_i/dS in place, scaled by kappa: per function first
     if (l < NA) {
       const float* Sn = S_s + l * K;
@@ -688,7 +669,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
       }
       psi_s[l] = psi1;
     }
-    lds_fence();
+    wave_fence();
     if (sum.own) {
       const int lm = sum.lm, ll = lm < 3 ? 1 : (lm < 8 ? 2 : (lm < 15 ? 3 : 4));
 #pragma unroll
@@ -704,9 +685,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     // pair forces of the chunk for groups h0 .. h0 + nh - 1: a (pair,
     // function) per lane for Z_n, then a (pair, group) per lane
     auto forces = [&](int m, int h0, int nh) {
-      lds_fence();
+      wave_fence();
       harmonics(m, false);
-      lds_fence();
+      wave_fence();
       for (int it = l; it < m * NA; it += W) {
         const int j = it / NA, nn = it % NA;
         float zn = 0.f;
@@ -714,7 +695,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
         for (int lm = 0; lm < K; ++lm) zn = fmaf(S_s[nn * K + lm], pS[j * PW + lm], zn);
         zS[j * ZW + nn] = zn;
       }
-      lds_fence();
+      wave_fence();
       const int h = h0 + l / PC, j = l % PC;
       if (j < m && h < h0 + nh) {
         const float* row = qS + j * QW;
@@ -739,7 +720,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
         f[1] = fmaf(s, uy, (vy - uv * uy) * inv);
         f[2] = fmaf(s, uz, (vz - uv * uz) * inv);
       }
-      lds_fence();
+      wave_fence();
     };
     // own force and virial of group h over the chunk, in order
     const int fc = l < 3 ? l : wi, rc = l < 3 ? 7 : 4 + wj;

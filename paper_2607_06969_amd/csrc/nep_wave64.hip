@@ -13,13 +13,6 @@
 
 namespace nepmi {
 
-__device__ __forceinline__ void lds_order64() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-__device__ __forceinline__ int rank64(uint64_t m) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
 __device__ __forceinline__ double sum64(double v, int from) {
   for (int o = 32; o >= from; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
@@ -88,27 +81,27 @@ __global__ __launch_bounds__(64 * kAtomWaves) void k_atom64(TrainIOT<double> io,
     for (int b = 0; b < T; ++b) {
       const uint64_t mb = __ballot(in && (T == 1 || v.zj == b));
       const int nb = __builtin_popcountll(mb);
-      if (T == 1 || v.zj == b) row = rows + rank64(mb);
+      if (T == 1 || v.zj == b) row = rows + lanes_below(mb);
       if (lane / BR == b) {
         j0 = rows;
         nj = nb;
       }
       rows += nb;
     }
-    lds_order64();
+    wave_fence();
     if (in) {
       double Q[BR], dQ[BR];
       cheb_basis_d<BR>(sqrt_(v.d2), rcR_inv, Q, dQ);
 #pragma unroll
       for (int kk = 0; kk < BR; ++kk) m.buf[row * RW + kk] = Q[kk];
     }
-    lds_order64();
+    wave_fence();
 #pragma unroll 4
     for (int j = 0; j < nj; ++j) P += m.buf[(j0 + j) * RW + lane % BR];
   }
-  lds_order64();
+  wave_fence();
   if (lane < T * BR) m.buf[lane] = P;
-  lds_order64();
+  wave_fence();
   if (lane < NR) {
     double a = 0.0;
 #pragma unroll
@@ -123,7 +116,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void k_atom64(TrainIOT<double> io,
   const uint32_t* list = nbrTA + p * rowTA;
   const int nA = cntAV[p];
   auto chunk = [&](int a0, int np) {
-    lds_order64();
+    wave_fence();
     if (lane < np) {
       const PV<double> v = pvec(io.pos4, list[a0 + lane], xi, Hc);
       const double d = sqrt_(v.d2), inv = 1.0 / d;
@@ -145,7 +138,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void k_atom64(TrainIOT<double> io,
       uS[lane * 4 + 3] = inv;
       cS[lane] = (double)v.zj;
     }
-    lds_order64();
+    wave_fence();
     for (int it = lane; it < np * NA; it += 64) {
       const int j = it / NA, nn = it % NA;
       const double* cl = params + S::PCR + ((Zi * T + (int)cS[j]) * NA + nn) * BA;
@@ -158,7 +151,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void k_atom64(TrainIOT<double> io,
       gS[j * GW + nn] = g;
       dS[j * GW + nn] = gp;
     }
-    lds_order64();
+    wave_fence();
   };
   auto chunk_len = [&](int a0) { return nA - a0 < PC ? nA - a0 : PC; };
   const int lm = lane % K, ll = lm < 3 ? 1 : (lm < 8 ? 2 : (lm < 15 ? 3 : 4));
@@ -180,7 +173,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void k_atom64(TrainIOT<double> io,
 #pragma unroll
   for (int r = 0; r < R; ++r)
     if (own) m.S_[(n0 + r) * K + lm] = Sv[r];
-  lds_order64();
+  wave_fence();
 
   // ---- descriptors (A and A^2 of the 4-body terms stay with their function's lane)
   double A2[6];
@@ -201,7 +194,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void k_atom64(TrainIOT<double> io,
       m.q[S::OFF4 + lane] = sym_dot(A2, A);
     }
   }
-  lds_order64();
+  wave_fence();
 
   // ---- network: a hidden unit, then a descriptor, per lane
   const int h = lane < H ? lane : H - 1;
@@ -213,14 +206,14 @@ __global__ __launch_bounds__(64 * kAtomWaves) void k_atom64(TrainIOT<double> io,
   m.z[lane] = w1h * (1.0 - t * t);
   if (lane == 0 && io.Ei) io.Ei[io.orig[p]] = E;
   const double q1 = m.q[NR + (lane < NA ? lane : 0)];  // sum of squares of l = 1
-  lds_order64();
+  wave_fence();
   const int d0 = lane < D ? lane : D - 1;
   double Fp = 0.0;
 #pragma unroll 8
   for (int x = 0; x < H; ++x) Fp = fma(m.z[x], W0s[x * WW + d0], Fp);
-  lds_order64();
+  wave_fence();
   m.q[lane] = Fp;
-  lds_order64();
+  wave_fence();
   if (lane < T * BR) {
     const int b = lane / BR, kk = lane % BR;
     double acc = 0.0;
@@ -243,7 +236,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void k_atom64(TrainIOT<double> io,
     // of l = 1, with the 5-body part
     m.z[lane] = 2.0 * m.q[NR + lane] + (S::F5 ? 4.0 * m.q[S::F5 ? S::OFF5 + lane : 0] * q1 : 0.0);
   }
-  lds_order64();
+  wave_fence();
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int nn = n0 + r;
@@ -259,7 +252,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void k_atom64(TrainIOT<double> io,
   for (int a0 = 0; a0 < nA; a0 += PC) {
     const int np = chunk_len(a0);
     if (nA > PC) chunk(a0, np);
-    lds_order64();
+    wave_fence();
     const int j = lane % PC, f0 = lane / PC * NH;
     double fx = 0.0, fy = 0.0, fz = 0.0;
     if (j < np) {
@@ -316,7 +309,7 @@ __global__ __launch_bounds__(64) void k_pair64(TrainIOT<double> io, CutoffsT<dou
   double Hc[9];
   load_cell9(io.cfgs, c, Hc);
   const double rcR_inv = 1.0 / cut.rcR;
-  lds_order64();
+  wave_fence();
   double acc[12];  // force, virial
 #pragma unroll
   for (int x = 0; x < 12; ++x) acc[x] = 0.0;
@@ -329,7 +322,7 @@ __global__ __launch_bounds__(64) void k_pair64(TrainIOT<double> io, CutoffsT<dou
     const uint32_t rv = valid ? vrev[gk] : 0xFFFFFFFFu;
     const PV<double> v = pvec(io.pos4, io.nbrR[gk], xi, Hc);
     const uint64_t mp = __ballot(rv != 0xFFFFFFFFu);
-    const int ka = ka0 + rank64(mp);
+    const int ka = ka0 + lanes_below(mp);
     ka0 += __builtin_popcountll(mp);
     double f[3] = {0.0, 0.0, 0.0};  // dE_i/dr_ij
     if (valid && v.d2 < cut.rcR2) {

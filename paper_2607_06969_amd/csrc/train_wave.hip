@@ -9,21 +9,14 @@
 // the lanes hold over all atoms of their wavefront: lane h the row h of the
 // first layer, and so on.  Nothing per atom goes through memory.
 //
-// A wavefront's atoms are of one species.  A wavefront takes at most 12
-// atoms (48 in float64), whose shares are summed in its arithmetic; the block's
+// A wavefront's atoms are of one species: some 12 at the largest batches (48 in
+// float64), up to 16 (80) of a species whose share of the blocks is rounded down to
+// one.  Their shares are summed in the wavefront's arithmetic; the block's
 // wavefronts are then added in float64, in order, and the blocks by
 // k_train_final, in order: the order depends on the batch only.
 #include "train_device.hpp"
 
 namespace nepmi {
-
-__device__ __forceinline__ void lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-__device__ __forceinline__ int ballot_rank(uint64_t m) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
 
 constexpr int kTWaves = 4;  // wavefronts per block
 
@@ -42,24 +35,6 @@ struct GradEntries {
   static constexpr int W0 = 0, CR = W0 + S::H * S::D, CA = CR + S::NR * S::T * S::BR, B0 = CA + S::T * S::NA * S::BA,
                        W1 = B0 + S::H, B1 = W1 + S::H, N = B1 + 1;
 };
-
-// A row of N coefficients (N a multiple of 4, rows 16-byte aligned).
-template <int N>
-__device__ __forceinline__ void load_coef(const float* __restrict__ src, float (&c)[N]) {
-#pragma unroll
-  for (int k = 0; k < N / 4; ++k) {
-    const float4 v = reinterpret_cast<const float4*>(src)[k];
-    c[4 * k] = v.x;
-    c[4 * k + 1] = v.y;
-    c[4 * k + 2] = v.z;
-    c[4 * k + 3] = v.w;
-  }
-}
-template <int N>
-__device__ __forceinline__ void load_coef(const double* __restrict__ src, double (&c)[N]) {
-#pragma unroll
-  for (int k = 0; k < N; ++k) c[k] = src[k];
-}
 
 // Bound by the latency of its phases at two wavefronts per SIMD (255 registers,
 // 11.5 KB of LDS each; the vector units are busy 40 % of the time), some 2,300
@@ -193,7 +168,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
 
     // geometry and harmonics of pairs a0 .. a0 + np - 1 of the round, one per lane
     auto chunk = [&](int a0, int np) {
-      lds_order();
+      wave_fence();
       if (lane < np) {
         const R* row = m.angr + (a0 + lane) * AW;
         const R rx = row[0], ry = row[1], rz = row[2], tx = row[3], ty = row[4], tz = row[5];
@@ -225,7 +200,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
         uS[lane] = ut;
         zS[lane] = row[6];
       }
-      lds_order();
+      wave_fence();
     };
     // the list in rounds of 64 entries: the angular pairs of each round go to
     // m.angr; radial(in, v, ut): the radial pairs; angular(np): a chunk of
@@ -248,9 +223,9 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
         const R tz = lj.z - li.z + mu[6] * v.rx + mu[7] * v.ry + mu[8] * v.rz;
         const bool inR = k < n && v.d2 < cut.rcR2, inA = inR && v.d2 < cut.rcA2;
         const uint64_t mA = __ballot(inA);
-        lds_order();
+        wave_fence();
         if (inA) {
-          R* row = m.angr + ballot_rank(mA) * AW;
+          R* row = m.angr + lanes_below(mA) * AW;
           row[0] = v.rx;
           row[1] = v.ry;
           row[2] = v.rz;
@@ -279,7 +254,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
           for (int b = 0; b < T; ++b) {
             const uint64_t mR = __ballot(in && (T == 1 || v.zj == b));
-            if (T == 1 || v.zj == b) kr = nr + ballot_rank(mR);
+            if (T == 1 || v.zj == b) kr = nr + lanes_below(mR);
             const int nb = __builtin_popcountll(mR);
             if (lane / BR == b) {
               j0 = nr;
@@ -294,7 +269,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
             cheb_basis_d<BR>(d, rcR_inv, Q, dQ);
           }
           for (int r0 = 0; r0 < nr; r0 += RR) {
-            lds_order();
+            wave_fence();
             if (in && kr >= r0 && kr < r0 + RR) {
               R* row = m.buf + (kr - r0) * RW;
 #pragma unroll
@@ -303,7 +278,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
                 row[BR + k] = dQ[k] * ut;
               }
             }
-            lds_order();
+            wave_fence();
             const R* q = m.buf - r0 * RW + lane % BR;
             const int i1 = j1 < r0 + RR ? j1 : r0 + RR;
 #pragma unroll 4
@@ -319,7 +294,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
             const R* cl = cA + ((int)zS[i] * NA + nn) * BA;
             const R* q = qS + i * QW;
             R g = R(0), gp = R(0), ck[BA];
-            load_coef<BA>(cl, ck);
+            load_row<BA>(cl, ck);
 #pragma unroll
             for (int k = 0; k < BA; ++k) {
               g = fma_(ck[k], q[k], g);
@@ -328,7 +303,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
             gS[i * GW + nn] = g;
             dS[i * GW + nn] = gp * uS[i];
           }
-          lds_order();
+          wave_fence();
 #pragma unroll 2
           for (int i = 0; i < np; ++i) {
             const R y = yS[i * YW + lm], yl = lS[i * YW + lm];
@@ -340,7 +315,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
             }
           }
         });
-    lds_order();
+    wave_fence();
     if (lane < T * BR) {
       m.P[lane] = P;
       m.Pd[lane] = Pd;
@@ -351,7 +326,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
         m.S_[(n0 + r) * K + lm] = Sa[r];
         m.Sd[(n0 + r) * K + lm] = Sb[r];
       }
-    lds_order();
+    wave_fence();
     ahead_entry(nxt, pn);
     // ---- descriptors and their derivatives along t
     if (lane < NR) {
@@ -359,7 +334,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
       for (int b = 0; b < T; ++b) {
         R ck[BR];
-        load_coef<BR>(cR + (b * NR + lane) * BR, ck);
+        load_row<BR>(cR + (b * NR + lane) * BR, ck);
 #pragma unroll
         for (int k = 0; k < BR; ++k) {
           a = fma_(ck[k], m.P[b * BR + k], a);
@@ -396,7 +371,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
         m.qd[S::OFF4 + lane] = R(3.0) * sym_dot(A2, Ad);
       }
     }
-    lds_order();
+    wave_fence();
     // ---- network: hidden unit `lane`, then descriptor `lane`
     {
       const R* row = W0s + (lane < H ? lane : H - 1) * WD;
@@ -422,7 +397,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
         if (d % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // keeps the reads near their use
       }
     }
-    lds_order();
+    wave_fence();
     {
       const R* col = W0s + (lane < D ? lane : D - 1);
       R qb = R(0), Fp = R(0);
@@ -434,7 +409,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
       m.qb[lane] = qb;
       m.Fp[lane] = Fp;
     }
-    lds_order();
+    wave_fence();
     ahead_pos(nxt, pn);
     // c^R: qbar_R (x) P - dE/dq_R (x) P'
 #pragma unroll
@@ -468,7 +443,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
           m.g4b[lane * 5 + x] = gq[x];
         }
       }
-      lds_order();
+      wave_fence();
     }
     for (int a = lane; a < NA * K; a += 64) {
       const int nn = a / K, lm = a % K;
@@ -494,7 +469,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
       m.S_[a] = sg;
       m.Sd[a] = sb;
     }
-    lds_order();
+    wave_fence();
     // ---- angular coefficients: (alpha + gamma) Q_k + beta dQ_k, with alpha =
     //      sum_lm Sbar Y, beta = -(u.t) sum_lm sigma Y, gamma = -sum_lm sigma grad Y.t
     auto coef = [&](int np) {
@@ -513,7 +488,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
         gS[i * GW + nn] = al - ga;
         dS[i * GW + nn] = -uS[i] * sy;
       }
-      lds_order();
+      wave_fence();
 #pragma unroll 2
       for (int i = 0; i < np; ++i) {
         const int zj = __builtin_amdgcn_readfirstlane((int)zS[i]);
@@ -530,7 +505,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
             for (int r = 0; r < NG; ++r) gA[b][r] += v[r];
       }
-      lds_order();
+      wave_fence();
     };
     // the pairs are still in LDS if one round and one chunk held them all
     if (n <= 64 && n_ang <= PC) {
@@ -538,7 +513,7 @@ __global__ __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2)
     } else {
       walk([](bool, const PV<R>&, R) {}, coef);
     }
-    lds_order();
+    wave_fence();
   }
 
   // ---- the block's wavefronts, in order, in float64: each puts its sums in LDS,
