@@ -23,11 +23,12 @@ enum {
 };
 
 // Whether the lists are void: the call that built them is going to build them
-// again or to end in an error.  Kernels launched on lists whose flags the host
-// has not read yet look first (`stop`: the flags, or the words at kFlagNone where
-// the lists are known to be good), so that such a call leaves its outputs as they
-// were.  They load the flags beside their first loads (behind a branch of its own
-// the load cost each kernel some 0.2 us).
+// again or to end in an error.  Of the work launched on lists whose flags the host
+// has not read yet, the descriptor kernel then leaves every atom without pairs, and
+// the kernels behind it run on that but write no output, so that such a call leaves
+// its outputs as they were (`stop`: the flags, or the words at kFlagNone where the
+// lists are known to be good).  All but the descriptor kernel look at what they
+// loaded only where they write (a wait for it up front cost each some 0.2 us).
 __device__ __forceinline__ bool lists_void(const int* stop) {
   const int4 f = *reinterpret_cast<const int4*>(stop);
   return (f.x | f.y | f.z | f.w) != 0;

@@ -616,7 +616,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
   const float4 xi = pos4[p];
   const int Zs = __builtin_amdgcn_readfirstlane(__float_as_int(xi.w));
   const int c = cfg_of[p];
-  if (c < 0 || none) return;
+  if (c < 0) return;
   float Hc[9];
   load_cell(cfgs, c, Hc);
   const float rcR_inv = 1.0f / cut.rcR, rcA_inv = 1.0f / cut.rcA;
@@ -813,6 +813,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     });
   }
   frad[p] = make_float4(Fx, Fy, Fz, 0.f);
+  if (none) return;
   const int i = orig[p];
   float* w = Wi + (int64_t)i * 9;
 #pragma unroll
@@ -891,7 +892,6 @@ __global__ __launch_bounds__(BS) void k_gather(int64_t n_slots, const int* __res
   }
   if (p >= n_slots) return;
   const int i = orig[p];
-  if (none) return;
   if (i < 0) {
     if (Fproc) Fproc[p] = make_float4(0.f, 0.f, 0.f, 0.f);
     return;
@@ -945,7 +945,7 @@ __global__ __launch_bounds__(BS) void k_gather(int64_t n_slots, const int* __res
       step(sc, sa, sb, g + 2);
     }
   }
-  if (Fuser) {
+  if (Fuser && !none) {
     Fuser[(int64_t)i * 3 + 0] = F.x;
     Fuser[(int64_t)i * 3 + 1] = F.y;
     Fuser[(int64_t)i * 3 + 2] = F.z;

@@ -142,11 +142,10 @@ struct GroupAtom {
   bool act;      // the slot holds an atom
 };
 template <int W>
-__device__ __forceinline__ bool group_atom(const NepIO& io, int64_t p0, GroupAtom<W>& a) {
+__device__ __forceinline__ bool group_atom(const NepIO& io, int64_t p0, bool none, GroupAtom<W>& a) {
   a.g = W == kWave ? 0 : (int)threadIdx.x / W;
   a.l = W == kWave ? (int)threadIdx.x : (int)threadIdx.x % W;
   a.p = p0 + a.g;
-  const bool none = lists_void(io.stop);
   a.act = a.p < io.n_slots && io.cfg_of[a.p < io.n_slots ? a.p : io.n_slots - 1] >= 0 && !none;
   const uint64_t m = __ballot(a.act);
   if (!m) return false;
@@ -190,7 +189,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     return;
   }
   GroupAtom<W> at;
-  if (!group_atom(io, p0, at)) {
+  if (!group_atom(io, p0, lists_void(io.stop), at)) {
     if (at.l == 0 && at.p < ns) io.ccR[at.p] = io.ccA[at.p] = 0;
     return;
   }
@@ -499,7 +498,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
 
   const int64_t ns = io.n_slots;
   GroupAtom<W> at;
-  if (!group_atom(io, xcd_tile() * G, at)) return;
+  const bool none = lists_void(io.stop);
+  if (!group_atom(io, xcd_tile() * G, false, at)) return;
   const int64_t p = at.pa;
   const int l = at.l;
   Atom& A = atoms[at.g];
@@ -763,7 +763,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
   float* fr = reinterpret_cast<float*>(io.frad + p);
   if (l < 3) fr[l] = acc;
   if (l == 12) fr[3] = 0.f;
-  if (l >= 3 && l < 12) io.Wi[(int64_t)io.orig[p] * 9 + l - 3] = acc;
+  if (l >= 3 && l < 12 && !none) io.Wi[(int64_t)io.orig[p] * 9 + l - 3] = acc;
 }
 
 // Lanes per atom: half a wavefront if it holds the angular pairs of nearly every

@@ -77,7 +77,8 @@ struct Reducer {
 // of BS threads; the block that ends a configuration's last item sums its
 // items.  Both sums have the shape of a block of kRedThreads threads, whatever
 // BS: a thread's atoms in order, a butterfly over the 64 lanes of each
-// wavefront, then the wavefronts in order.
+// wavefront, then the wavefronts in order.  none: all of it but the outputs (see
+// lists_void).
 constexpr int kRedThreads = 256;
 struct SumShared {
   double wave[kRedThreads / 64][kRedValues];
@@ -114,7 +115,6 @@ template <int BS, class T>
 __device__ __forceinline__ void sum_item(int item, const SumArgs<T>& a, SumShared& sh, bool none = false) {
   constexpr int NV = kRedValues;
   const RedItem it = a.items[item];
-  if (none) return;  // all items of a launch or no item
   double s = block_sum<BS>(
       [&](int t, double(&acc)[NV]) {
         for (int64_t i = it.a0 + t; i < it.a1; i += kRedThreads) {
@@ -155,6 +155,7 @@ __device__ __forceinline__ void sum_item(int item, const SumArgs<T>& a, SumShare
         sh);
     if (v == 0) __hip_atomic_store(&a.done[it.cfg], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  if (none) return;
   if (v == 0 && a.E) a.E[it.cfg] = s;
   if (v >= 1 && v <= 9 && a.V) a.V[(int64_t)it.cfg * 9 + v - 1] = s;
   if (v == 10 && a.K) a.K[it.cfg] = s;

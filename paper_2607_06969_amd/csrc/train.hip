@@ -37,7 +37,6 @@ __global__ __launch_bounds__(kTB) void k_loss(TrainSeedArgs a) {
   __shared__ int last;
   const bool none = lists_void(a.stop);
   const RedItem it = a.items[blockIdx.x];
-  if (none) return;
   const double B = (double)a.n_cfg;
   {
     const double Nc = (double)(a.off[it.cfg + 1] - a.off[it.cfg]);
@@ -96,12 +95,12 @@ __global__ __launch_bounds__(kTB) void k_loss(TrainSeedArgs a) {
       for (int x = 0; x < 3; ++x) sh[x][threadIdx.x] += sh[x][threadIdx.x + st];
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == 0) __hip_atomic_store(a.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0 && !none) {
     a.loss[0] = sh[0][0] + sh[1][0] + sh[2][0];
     a.loss[1] = sh[0][0];
     a.loss[2] = sh[1][0];
     a.loss[3] = sh[2][0];
-    __hip_atomic_store(a.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
