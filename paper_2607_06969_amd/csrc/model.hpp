@@ -60,8 +60,8 @@ struct EvalWork {
 // Neighbour lists (pairs within the cutoffs + skin), work buffers and
 // reduction plan of a batch in `w`: launched by prepare_start; prepare_end
 // waits for the lists' flags and reports what is wrong with the input.  Work
-// on the lists can be launched between the two: it stays within its buffers
-// whatever the flags say, and has to be launched again if prepare_end says so
+// on the lists can be launched between the two: it does nothing on lists that are
+// void (see lists_void), and has to be launched again if prepare_end says so
 // (the lists were too short and have been rebuilt).  With `post`, that work
 // has to deliver the flags: its first kernel gets them (NepIO::mail).
 int prepare_start(EvalWork& w, const Ops* ops, const nepmi_hparams& hp, int n_cfg, const int64_t* atom_off,

@@ -269,8 +269,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     // with a reverse position) is in the compact angular list
     uint64_t mword = 0;
     int ka = 0;  // position in the angular part of the list
-    // words the mask holds (a list cut off at its capacity, which is rebuilt
-    // before its results are used, may have more angular entries)
+    // words the mask holds (a list cut off at its capacity, as MD may step with
+    // until its chunk of steps is undone, may have more angular entries)
     const int kaMax = (capA + 63) / 64 * 64;
     walk_groups<true>(reinterpret_cast<const uint4*>(nbrR), n_slots, p, n, pos4, NoPre{},
                       [&](int, uint32_t e, float4 xq, uint32_t rvk, int) {

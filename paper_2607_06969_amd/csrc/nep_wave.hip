@@ -210,8 +210,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
   load_cell(io.cfgs, io.cfg_of[p], Hc);
   const float rcR_inv = 1.0f / io.cut.rcR, rcA_inv = 1.0f / io.cut.rcA;
   const int n = at.act ? io.cntR[p] : 0;
-  // entries the mask's words hold (a list cut off at its capacity, which is
-  // rebuilt before its results are used, may have more)
+  // entries the mask's words hold (a list cut off at its capacity, as MD may step
+  // with until its chunk of steps is undone, may have more)
   const int kaMax = (io.capA + 63) / 64 * 64;
   wave_fence();
 
